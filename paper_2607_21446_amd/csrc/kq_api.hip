@@ -366,7 +366,7 @@ kq_status kq_mxfp4_gemm_bf16(const uint8_t* a_codes, const uint8_t* a_scales, in
     if (st != KQ_SUCCESS || M == 0 || N == 0) return st;
     kq::GemmParams g = gemm_params(a_codes, a_scales, M, b_codes, b_scales, N, K, nullptr, ldc, 0, nullptr);
     g.C16 = C;
-    g.vec_ok = aligned(C, 8) && ldc % 4 == 0;
+    g.vec_ok = aligned(C, 16) && ldc % 8 == 0;
     return from_hip(kq::launch_mxfp4_gemm(g, (hipStream_t)stream), "kq_mxfp4_gemm_bf16");
 }
 

@@ -13,14 +13,13 @@
 // values times the two scales are exact in fp32; the sum over K is
 // accumulated in fp32 (order not specified).
 //
-// Tiling: a 256-thread workgroup owns a 128 x 128 tile of C; its four waves
-// own 64 x 64 quadrants, 2 x 2 instruction tiles of 32 x 32 each (four fp32
-// accumulators).  Fragments are loaded straight from global memory (the
-// workgroup's two waves per row/column quadrant share them through L1/L2),
-// with the next K step's fragments in flight while the current step's four
-// instructions run.
+// Kernels: the pipelined kernel below on a 256 x 256 (eight waves) or 128 x 128
+// (four waves) tile of C, for any K up to 2^24; a plain direct-load kernel for
+// longer rows, whose tile offsets pass 32 bits.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+
+#include <type_traits>
 
 #include "kq_kernels.h"
 
@@ -56,23 +55,8 @@ __device__ __forceinline__ i32x8 operand(const Frag& f) {
     return v;
 }
 
-// Four consecutive C values of row m from column n: fp32 (with the bias or
-// the accumulate mode), or rounded to bf16 (nearest even) when C16 is set.
+// Four consecutive fp32 C values of row m from column n, with the bias or the accumulate mode.
 __device__ __forceinline__ void store_c4(const GemmParams& g, int64_t m, int64_t n, float4 v) {
-    if (g.C16) {
-        uint16_t* crow = g.C16 + m * g.ldc_out;
-        const float f[4] = {v.x, v.y, v.z, v.w};
-        if (g.vec_ok && n + 3 < g.N) {
-            typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
-            const bf16x4 b = {(__bf16)v.x, (__bf16)v.y, (__bf16)v.z, (__bf16)v.w};
-            *reinterpret_cast<uint2*>(crow + n) = __builtin_bit_cast(uint2, b);
-        } else {
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-                if (n + e < g.N) crow[n + e] = __builtin_bit_cast(uint16_t, (__bf16)f[e]);
-        }
-        return;
-    }
     float* crow = g.C + m * g.ldc_out;
     const float* brow = g.bias ? g.bias + m * g.ldc_out : g.accumulate ? crow : nullptr;
     if (g.vec_ok && n + 3 < g.N) {
@@ -91,6 +75,9 @@ __device__ __forceinline__ void store_c4(const GemmParams& g, int64_t m, int64_t
 
 }  // namespace
 
+// K above kPipeMaxK: a 256-thread workgroup owns a 128 x 128 tile of C, its four
+// waves 64 x 64 quadrants; fragments straight from global memory, the next K
+// step's in flight while the current step's four instructions run.
 __global__ __launch_bounds__(256) void mxfp4_gemm_kernel(const GemmParams g) {
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int r = lane & 31, h = lane >> 5;
@@ -154,37 +141,33 @@ __global__ __launch_bounds__(256) void mxfp4_gemm_kernel(const GemmParams g) {
         }
 }
 
-// K advances 128 (four 32-blocks) per pipeline stage in the LDS-pipelined kernels below.
-constexpr int kGemmTileK = 128;
+// ------------------------------------------------------------------ pipelined kernels
+// K advances 128 (four 32-blocks) per stage.  Codes and scales go from global
+// memory straight into LDS (global_load_lds: lane l's 16 bytes land at the
+// wave-uniform LDS address + 16 l), three stages ahead, so there is no register
+// staging and no ds_write.
+constexpr int kStages = 4;  // LDS stage buffers: one in use, three in flight
 
-// Pipelined variant (K a multiple of 128, 4-byte-aligned scales): workgroup
-// tile 128 (N) x 128 (M), waves 2 x 2 of 64 x 64, K 128 per stage.  Codes and
-// scales go from global memory straight into LDS (global_load_lds: lane l's
-// 16 or 4 bytes land at the wave-uniform LDS address + 16 l or 4 l) with
-// kGemmStages stages in flight, so no register staging and no ds_write.
-// Per stage the workgroup issues 20 such loads, 5 per wave:
-//   W and X codes of rows 32 w .. 32 w + 31 (two loads each, 16 rows x 64 B), and
-//   one scale group: wave 0 W rows 0-63, 1 W rows 64-127, 2 X rows 0-63, 3 X rows 64-127;
-// rows past N or M load row N-1 or M-1 (their products land in C rows or
-// columns that are never stored).  Before a stage is used each wave waits
-// until only its later stages' loads are outstanding, then one barrier.
-constexpr int kGemmStages = 3;
-constexpr int kPipeLoadsPerWave = 5;
-
-struct PipeBuf {
-    uint4 wc[4 * 128];   // 128 rows x 4 blocks of 16 B, slot pipe_slot(row, block)
-    uint4 xc[4 * 128];
-    uint32_t ws[128];    // scales of the stage's 4 blocks, one dword per row
-    uint32_t xs[128];
-};
-
-__device__ __forceinline__ void lds_load16(const uint8_t* src, void* lds_base) {
-    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src,
-                                     (__attribute__((address_space(3))) void*)lds_base, 16, 0, 0);
+// One such load, as asm: the compiler puts a vmcnt(0) before LDS reads that may
+// alias a load into LDS it knows of, which would drain the stages in flight.
+// The waits are explicit here (wait_stage), the load has no register result,
+// and nothing else in these kernels uses m0.
+__device__ __forceinline__ void lds_dma16(uint32_t lds, uint32_t voff, const uint8_t* base) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(voff), "s"(base)
+                 : "memory");
 }
-__device__ __forceinline__ void lds_load4(const uint8_t* src, void* lds_base) {
-    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src,
-                                     (__attribute__((address_space(3))) void*)lds_base, 4, 0, 0);
+
+__device__ __forceinline__ void stage_barrier() {
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("s_barrier" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+}
+
+// Until at most 4 * later code loads of this wave are outstanding.
+__device__ __forceinline__ void wait_stage(int later) {
+    if (later >= 2) asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
+    else if (later == 1) asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
+    else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 }
 
 // LDS slot of block b of tile row q: 4 q + (b ^ ((q >> 2) & 3)).  A DMA
@@ -194,237 +177,306 @@ __device__ __forceinline__ void lds_load4(const uint8_t* src, void* lds_base) {
 // block) spreads over all LDS banks.
 __device__ __forceinline__ int pipe_slot(int q, int b) { return 4 * q + (b ^ ((q >> 2) & 3)); }
 
-__device__ __forceinline__ void pipe_issue(const GemmParams& g, PipeBuf& b, int wave, int lane, int64_t nb0,
-                                           int64_t mb0, int64_t row_bytes, int64_t nkb, int64_t st) {
-    const int q = lane >> 2;                                  // row within the instruction's 16
-    const int blk = (lane & 3) ^ ((q >> 2) & 3);
-    const int64_t kbyte = (4 * st + blk) * 16;
-#pragma unroll
-    for (int gr = 0; gr < 2; ++gr) {
-        const int row = 16 * (2 * wave + gr) + q;             // this wave fills rows 32 w .. 32 w + 31
-        const int64_t n = min(nb0 + row, g.N - 1);
-        const int64_t m = min(mb0 + row, g.M - 1);
-        lds_load16(g.b_codes + n * row_bytes + kbyte, &b.wc[64 * (2 * wave + gr)]);
-        lds_load16(g.a_codes + m * row_bytes + kbyte, &b.xc[64 * (2 * wave + gr)]);
-    }
-    const int gr = wave & 1;
-    if (wave < 2) {
-        const int64_t n = min(nb0 + 64 * gr + lane, g.N - 1);
-        lds_load4(g.b_scales + n * nkb + 4 * st, &b.ws[64 * gr]);
-    } else {
-        const int64_t m = min(mb0 + 64 * gr + lane, g.M - 1);
-        lds_load4(g.a_scales + m * nkb + 4 * st, &b.xs[64 * gr]);
-    }
-}
-
-template <int STEP>
-__device__ __forceinline__ void pipe_step(const PipeBuf& b, int h, int wn, int wm, int r, const uint32_t (&scw)[2],
-                                          const uint32_t (&scx)[2], f32x16g (&acc)[2][2]) {
-    uint4 fw[2], fx[2];
-#pragma unroll
-    for (int i = 0; i < 2; ++i) fw[i] = b.wc[pipe_slot(wn * 64 + 32 * i + r, 2 * STEP + h)];
-#pragma unroll
-    for (int j = 0; j < 2; ++j) fx[j] = b.xc[pipe_slot(wm * 64 + 32 * j + r, 2 * STEP + h)];
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-            acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(
-                operand(Frag{fw[i], 0u}), operand(Frag{fx[j], 0u}), acc[i][j], 4, 4, STEP, (int)scw[i], STEP, (int)scx[j]);
-}
-
-// The three stage buffers are distinct LDS objects, and the main loop is
-// unrolled by three so that every access names its buffer at compile time:
-// the waits the compiler adds before LDS reads then cover only loads into
-// that buffer, and the barrier between stages is a bare s_barrier after an
-// explicit vmcnt wait (a fenced barrier would drain the loads in flight for
-// the later stages).
-__shared__ PipeBuf g_pipe0, g_pipe1, g_pipe2;
-
-template <int B>
-__device__ __forceinline__ PipeBuf& pipe_buf() {
-    if constexpr (B == 0) return g_pipe0;
-    else if constexpr (B == 1) return g_pipe1;
-    else return g_pipe2;
-}
-
-struct PipeCtx {
-    int wave, lane, r, h, wn, wm;
-    int64_t nb0, mb0, nkb, row_bytes, nst;
-    uint32_t psel;
+// Workgroup tile of BN (N) x BM (M): WN x WM waves of TN x TM instruction tiles
+// of 32 x 32.  Every wave issues four code loads (16 rows x 64 bytes each) per
+// stage and one scale load (64 rows x 16 bytes) per four stages.
+template <int WN, int WM, int TN, int TM>
+struct Tile {
+    static constexpr int BN = 32 * WN * TN, BM = 32 * WM * TM, ROWS = BN + BM, WAVES = WN * WM;
+    static_assert(ROWS == 64 * WAVES, "four code loads and one scale load per wave");
+    // rows 0 .. BN-1 are W rows, BN .. ROWS-1 X rows, in every array
+    struct Lds {
+        uint4 codes[kStages][4 * ROWS];  // slot pipe_slot(row, block of the stage)
+        uint4 scales[2][ROWS];           // [chunk parity][row]: the 16 scales of four stages
+    };
 };
 
-// stage st lives in buffer CUR = st % 3; stage st + 2 is issued into NXT = (st + 2) % 3
-template <int CUR, int NXT>
-__device__ __forceinline__ void pipe_iter(const GemmParams& g, const PipeCtx& c, int64_t st, f32x16g (&acc)[2][2]) {
-    if (st + 1 < c.nst)
-        __builtin_amdgcn_s_waitcnt((kPipeLoadsPerWave & 15) | (7 << 4) | (15 << 8));  // vmcnt(5)
-    else
-        __builtin_amdgcn_s_waitcnt((7 << 4) | (15 << 8));  // vmcnt(0)
-    __builtin_amdgcn_s_barrier();
-    if (st + 2 < c.nst) pipe_issue(g, pipe_buf<NXT>(), c.wave, c.lane, c.nb0, c.mb0, c.row_bytes, c.nkb, st + 2);
-    const PipeBuf& b = pipe_buf<CUR>();
-    uint32_t scw[2], scx[2];
+// The 16 (or the last nvalid) scale bytes at p, any alignment.
+__device__ __forceinline__ uint4 load_scales16(const uint8_t* p, int nvalid) {
+    typedef uint32_t u32x4u __attribute__((ext_vector_type(4), aligned(1)));
+    if (nvalid >= 16) {
+        const u32x4u v = *reinterpret_cast<const u32x4u*>(p);
+        return make_uint4(v.x, v.y, v.z, v.w);
+    }
+    uint32_t w[4] = {0u, 0u, 0u, 0u};
 #pragma unroll
-    for (int i = 0; i < 2; ++i) scw[i] = __builtin_amdgcn_perm(0u, b.ws[c.wn * 64 + 32 * i + c.r], c.psel);
-#pragma unroll
-    for (int j = 0; j < 2; ++j) scx[j] = __builtin_amdgcn_perm(0u, b.xs[c.wm * 64 + 32 * j + c.r], c.psel);
-    pipe_step<0>(b, c.h, c.wn, c.wm, c.r, scw, scx, acc);
-    pipe_step<1>(b, c.h, c.wn, c.wm, c.r, scw, scx, acc);
+    for (int i = 0; i < 16; ++i)
+        if (i < nvalid) w[i / 4] |= (uint32_t)p[i] << (8 * (i % 4));
+    return make_uint4(w[0], w[1], w[2], w[3]);
 }
 
-__global__ __launch_bounds__(256) void mxfp4_gemm_pipe_kernel(const GemmParams g) {
-    PipeCtx c;
+// C tile [nb0, nb0 + BN) x [mb0, mb0 + BM).  Rows past N or M read row N-1 or
+// M-1 (their products land in C rows or columns that are never stored).
+//
+// PING (eight waves, two per SIMD): waves 4-7 run half a stage behind waves
+// 0-3, held apart by one extra barrier at the start, so that on every SIMD one
+// wave reads its fragments from LDS and issues loads while the other runs its
+// matrix-core instructions; with both in step the LDS reads (about 770 cycles a
+// stage at 128 bytes a cycle) and the matrix cores (1024 cycles) add up.
+// In phase 2k waves 0-3 read stage k and issue stage k + 3, and compute it in
+// phase 2k + 1; waves 4-7 do so in phases 2k + 1 and 2k + 2.  Stage k + 3
+// overwrites the buffer of stage k - 1, last read in phase 2k - 1, whose reads
+// have returned before that phase's barrier.  Every wave has waited for its
+// loads of stage k before the barrier that ends phase 2k - 1.
+//
+// Per stage (K 12288 less K 3072, 216 tiles, C stores left out): 0.91 us, of which
+// 0.59 is what the matrix cores take at the clock they hold; 0.75 without the
+// loads, 0.69 without the matrix instructions.  Both groups in step, with three
+// buffers: 1.15 us.
+//
+// DMA_SCALES: a scale row has a multiple of 4 bytes, at least 16, and starts
+// at a multiple of 4: the 16 scales of four stages come by a DMA load per row.
+// The last such load of the last row would pass the end of the array, so it
+// ends there instead and is read at an offset.  Otherwise each thread loads
+// its row's 16 bytes into registers (byte-exact) and parks them in LDS two
+// stages later.
+template <int WN, int WM, int TN, int TM, bool PING, bool DMA_SCALES>
+__device__ __forceinline__ void gemm_tile(const GemmParams& g, typename Tile<WN, WM, TN, TM>::Lds& lds, int64_t nb0,
+                                          int64_t mb0, f32x16g (&acc)[TN][TM]) {
+    typedef Tile<WN, WM, TN, TM> T;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int r = lane & 31, h = lane >> 5, wn = wave / WM, wm = wave % WM;
+    const int64_t row_bytes = g.K / 2, nkb = g.K / 32;
+    const int nst = (int)((nkb + 3) / 4), tb = (int)(nkb & 3);  // tb: blocks of a partial last stage
+    const int nch = (int)((nkb + 15) / 16);
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)&lds;
+    constexpr uint32_t kStageBytes = 64u * T::ROWS;
+    constexpr uint32_t kScales0 = kStages * kStageBytes, kChunkBytes = 16u * T::ROWS;
+
+    // this wave's code rows 64 wave .. 64 wave + 63 (all W or all X), its scale rows the same
+    const bool isw = 64 * wave < T::BN;
+    const int rel0 = 64 * wave - (isw ? 0 : T::BN);
+    const int64_t row0 = (isw ? nb0 : mb0) + rel0, rows = isw ? g.N : g.M;
+    const int last = (int)min<int64_t>(63, max<int64_t>(0, rows - 1 - row0));  // last row of the 64 to read
+    const int64_t rowc = min(row0, rows - 1);
+    const uint8_t* const cbase = (isw ? g.b_codes : g.a_codes) + rowc * row_bytes;
+    const uint8_t* const sbase = (isw ? g.b_scales : g.a_scales) + rowc * nkb;
+    const int q = lane >> 2, blk = (lane & 3) ^ ((q >> 2) & 3);
+    uint32_t voff[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) voff[i] = (uint32_t)min(16 * i + q, last) * (uint32_t)row_bytes + 16u * blk;
+    const uint32_t soff = (uint32_t)min(lane, last) * (uint32_t)nkb;
+    const uint32_t dst0 = lds0 + 4096u * wave, sdst0 = lds0 + kScales0 + 1024u * wave;
+
+    auto issue_codes = [&](int st, int buf) {
+        const uint8_t* const base = cbase + 64 * (int64_t)st;
+        // blocks past K (a partial last stage) read its last block; they are masked below
+        const uint32_t back = (tb && st == nst - 1 && blk >= tb) ? 16u * (blk - tb + 1) : 0u;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) lds_dma16(dst0 + buf * kStageBytes + 1024u * i, voff[i] - back, base);
+    };
+    // distance by which the last chunk's load of the matrix's last row ends early
+    // (the chunk's offset is added first: a row's own offset may be smaller than it)
+    const uint32_t early = DMA_SCALES ? (uint32_t)(-nkb & 15) : 0u;
+    auto issue_scales = [&](int ch) {
+        const bool back = early && ch == nch - 1 && row0 + min(lane, last) >= rows - 1;
+        lds_dma16(sdst0 + (ch & 1) * kChunkBytes, soff + 16u * ch - (back ? early : 0u), sbase);
+    };
+    uint4 parked = make_uint4(0u, 0u, 0u, 0u);
+    auto fetch_scales = [&](int ch) {
+        parked = load_scales16(sbase + soff + 16 * (int64_t)ch, (int)min<int64_t>(16, nkb - 16 * (int64_t)ch));
+    };
+    auto park_scales = [&](int ch) { lds.scales[ch & 1][threadIdx.x] = parked; };
+
+    // fragment and scale addresses of this lane
+    const uint32_t psel = h ? 0x0c0c0301u : 0x0c0c0200u;
+    const int wrow = wn * 32 * TN + r, xrow = T::BN + wm * 32 * TM + r;
+    const uint4* const sc0 = lds.scales[0];
+    uint32_t late = 0;  // bit i (W) or 8 + j (X): this lane's row is the matrix's last
+    if (DMA_SCALES && early) {
+#pragma unroll
+        for (int i = 0; i < TN; ++i) late |= (nb0 + wrow + 32 * i >= g.N - 1 ? 1u : 0u) << i;
+#pragma unroll
+        for (int j = 0; j < TM; ++j) late |= (mb0 + xrow - T::BN + 32 * j >= g.M - 1 ? 1u : 0u) << (8 + j);
+    }
+    struct Frags {
+        uint4 w[2][TN], x[2][TM];
+        uint32_t sw[TN], sx[TM];
+    };
+    auto read_frags = [&](int st, int buf, int j4, Frags& f) {
+        const uint4* const cb = lds.codes[buf];
+        const int ch = st >> 2;
+        const uint32_t* const sp = reinterpret_cast<const uint32_t*>(sc0 + (ch & 1) * T::ROWS) + j4;
+        if (DMA_SCALES && early && ch == nch - 1) {
+            const uint32_t e = early / 4;
+#pragma unroll
+            for (int i = 0; i < TN; ++i) f.sw[i] = sp[4 * (wrow + 32 * i) + ((late >> i) & 1u) * e];
+#pragma unroll
+            for (int j = 0; j < TM; ++j) f.sx[j] = sp[4 * (xrow + 32 * j) + ((late >> (8 + j)) & 1u) * e];
+        } else {
+#pragma unroll
+            for (int i = 0; i < TN; ++i) f.sw[i] = sp[4 * (wrow + 32 * i)];
+#pragma unroll
+            for (int j = 0; j < TM; ++j) f.sx[j] = sp[4 * (xrow + 32 * j)];
+        }
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+#pragma unroll
+            for (int i = 0; i < TN; ++i) f.w[s][i] = cb[pipe_slot(wrow + 32 * i, 2 * s + h)];
+#pragma unroll
+            for (int j = 0; j < TM; ++j) f.x[s][j] = cb[pipe_slot(xrow + 32 * j, 2 * s + h)];
+        }
+    };
+    // scales to the byte order of the instruction's selectors; blocks past K: zero codes, scale 1
+    auto finish_frags = [&](int st, Frags& f) {
+#pragma unroll
+        for (int i = 0; i < TN; ++i) f.sw[i] = __builtin_amdgcn_perm(0u, f.sw[i], psel);
+#pragma unroll
+        for (int j = 0; j < TM; ++j) f.sx[j] = __builtin_amdgcn_perm(0u, f.sx[j], psel);
+        if (tb && st == nst - 1) {
+#pragma unroll
+            for (int s = 0; s < 2; ++s) {
+                const bool past = 2 * s + h >= tb;
+                const uint32_t keep = past ? 0u : ~0u;
+                const uint32_t one = past ? 127u << (8 * s) : 0u, smask = past ? ~(255u << (8 * s)) : ~0u;
+#pragma unroll
+                for (int i = 0; i < TN; ++i) {
+                    f.w[s][i] = make_uint4(f.w[s][i].x & keep, f.w[s][i].y & keep, f.w[s][i].z & keep, f.w[s][i].w & keep);
+                    f.sw[i] = (f.sw[i] & smask) | one;
+                }
+#pragma unroll
+                for (int j = 0; j < TM; ++j) {
+                    f.x[s][j] = make_uint4(f.x[s][j].x & keep, f.x[s][j].y & keep, f.x[s][j].z & keep, f.x[s][j].w & keep);
+                    f.sx[j] = (f.sx[j] & smask) | one;
+                }
+            }
+        }
+    };
+    auto products = [&](const Frags& f) {
+#pragma unroll
+        for (int i = 0; i < TN; ++i)
+#pragma unroll
+            for (int j = 0; j < TM; ++j)
+                acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(operand(Frag{f.w[0][i], 0u}),
+                                                                             operand(Frag{f.x[0][j], 0u}), acc[i][j], 4, 4,
+                                                                             0, (int)f.sw[i], 0, (int)f.sx[j]);
+#pragma unroll
+        for (int i = 0; i < TN; ++i)
+#pragma unroll
+            for (int j = 0; j < TM; ++j)
+                acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(operand(Frag{f.w[1][i], 0u}),
+                                                                             operand(Frag{f.x[1][j], 0u}), acc[i][j], 4, 4,
+                                                                             1, (int)f.sw[i], 1, (int)f.sx[j]);
+    };
+
+#pragma unroll
+    for (int i = 0; i < TN; ++i)
+#pragma unroll
+        for (int j = 0; j < TM; ++j) acc[i][j] = f32x16g{};
+    if (DMA_SCALES) issue_scales(0);
+    else fetch_scales(0);
+#pragma unroll
+    for (int s = 0; s < kStages - 1; ++s)
+        if (s < nst) issue_codes(s, s);
+    if (!DMA_SCALES) {
+        park_scales(0);
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    }
+    const bool behind = PING && wave >= T::WAVES / 2;
+
+    // stage st in buffer J = st % 4
+    auto stage = [&](int st, auto Jc) {
+        constexpr int J = decltype(Jc)::value;
+        Frags f;
+        read_frags(st, J, J, f);
+        if (DMA_SCALES) {
+            if (J == 0 && (st >> 2) + 1 < nch) issue_scales((st >> 2) + 1);
+        } else {
+            if (J == 2 && (st >> 2) + 1 < nch) park_scales((st >> 2) + 1);
+            if (J == 0 && (st >> 2) + 1 < nch) fetch_scales((st >> 2) + 1);
+        }
+        if (st + 3 < nst) issue_codes(st + 3, (J + 3) & 3);
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        finish_frags(st, f);
+        if (PING) {
+            if (behind) wait_stage(nst - 2 - st);
+            stage_barrier();
+            products(f);
+            if (!behind) wait_stage(nst - 2 - st);
+            stage_barrier();
+        } else {
+            products(f);
+            wait_stage(nst - 2 - st);
+            stage_barrier();
+        }
+    };
+    wait_stage(nst - 1);
+    stage_barrier();
+    if (behind) stage_barrier();
+    for (int st = 0; st < nst; st += 4) {
+        stage(st, std::integral_constant<int, 0>{});
+        if (st + 1 < nst) stage(st + 1, std::integral_constant<int, 1>{});
+        if (st + 2 < nst) stage(st + 2, std::integral_constant<int, 2>{});
+        if (st + 3 < nst) stage(st + 3, std::integral_constant<int, 3>{});
+    }
+    if (PING && !behind) stage_barrier();
+}
+
+// The tile's accumulators, acc[i][j][4q + e] = C[mb0 + 32 (wm TM + j) + r][nb0 +
+// 32 (wn TN + i) + 8 q + 4 h + e], to C through LDS, so that C (and the bias) is
+// accessed along its rows, 512 bytes at a time, and not in 8- or 16-byte pieces
+// of 32 rows (4608 x 12288 x 3072, bf16 / fp32: 141 / 155 us so, 119 / 137 now).  Rows in LDS are 16 bytes apart from a multiple of 512 (256), so
+// that the 16 rows of a write phase cover all banks.  When a tile of fp32 does not
+// fit, it goes in NP passes of TN / NP of every wave's column tiles.
+template <int WN, int WM, int TN, int TM, bool BF16>
+__device__ __forceinline__ void store_tile(const GemmParams& g, uint8_t* lds, int64_t nb0, int64_t mb0,
+                                           const f32x16g (&acc)[TN][TM]) {
+    typedef Tile<WN, WM, TN, TM> T;
+    constexpr int ES = BF16 ? 2 : 4;
+    constexpr int NP = (T::BM * (T::BN * ES + 16) <= (int)sizeof(typename T::Lds)) ? 1 : 2;
+    constexpr int TP = TN / NP;                    // column tiles per wave and pass
+    constexpr int RB = T::BN / NP * ES, RS = RB + 16;  // data and stride of a row in bytes
+    static_assert(T::BM * RS <= (int)sizeof(typename T::Lds), "a pass fits LDS");
+    constexpr int CPR = RB / 16, EPC = 16 / ES;    // 16-byte chunks per row, elements per chunk
     const int t = threadIdx.x;
-    c.wave = t >> 6;
-    c.lane = t & 63;
-    c.r = c.lane & 31;
-    c.h = c.lane >> 5;
-    c.wn = c.wave >> 1;
-    c.wm = c.wave & 1;
-    c.nb0 = (int64_t)blockIdx.x * 128;
-    c.mb0 = (int64_t)blockIdx.y * 128;
-    c.nkb = g.K / 32;
-    c.row_bytes = g.K / 2;
-    c.nst = g.K / 128;
-    c.psel = c.h ? 0x0c0c0301u : 0x0c0c0200u;
-    f32x16g acc[2][2];
+    const int wave = t >> 6, lane = t & 63;
+    const int r = lane & 31, h = lane >> 5, wn = wave / WM, wm = wave % WM;
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int p = 0; p < NP; ++p) {
+        if (p > 0) __syncthreads();
 #pragma unroll
-        for (int j = 0; j < 2; ++j) acc[i][j] = f32x16g{};
-    pipe_issue(g, g_pipe0, c.wave, c.lane, c.nb0, c.mb0, c.row_bytes, c.nkb, 0);
-    if (c.nst > 1) pipe_issue(g, g_pipe1, c.wave, c.lane, c.nb0, c.mb0, c.row_bytes, c.nkb, 1);
-    for (int64_t st = 0; st < c.nst; st += 3) {
-        pipe_iter<0, 2>(g, c, st, acc);
-        if (st + 1 < c.nst) pipe_iter<1, 0>(g, c, st + 1, acc);
-        if (st + 2 < c.nst) pipe_iter<2, 1>(g, c, st + 2, acc);
-    }
-    const int r = c.r, h = c.h, wn = c.wn, wm = c.wm;
-    const int64_t nb0 = c.nb0, mb0 = c.mb0;
-    // acc[i][j][4q + e] = C[mb0 + wm 64 + 32 j + r][nb0 + wn 64 + 32 i + 8 q + 4 h + e]
+        for (int i = 0; i < TP; ++i)
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
-        const int64_t m = mb0 + wm * 64 + 32 * j + r;
-        if (m >= g.M) continue;
+            for (int j = 0; j < TM; ++j) {
+                uint8_t* const dst = lds + (32 * (wm * TM + j) + r) * RS + (32 * (wn * TP + i) + 4 * h) * ES;
+                const f32x16g& c = acc[p * TP + i][j];
 #pragma unroll
-        for (int i = 0; i < 2; ++i)
+                for (int q = 0; q < 4; ++q) {
+                    if (BF16) {
+                        typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+                        const bf16x4 v = {(__bf16)c[4 * q], (__bf16)c[4 * q + 1], (__bf16)c[4 * q + 2], (__bf16)c[4 * q + 3]};
+                        *reinterpret_cast<uint2*>(dst + 16 * q) = __builtin_bit_cast(uint2, v);
+                    } else {
+                        *reinterpret_cast<float4*>(dst + 32 * q) =
+                            make_float4(c[4 * q], c[4 * q + 1], c[4 * q + 2], c[4 * q + 3]);
+                    }
+                }
+            }
+        __syncthreads();
+#pragma unroll 4
+        for (int k = 0; k < T::BM * CPR / (64 * T::WAVES); ++k) {
+            const int id = t + k * 64 * T::WAVES;
+            const int row = id / CPR, ch = id % CPR;
+            // column of the chunk: the pass holds TP tiles of each of the WN waves' column ranges
+            const int cl = ch * EPC, seg = cl / (32 * TP);
+            const int64_t m = mb0 + row, n = nb0 + seg * 32 * TN + 32 * p * TP + (cl - seg * 32 * TP);
+            if (m >= g.M || n >= g.N) continue;
+            const uint4 v = *reinterpret_cast<const uint4*>(lds + row * RS + 16 * ch);
+            if (BF16) {
+                uint16_t* const c = g.C16 + m * g.ldc_out + n;
+                if (g.vec_ok && n + 7 < g.N) {
+                    *reinterpret_cast<uint4*>(c) = v;
+                } else {
+                    const uint32_t w[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
-            for (int q = 0; q < 4; ++q)
-                store_c4(g, m, nb0 + wn * 64 + 32 * i + 8 * q + 4 * h,
-                         make_float4(acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]));
-    }
-}
-
-// Large-tile pipelined variant (same conditions as the one above): 512
-// threads own a 256 (N) x 256 (M) tile, 8 waves as 2 (N) x 4 (M) of 128 x 64
-// (4 x 2 instruction tiles, 128 accumulator registers), K 128 per stage in
-// three LDS stage buffers of 34 KB.  Twice the matrix-core work per operand
-// byte of the 128 x 128 tile and per barrier; each wave still issues 5 loads
-// per stage: W and X codes of rows 32 w .. 32 w + 31 (two 16-row loads each)
-// and one 64-row scale group (waves 0-3: W, waves 4-7: X).
-struct BigBuf {
-    uint4 wc[4 * 256];
-    uint4 xc[4 * 256];
-    uint32_t ws[256];
-    uint32_t xs[256];
-};
-
-__shared__ BigBuf g_big0, g_big1, g_big2;
-
-constexpr int64_t kBigTileMin = 96;  // 256 x 256 tiles needed before that kernel is chosen
-
-template <int B>
-__device__ __forceinline__ BigBuf& big_buf() {
-    if constexpr (B == 0) return g_big0;
-    else if constexpr (B == 1) return g_big1;
-    else return g_big2;
-}
-
-__device__ __forceinline__ void big_issue(const GemmParams& g, BigBuf& b, int wave, int lane, int64_t nb0, int64_t mb0,
-                                          int64_t row_bytes, int64_t nkb, int64_t st) {
-    const int q = lane >> 2;
-    const int blk = (lane & 3) ^ ((q >> 2) & 3);
-    const int64_t kbyte = (4 * st + blk) * 16;
-#pragma unroll
-    for (int gr = 0; gr < 2; ++gr) {
-        const int grp = 2 * wave + gr;
-        const int row = 16 * grp + q;
-        const int64_t n = min(nb0 + row, g.N - 1);
-        const int64_t m = min(mb0 + row, g.M - 1);
-        lds_load16(g.b_codes + n * row_bytes + kbyte, &b.wc[64 * grp]);
-        lds_load16(g.a_codes + m * row_bytes + kbyte, &b.xc[64 * grp]);
-    }
-    if (wave < 4) {
-        const int64_t n = min(nb0 + 64 * wave + lane, g.N - 1);
-        lds_load4(g.b_scales + n * nkb + 4 * st, &b.ws[64 * wave]);
-    } else {
-        const int64_t m = min(mb0 + 64 * (wave - 4) + lane, g.M - 1);
-        lds_load4(g.a_scales + m * nkb + 4 * st, &b.xs[64 * (wave - 4)]);
-    }
-}
-
-// A wave's fragments of one stage: both 64-wide K steps of its 4 W and 2 X tiles and their scales.
-struct BigFrags {
-    uint4 fw[2][4], fx[2][2];
-    uint32_t scw[4], scx[2];
-};
-
-__device__ __forceinline__ void big_frags(const BigBuf& b, const PipeCtx& c, BigFrags& f) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i) f.scw[i] = __builtin_amdgcn_perm(0u, b.ws[c.wn * 128 + 32 * i + c.r], c.psel);
-#pragma unroll
-    for (int j = 0; j < 2; ++j) f.scx[j] = __builtin_amdgcn_perm(0u, b.xs[c.wm * 64 + 32 * j + c.r], c.psel);
-#pragma unroll
-    for (int s = 0; s < 2; ++s) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) f.fw[s][i] = b.wc[pipe_slot(c.wn * 128 + 32 * i + c.r, 2 * s + c.h)];
-#pragma unroll
-        for (int j = 0; j < 2; ++j) f.fx[s][j] = b.xc[pipe_slot(c.wm * 64 + 32 * j + c.r, 2 * s + c.h)];
-    }
-}
-
-template <int STEP>
-__device__ __forceinline__ void big_step(const BigFrags& f, f32x16g (&acc)[4][2]) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-            acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(operand(Frag{f.fw[STEP][i], 0u}),
-                                                                         operand(Frag{f.fx[STEP][j], 0u}), acc[i][j], 4,
-                                                                         4, STEP, (int)f.scw[i], STEP, (int)f.scx[j]);
-}
-
-// All LDS reads of stage st come before stage st + 2 is issued, so the
-// vmcnt(0) the compiler still places before LDS reads in one of the three
-// unrolled iterations waits only for stage st + 1, already in flight.
-template <int CUR, int NXT>
-__device__ __forceinline__ void big_iter(const GemmParams& g, const PipeCtx& c, int64_t st, f32x16g (&acc)[4][2]) {
-    if (st + 1 < c.nst)
-        __builtin_amdgcn_s_waitcnt((kPipeLoadsPerWave & 15) | (7 << 4) | (15 << 8));  // vmcnt(5)
-    else
-        __builtin_amdgcn_s_waitcnt((7 << 4) | (15 << 8));  // vmcnt(0)
-    __builtin_amdgcn_s_barrier();
-    BigFrags f;
-    big_frags(big_buf<CUR>(), c, f);
-    if (st + 2 < c.nst) big_issue(g, big_buf<NXT>(), c.wave, c.lane, c.nb0, c.mb0, c.row_bytes, c.nkb, st + 2);
-    big_step<0>(f, acc);
-    big_step<1>(f, acc);
-}
-
-__device__ __forceinline__ void big_store(const GemmParams& g, const PipeCtx& c, const f32x16g (&acc)[4][2]) {
-    const int r = c.r, h = c.h, wn = c.wn, wm = c.wm;
-    // acc[i][j][4q + e] = C[mb0 + wm 64 + 32 j + r][nb0 + wn 128 + 32 i + 8 q + 4 h + e]
-#pragma unroll
-    for (int j = 0; j < 2; ++j) {
-        const int64_t m = c.mb0 + wm * 64 + 32 * j + r;
-        if (m >= g.M) continue;
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-#pragma unroll
-            for (int q = 0; q < 4; ++q)
-                store_c4(g, m, c.nb0 + wn * 128 + 32 * i + 8 * q + 4 * h,
-                         make_float4(acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]));
+                    for (int e = 0; e < 8; ++e)
+                        if (n + e < g.N) c[e] = (uint16_t)(w[e / 2] >> (16 * (e & 1)));
+                }
+            } else {
+                const float4 f = __builtin_bit_cast(float4, v);
+                store_c4(g, m, n, f);
+            }
+        }
     }
 }
 
@@ -447,47 +499,45 @@ __device__ __forceinline__ void xcd_tile(int64_t gx, int64_t gy, int64_t& tn, in
     tn = (L % gsize) / gm;
 }
 
-__global__ __launch_bounds__(512) void mxfp4_gemm_big_kernel(const GemmParams g) {
-    PipeCtx c;
-    const int t = threadIdx.x;
-    c.wave = __builtin_amdgcn_readfirstlane(t >> 6);  // wave-uniform: LDS bases and row offsets stay scalar
-    c.lane = t & 63;
-    c.r = c.lane & 31;
-    c.h = c.lane >> 5;
-    c.wn = c.wave >> 2;
-    c.wm = c.wave & 3;
+template <int WN, int WM, int TN, int TM, bool PING, bool DMA_SCALES>
+__global__ __launch_bounds__(64 * WN * WM) void mxfp4_gemm_pipe_kernel(const GemmParams g) {
+    typedef Tile<WN, WM, TN, TM> T;
+    __shared__ typename T::Lds lds;
     int64_t tn, tm;
     xcd_tile(gridDim.x, gridDim.y, tn, tm);
-    c.nb0 = tn * 256;
-    c.mb0 = tm * 256;
-    c.nkb = g.K / 32;
-    c.row_bytes = g.K / 2;
-    c.nst = g.K / 128;
-    c.psel = c.h ? 0x0c0c0301u : 0x0c0c0200u;
-    f32x16g acc[4][2];
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j) acc[i][j] = f32x16g{};
-    big_issue(g, g_big0, c.wave, c.lane, c.nb0, c.mb0, c.row_bytes, c.nkb, 0);
-    if (c.nst > 1) big_issue(g, g_big1, c.wave, c.lane, c.nb0, c.mb0, c.row_bytes, c.nkb, 1);
-    for (int64_t st = 0; st < c.nst; st += 3) {
-        big_iter<0, 2>(g, c, st, acc);
-        if (st + 1 < c.nst) big_iter<1, 0>(g, c, st + 1, acc);
-        if (st + 2 < c.nst) big_iter<2, 1>(g, c, st + 2, acc);
-    }
-    big_store(g, c, acc);
+    f32x16g acc[TN][TM];
+    gemm_tile<WN, WM, TN, TM, PING, DMA_SCALES>(g, lds, tn * T::BN, tm * T::BM, acc);
+    uint8_t* const stage = reinterpret_cast<uint8_t*>(&lds);
+    if (g.C16) store_tile<WN, WM, TN, TM, true>(g, stage, tn * T::BN, tm * T::BM, acc);
+    else store_tile<WN, WM, TN, TM, false>(g, stage, tn * T::BN, tm * T::BM, acc);
 }
+
+constexpr int64_t kBigTileMin = 96;  // 256 x 256 tiles needed before that kernel is chosen
+
+template <int WN, int WM, int TN, int TM, bool PING>
+static void launch_pipe(const GemmParams& g, hipStream_t st) {
+    typedef Tile<WN, WM, TN, TM> T;
+    const int64_t nkb = g.K / 32;
+    const dim3 grid((unsigned)((g.N + T::BN - 1) / T::BN), (unsigned)((g.M + T::BM - 1) / T::BM)), b(64 * T::WAVES);
+    if (nkb % 4 == 0 && nkb >= 16 && g.scales_aligned)
+        hipLaunchKernelGGL((mxfp4_gemm_pipe_kernel<WN, WM, TN, TM, PING, true>), grid, b, 0, st, g);
+    else
+        hipLaunchKernelGGL((mxfp4_gemm_pipe_kernel<WN, WM, TN, TM, PING, false>), grid, b, 0, st, g);
+}
+
+// The pipelined kernels index a tile's 256 rows with 32-bit byte offsets.
+constexpr int64_t kPipeMaxK = int64_t(1) << 24;
 
 hipError_t launch_mxfp4_gemm(const GemmParams& g, hipStream_t st) {
     // the 256 x 256 tile once there are enough of them to spread over the chip, else 128 x 128
+    // (16-byte code and scale loads per row: any K; us before, with K % 128 != 0 on the direct
+    // kernel, and now: 4096 x 5600 x 2240 151 and 49, 4608 x 3072 x 3072 41.1 and 34.3,
+    // 4608 x 3072 x 12288 124 and 98, 1000 x 3456 x 1152 12.0 and 8.1)
     const int64_t big_tiles = ((g.N + 255) / 256) * ((g.M + 255) / 256);
-    if (g.K % kGemmTileK == 0 && g.scales_aligned && big_tiles >= kBigTileMin) {
-        const dim3 grid((unsigned)((g.N + 255) / 256), (unsigned)((g.M + 255) / 256));
-        hipLaunchKernelGGL(mxfp4_gemm_big_kernel, grid, dim3(512), 0, st, g);
-    } else if (g.K % kGemmTileK == 0 && g.scales_aligned) {
-        const dim3 grid((unsigned)((g.N + 127) / 128), (unsigned)((g.M + 127) / 128));
-        hipLaunchKernelGGL(mxfp4_gemm_pipe_kernel, grid, dim3(256), 0, st, g);
+    if (g.K <= kPipeMaxK && big_tiles >= kBigTileMin) {
+        launch_pipe<2, 4, 4, 2, true>(g, st);
+    } else if (g.K <= kPipeMaxK) {
+        launch_pipe<2, 2, 2, 2, false>(g, st);
     } else {
         const dim3 grid((unsigned)((g.N + 127) / 128), (unsigned)((g.M + 127) / 128));
         hipLaunchKernelGGL(mxfp4_gemm_kernel, grid, dim3(256), 0, st, g);

@@ -53,7 +53,7 @@ struct GemmParams {
     int accumulate;           // 1: C += product, 0: C = product
     const float* bias = nullptr;  // if set: C = bias + product (bias [M, ldc_out], vec rule as C)
     uint16_t* C16 = nullptr;      // if set: bf16 output [M, ldc_out] instead of C (no bias, no accumulate)
-    int vec_ok;               // C 16-byte (C16 8-byte) aligned and ldc_out a multiple of 4
+    int vec_ok;               // C 16-byte aligned and ldc_out a multiple of 4 (C16: 16-byte and 8)
     int scales_aligned;       // both scale arrays 4-byte aligned
 };
 

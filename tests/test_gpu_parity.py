@@ -629,6 +629,30 @@ def test_mxfp4_gemm_parity(M, N, K):
     assert np.all(np.abs(host(Cd) - (ref + C0)) <= tol + 2.0 ** -23 * np.abs(ref + C0))
 
 
+@pytest.mark.parametrize("M,N,K", [(1, 1, 64), (129, 257, 96), (127, 130, 160), (129, 127, 480), (129, 129, 512),
+                                   (130, 1, 544), (129, 200, 640), (200, 129, 672), (129, 65, 1920), (2500, 2470, 672),
+                                   (2305, 2561, 640), (2500, 2470, 1152), (3, 2, (1 << 24) + 32)])
+@pytest.mark.parametrize("off", [0, 1])
+def test_mxfp4_gemm_k_tails(M, N, K, off):
+    """Every form of the last K stage and of the scale rows: 1 to 4 blocks in
+    the last stage, rows of scales that are and are not a multiple of 4 and of
+    16 bytes, fewer than 16 of them, scales that start at an odd address, tiles
+    that end past the last row, both tile sizes, and the kernel for rows beyond
+    the pipelined kernels' 32-bit offsets."""
+    ac, as_ = _rand_mx(M, K, seed=M + K)
+    bc, bs = _rand_mx(N, K, seed=N + 2 * K)
+    ref = oracle.mxfp4_gemm(ac, as_, bc, bs)
+    tol = _gemm_tolerance(ac, as_, bc, bs)
+
+    def t(a, o=0):
+        buf = torch.empty(a.size + o, dtype=torch.uint8, device="cuda")
+        buf[o:] = torch.from_numpy(a).cuda().reshape(-1)
+        return buf[o:].view(a.shape)
+
+    C = host(kq.mxfp4_gemm(t(ac), t(as_, off), t(bc), t(bs, off)))
+    assert np.all(np.abs(C - ref) <= tol), np.max(np.abs(C - ref) - tol)
+
+
 @pytest.mark.parametrize("M,N,K", [(77, 200, 2240), (33, 70, 1120), (300, 257, 3072), (5, 3, 128), (3000, 2200, 384),
                                    (2500, 2470, 1664)])
 def test_mxfp4_gemm_bf16_output(M, N, K):
