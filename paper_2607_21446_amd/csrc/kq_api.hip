@@ -521,25 +521,31 @@ kq_status kq_calib_reference(const uint16_t* X, int64_t R, int64_t d, const uint
 static kq_status calib_step_impl(const kq::CalibPlan& pl, const uint16_t* X, const uint16_t* W, const float* Yneg,
                                  float* lu, const float* lambdas, float* grad, double* losses, float* adam_m,
                                  float* adam_v, int adam_t, float lr, unsigned char* ws, hipStream_t s) {
-    const int a = pl.a, b = 32 / a;
-    float* fa = reinterpret_cast<float*>(ws + pl.fa);
-    float* fb = reinterpret_cast<float*>(ws + pl.fb);
-    hipError_t e = kq::launch_calib_inverse_factors(lu, a, pl.nfac, fa, fb, s);
-    if (e != hipSuccess) return from_hip(e, "kq_calib_step (inverse factors)");
-    kq_status st = kq_quantize_lu(X, pl.R, pl.d, lu, a, pl.nfac, ws + pl.cA, ws + pl.sA,
-                                  reinterpret_cast<float*>(ws + pl.yA), nullptr, s);
-    if (st != KQ_SUCCESS) return st;
-    st = kq_quantize(W, pl.o, pl.d, fa, fb, a, b, pl.nfac, ws + pl.cW, ws + pl.sW,
-                     reinterpret_cast<float*>(ws + pl.yW), s);
-    if (st != KQ_SUCCESS) return st;
-    // residual Q(X T) Q(W T^-T)^T - X W^T on the W4A4 GEMM with Yneg as its bias
-    float* res = reinterpret_cast<float*>(ws + pl.res);
-    const kq::GemmParams g =
-        gemm_params(ws + pl.cA, ws + pl.sA, pl.R, ws + pl.cW, ws + pl.sW, pl.o, pl.d, res, pl.o, 0, Yneg);
+    auto operand = [&](const uint16_t* M, int64_t rows, size_t c, size_t sc, size_t y, size_t q, int inverse) {
+        kq::Params p = make_params(M, rows, pl.d, ws + c, ws + sc, reinterpret_cast<float*>(ws + y));
+        p.nfac = pl.nfac;
+        p.lu = lu;
+        p.q16 = reinterpret_cast<uint16_t*>(ws + q);
+        p.inverse = inverse;
+        return p;
+    };
+    // Q(X T) and Q(W T^-T), their fp32 and dequantized values
+    hipError_t e = kq::launch_calib_quant(pl.a, operand(X, pl.R, pl.cA, pl.sA, pl.yA, pl.qA, 0),
+                                          operand(W, pl.o, pl.cW, pl.sW, pl.yW, pl.qW, 1), s);
+    if (e != hipSuccess) return from_hip(e, "kq_calib_step (quantize)");
+    // residual Q(X T) Q(W T^-T)^T - X W^T on the W4A4 GEMM with Yneg as its bias, as two bf16 terms
+    kq::GemmParams g =
+        gemm_params(ws + pl.cA, ws + pl.sA, pl.R, ws + pl.cW, ws + pl.sW, pl.o, pl.d, nullptr, pl.o, 0, Yneg);
+    g.vec_ok = aligned(Yneg, 16) && pl.o % 4 == 0;
+    g.rh = reinterpret_cast<uint16_t*>(ws + pl.rh);
+    g.rl = reinterpret_cast<uint16_t*>(ws + pl.rl);
+    g.ldr = pl.op;
+    g.rows_pad = pl.Rp;
+    g.sq_part = reinterpret_cast<double*>(ws + pl.sr);
     e = kq::launch_mxfp4_gemm(g, s);
     if (e != hipSuccess) return from_hip(e, "kq_calib_step (residual)");
     kq::CalibStepArgs args{X, W, lu, lambdas, grad, losses, lu, adam_m, adam_v, adam_t, lr, ws};
-    return from_hip(kq::launch_calib_backward(pl, args, s), "kq_calib_step (backward)");
+    return from_hip(kq::launch_calib_backward(pl, args, kq::mxfp4_gemm_workgroups(g), s), "kq_calib_step (backward)");
 }
 
 static kq_status check_workspace(const kq::CalibPlan& pl, const void* ws, size_t ws_bytes) {

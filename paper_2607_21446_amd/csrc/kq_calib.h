@@ -11,15 +11,17 @@ namespace kq {
 struct CalibPlan {
     int64_t R = 0, o = 0, d = 0, nb = 0, nfac = 0;
     int a = 4;
-    int64_t ntn = 0;                      // 256-column tiles of the d axis (backward GEMMs)
-    int64_t act_mt = 0, act_chunks = 0;   // activation-side backward: row tiles, workgroup rows
-    int64_t w_mt = 0, w_ks = 0, w_kchunk = 0, w_chunks = 0;  // weight side: row tiles, K splits
-    int64_t nsum = 0;                     // partial sums of the residual's squares (one per 64 x 64 tile)
+    bool big = true;                      // 256 x 256 tiles of the backward products, else 128 x 128
+    int64_t ntn = 0;                      // column tiles of the d axis
+    // activation side: row tiles, workgroup rows that share them, K parts and their length; weight side
+    int64_t act_mt = 0, act_chunks = 0, act_ks = 0, act_kchunk = 0;
+    int64_t w_mt = 0, w_chunks = 0, w_ks = 0, w_kchunk = 0;
+    int64_t nsum = 0;                     // room for the partial sums of the residual's squares
     int64_t Rp = 0, op = 0;               // R and o rounded up to the 32-deep K stage
     // byte offsets into the workspace (each 256-byte aligned)
-    size_t yA = 0, cA = 0, sA = 0, yW = 0, cW = 0, sW = 0, res = 0, fa = 0, fb = 0;
-    size_t rnh = 0, rnl = 0, rth = 0, rtl = 0, aht = 0, wht = 0;  // K-contiguous bf16 operands of the backward products
-    size_t gpa = 0, gpw = 0, sqa = 0, sqw = 0, sr = 0, ga = 0, gw = 0;
+    size_t yA = 0, cA = 0, sA = 0, qA = 0, yW = 0, cW = 0, sW = 0, qW = 0;  // y, codes, scales, dequantized bf16
+    size_t rh = 0, rl = 0;                // the residual's two bf16 terms [Rp, op]
+    size_t gpa = 0, gpw = 0, sqa = 0, sqw = 0, sr = 0;
     size_t grad = 0, am = 0, av = 0, lam = 0;
     size_t total = 0;
 };
@@ -29,10 +31,6 @@ CalibPlan calib_plan(int64_t R, int64_t o, int64_t d, int a, int64_t nfac);
 // Yneg[r][n] = -sum_c X[r][c] W[n][c] (bf16 matrix cores, exact products, fp32 accumulation).
 hipError_t launch_calib_reference(const uint16_t* X, int64_t R, int64_t d, const uint16_t* W, int64_t o,
                                   float* Yneg, hipStream_t st);
-
-// Factors of the inverse block T^-1 = G_1^-1 (x) ... (x) G_5^-1 for the weight side.
-hipError_t launch_calib_inverse_factors(const float* lu, int a, int64_t nfac, float* Ainv, float* Binv,
-                                        hipStream_t st);
 
 struct CalibStepArgs {
     const uint16_t* X;      // [R, d] bf16
@@ -50,8 +48,9 @@ struct CalibStepArgs {
 };
 
 // Backward and update part of a step; the forward products (quantized operands,
-// their fp32 values and the residual) must already be in the workspace.
-hipError_t launch_calib_backward(const CalibPlan& pl, const CalibStepArgs& s, hipStream_t st);
+// their fp32 and dequantized values, the residual's terms and the nsr partial
+// sums of its squares) must already be in the workspace.
+hipError_t launch_calib_backward(const CalibPlan& pl, const CalibStepArgs& s, int64_t nsr, hipStream_t st);
 
 // Small helpers of the calibration loop.
 hipError_t launch_calib_init(float* adam_m, float* adam_v, int64_t n, float* lambdas, hipStream_t st);

@@ -33,6 +33,7 @@
 
 #include <algorithm>
 #include <cmath>
+#include <type_traits>
 
 #include "kq_calib.h"
 
@@ -42,23 +43,9 @@ namespace {
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
-constexpr int CT = 128;          // C tile rows of a workgroup
-constexpr int BK = 32;           // K per LDS stage (bf16 elements; 64-byte rows)
-constexpr int kTargetWg = 2048;  // workgroups the backward GEMMs aim for
-// Workgroup shapes: 2 x WN waves of 64 x 64, a C tile of 128 x 64 WN.  The
-// backward GEMMs take WN = 4 (eight waves, 128 x 256: a stage's bytes then
-// carry 1.5 times the matrix-core work of the 128 x 128 tile, as A has two
-// terms), the reference product WN = 2.
-constexpr int kWnBackward = 4;
-constexpr int kWnReference = 2;
+constexpr int BK = 32;  // K per LDS stage (bf16 elements)
 
 __device__ __forceinline__ float bf16f(uint16_t v) { return __uint_as_float(uint32_t(v) << 16); }
-
-// bf16 nearest-even of a finite fp32 value.
-__device__ __forceinline__ uint32_t bf16_rne(float x) {
-    const uint32_t u = __float_as_uint(x);
-    return (u + 0x7FFFu + ((u >> 16) & 1u)) >> 16;
-}
 
 // Value of an E2M1 code at E8M0 scale byte s (OCP MX v1.0), exact in fp32 (and in bf16).
 __device__ __forceinline__ float mx_value(uint32_t nib, uint32_t s) {
@@ -77,110 +64,222 @@ __device__ __forceinline__ f32x16 mfma32(float a, float b, f32x16 c) {
     return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0);
 }
 
-// LDS stage of one operand: 128 rows x 32 bf16 (four 16-byte chunks per
-// row); chunk c of row r sits at slot c ^ ((r >> 2) & 3), so the 16 lanes of
-// a ds_read_b128 phase (rows r .. r + 15, one chunk each) cover all banks.
-__device__ __forceinline__ int lds_off(int r, int c) { return r * 64 + 16 * (c ^ ((r >> 2) & 3)); }
-
 // ---------------------------------------------------------------- operands
-// A GEMM operand: bf16 [rows][ld], K contiguous, K extent a multiple of 32
-// (zero padded by the producer), 16-byte aligned rows.  Stages of 32 K
-// columns x 128 rows go straight from global memory into LDS
-// (global_load_lds: lane l's 16 bytes land at the wave-uniform LDS address
-// + 16 l); one instruction fills 16 rows, lane l taking row l / 4 and the
-// chunk whose swizzled slot is l % 4.  Rows past the matrix load its last row
-// (their products land in rows or columns the epilogues never use).
+// A GEMM operand, bf16, rows 16-byte aligned, columns a multiple of 8:
+//   K-contiguous  [rows][ld]: a tile row's 32 K values of a stage are 64 bytes;
+//   K-strided     [K][ld] (TR): stage rows are K, the tile's columns contiguous,
+//                 and fragments come by transposing LDS reads
+//                 (ds_read_b64_tr_b16), so no transposed copy is made.
+// Rows past the matrix load its last row and columns past it its last 8 (their
+// products meet zeros of the other operand, or land in rows or columns the
+// epilogues never use).
 struct Opnd {
     const uint8_t* p;
-    int64_t rows, ld;  // ld in bytes
+    int64_t rows, cols, ld;  // ld in bytes
 };
 
-__device__ __forceinline__ void lds_load16(const uint8_t* src, void* lds_base) {
-    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src,
-                                     (__attribute__((address_space(3))) void*)lds_base, 16, 0, 0);
+// A load straight into LDS (lane l's 16 bytes land at the wave-uniform LDS
+// address + 16 l), as asm: the compiler puts a vmcnt(0) before LDS reads that may
+// alias such a load it knows of, which would drain the stages in flight.  The
+// waits are explicit (wait_stage), the load has no register result, and nothing
+// else in these kernels uses m0.
+__device__ __forceinline__ void lds_dma16(uint32_t lds, uint32_t voff, const uint8_t* base) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(voff), "s"(base)
+                 : "memory");
 }
 
-template <int TA, int WN>
-struct StageBuf {
-    uint4 a[TA][512];   // 128 rows x 4 slots of 16 bytes, slot lds_off(r, c) / 16
-    uint4 b[256 * WN];  // 64 WN rows, the same layout
-};
-
-// Loads of one stage per wave (one instruction = 16 rows x 64 bytes): of
-// each A term the GA = 4 / WN groups of 16 rows GA wave .. GA wave + GA - 1,
-// of B the groups 2 wave and 2 wave + 1; TA GA + 2 instructions in all.
-template <int TA, int WN>
-constexpr int stage_loads() { return TA * (4 / WN) + 2; }
-
-template <int TA, int WN>
-__device__ __forceinline__ void stage_issue(const Opnd (&A)[TA], const Opnd& B, StageBuf<TA, WN>& sb, int wave,
-                                            int lane, int64_t m0, int64_t n0, int64_t k0) {
-    constexpr int GA = 4 / WN;
-    const int q = lane >> 2;
-    const int blk = (lane & 3) ^ ((q >> 2) & 3);
-    const int64_t kb = k0 * 2 + 16 * blk;
-#pragma unroll
-    for (int gr = 0; gr < 2; ++gr) {
-        if (gr < GA) {
-            const int grp = GA * wave + gr;
-#pragma unroll
-            for (int x = 0; x < TA; ++x) {
-                const int64_t m = min(m0 + 16 * grp + q, A[x].rows - 1);
-                lds_load16(A[x].p + m * A[x].ld + kb, &sb.a[x][64 * grp]);
-            }
-        }
-        const int grp = 2 * wave + gr;
-        const int64_t n = min(n0 + 16 * grp + q, B.rows - 1);
-        lds_load16(B.p + n * B.ld + kb, &sb.b[64 * grp]);
-    }
+__device__ __forceinline__ void stage_barrier() {
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("s_barrier" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
 }
 
-template <int TA>
-struct Frags {
-    bf16x8 a[2][TA][2], b[2][2];  // [k half s][term][tile]
-};
+// Until only this wave's LOADS loads of a later stage (if there is one) are outstanding.
+template <int LOADS>
+__device__ __forceinline__ void wait_stage(bool later) {
+    static_assert(LOADS == 4 || LOADS == 6, "loads per stage");
+    if (!later) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    else if (LOADS == 6) asm volatile("s_waitcnt vmcnt(6)" ::: "memory");
+    else asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
+}
 
-// this wave's fragments of one stage (all LDS reads of the stage, before any
-// later stage is issued)
-template <int TA, int WN>
-__device__ __forceinline__ void stage_frags(const StageBuf<TA, WN>& sb, int h, int wm, int wn, int l32,
-                                            Frags<TA>& f) {
-#pragma unroll
-    for (int s = 0; s < 2; ++s)
+typedef __attribute__((address_space(3))) uint8_t lds_byte;
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
+typedef __attribute__((address_space(3))) uint4 lds_uint4;
+
+// One operand's stage in LDS (64 BX bytes) for a tile of BX rows (or columns).
+//   K-contiguous: 16-byte chunk c (of 4) of row r at 64 r + 16 (c ^ ((r >> 2) & 3)), so
+//     the 16 lanes of a ds_read_b128 phase cover all banks; one load fills 16 rows.
+//   K-strided: chunk c (8 columns) of K row r at 2 BX r + 16 (c ^ ((r & 3) << 2)), so the
+//     four K rows a 16-lane group of a transposing read takes lie in different banks;
+//     one load fills 512 / BX K rows.
+// Fragments: lane (h = lane / 32) holds K values 16 h + 8 s .. + 7 of k-step s.
+template <int BX, bool TR>
+struct OpndStage {
+    uint32_t voff[2], row[2], col[2];  // this lane's two chunks of a stage: byte offset; K row and byte column (TR)
+    uint32_t frag;                     // this lane's fragment address for tile 0, k-step 0
+
+    __device__ __forceinline__ void setup(const Opnd& m, int64_t x0, int wave, int lane) {
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
-#pragma unroll
-            for (int x = 0; x < TA; ++x)
-                f.a[s][x][i] = __builtin_bit_cast(bf16x8, sb.a[x][lds_off(wm * 64 + 32 * i + l32, 2 * h + s) / 16]);
-            f.b[s][i] = __builtin_bit_cast(bf16x8, sb.b[lds_off(wn * 64 + 32 * i + l32, 2 * h + s) / 16]);
+            if (TR) {
+                constexpr int RPI = 512 / BX, LPR = 64 / RPI;
+                row[i] = RPI * (2 * wave + i) + lane / LPR;
+                const int c = (lane % LPR) ^ ((row[i] & 3) << 2);
+                col[i] = 2u * (uint32_t)min<int64_t>(8 * c, m.cols - 8 - x0);
+                voff[i] = row[i] * (uint32_t)m.ld + col[i];
+            } else {
+                const int q = lane >> 2, blk = (lane & 3) ^ ((q >> 2) & 3);
+                voff[i] = (uint32_t)min<int64_t>(16 * (2 * wave + i) + q, m.rows - 1 - x0) * (uint32_t)m.ld + 16u * blk;
+            }
         }
-}
-
-template <int TA>
-__device__ __forceinline__ void stage_mfma(const Frags<TA>& f, f32x16 (&acc)[2][2]) {
-#pragma unroll
-    for (int s = 0; s < 2; ++s)
-#pragma unroll
-        for (int x = 0; x < TA; ++x)
+    }
+    // base of the tile: K-contiguous, row x0; K-strided, column x0
+    static __device__ __forceinline__ const uint8_t* base(const Opnd& m, int64_t x0) {
+        return m.p + (TR ? 2 * x0 : x0 * m.ld);
+    }
+    // K values k .. k + 31 to LDS address dst (of this operand's stage)
+    __device__ __forceinline__ void issue(const Opnd& m, const uint8_t* base, int64_t k, uint32_t dst, int wave) const {
+        const uint8_t* const b = base + (TR ? k * m.ld : 2 * k);
+        if (TR && k + BK > m.rows) {  // a last stage past the last K row
+            const uint32_t last = (uint32_t)(m.rows - 1 - k);
 #pragma unroll
             for (int i = 0; i < 2; ++i)
+                lds_dma16(dst + 1024u * (2 * wave + i), min(row[i], last) * (uint32_t)m.ld + col[i], b);
+        } else {
 #pragma unroll
-                for (int j = 0; j < 2; ++j)
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.a[s][x][i], f.b[s][j], acc[i][j], 0, 0, 0);
-}
+            for (int i = 0; i < 2; ++i) lds_dma16(dst + 1024u * (2 * wave + i), voff[i], b);
+        }
+    }
+    // t0: this wave's first 32-wide tile
+    __device__ __forceinline__ void frag_setup(int t0, int lane) {
+        const int h = lane >> 5, l32 = lane & 31;
+        if (TR) {
+            const int jr = (lane >> 2) & 3;  // K row within a group of 4
+            const int c = 4 * t0 + 2 * ((lane >> 4) & 1) + ((lane & 3) >> 1);
+            frag = (16 * h + jr) * (2 * BX) + 16 * (c ^ (jr << 2)) + 8 * (lane & 1);
+        } else {
+            frag = (32 * t0 + l32) * 64 + 16 * ((2 * h) ^ ((l32 >> 2) & 3));
+        }
+    }
+    // fragment of tile t0 + i (t0 a multiple of the wave's tile count), k-step s
+    __device__ __forceinline__ bf16x8 read(lds_byte* stage, int i, int s) const {
+        if (TR) {
+            lds_byte* const p = stage + (frag ^ (64u * i)) + 8 * s * (2 * BX);
+            const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16(reinterpret_cast<lds_s16x4*>(p));
+            const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(reinterpret_cast<lds_s16x4*>(p + 4 * (2 * BX)));
+            typedef short s16x8 __attribute__((ext_vector_type(8)));
+            return __builtin_bit_cast(bf16x8, s16x8{lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w});
+        }
+        lds_byte* const p = stage + (frag ^ (16u * s)) + 2048 * i;
+        return __builtin_bit_cast(bf16x8, *reinterpret_cast<lds_uint4*>(p));
+    }
+};
 
-// Before stage st is used (buffer st % 3; stage st + 2 is then issued into
-// buffer (st + 2) % 3, which every wave finished reading before the barrier)
-// each wave waits until only its loads of stage st + 1 are outstanding, then
-// a bare s_barrier (a fenced barrier would drain the loads in flight).
-template <int TA, int WN>
-__device__ __forceinline__ void pipe_wait(int64_t st, int64_t nst) {
-    constexpr int kLoads = stage_loads<TA, WN>();
-    if (st + 1 < nst)
-        __builtin_amdgcn_s_waitcnt((kLoads & 15) | (7 << 4) | (15 << 8));  // vmcnt(kLoads)
-    else
-        __builtin_amdgcn_s_waitcnt((7 << 4) | (15 << 8));  // vmcnt(0)
-    __builtin_amdgcn_s_barrier();
+// Workgroup tile: WM x WN waves of TM x TN tiles of 32 x 32, A in TA bf16 terms.
+template <int TA, int WM, int WN, int TM, int TN>
+struct CalibTile {
+    static constexpr int BM = 32 * WM * TM, BN = 32 * WN * TN, WAVES = WM * WN, THREADS = 64 * WAVES;
+    static_assert(BM == 32 * WAVES && BN == 32 * WAVES, "two loads per wave, operand term and stage");
+    static constexpr int kStageBytes = 64 * (TA * BM + BN), kStages = 3;
+    static constexpr int kLdsBytes = kStages * kStageBytes;
+};
+
+// acc = sum over K values k_lo .. k_hi (a multiple of 32 of them) of A[m0 + m][k]
+// B[n0 + n][k]; three stage buffers, two in flight.
+//
+// PING (eight waves, two per SIMD): waves 4-7 run half a stage behind waves 0-3
+// (one extra barrier at the start), so that on every SIMD one wave reads its
+// fragments and issues loads while the other computes.  Waves 0-3 read stage k
+// and issue stage k + 2 in phase 2k and compute it in phase 2k + 1, waves 4-7 one
+// phase later.  Stage k + 2 overwrites the buffer of stage k - 1, whose last reads
+// returned before the barrier that ends phase 2k - 1; every wave has waited for
+// its loads of stage k before that barrier.
+template <int TA, bool ATR, bool BTR, int WM, int WN, int TM, int TN, bool PING>
+__device__ __forceinline__ void calib_product(const Opnd (&A)[TA], const Opnd& B, uint8_t* lds_generic, int64_t m0,
+                                              int64_t n0, int64_t k_lo, int64_t k_hi, f32x16 (&acc)[TM][TN]) {
+    typedef CalibTile<TA, WM, WN, TM, TN> T;
+    constexpr int kLoads = 2 * (TA + 1);
+    lds_byte* const lds = (lds_byte*)lds_generic;
+    const uint32_t lds0 = (uint32_t)(uintptr_t)lds;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    int lane = threadIdx.x & 63;
+    asm volatile("" : "+v"(lane));  // the lane's addresses are not kept in registers through the epilogue
+    const int wm = wave / WN, wn = wave % WN;
+    const int nst = (int)((k_hi - k_lo) / BK);
+    OpndStage<T::BM, ATR> sa;  // the terms of A have one layout
+    OpndStage<T::BN, BTR> sb;
+    sa.setup(A[0], m0, wave, lane);
+    sb.setup(B, n0, wave, lane);
+    sa.frag_setup(wm * TM, lane);
+    sb.frag_setup(wn * TN, lane);
+    const uint8_t* abase[TA];
+#pragma unroll
+    for (int x = 0; x < TA; ++x) abase[x] = sa.base(A[x], m0);
+    const uint8_t* const bbase = sb.base(B, n0);
+    auto issue = [&](int st, int buf) {
+        const int64_t k = k_lo + (int64_t)st * BK;
+        const uint32_t dst = lds0 + buf * T::kStageBytes;
+#pragma unroll
+        for (int x = 0; x < TA; ++x) sa.issue(A[x], abase[x], k, dst + x * 64 * T::BM, wave);
+        sb.issue(B, bbase, k, dst + TA * 64 * T::BM, wave);
+    };
+    const bool behind = PING && wave >= T::WAVES / 2;
+    auto stage = [&](int st, auto bufc) {
+        constexpr int J = decltype(bufc)::value;
+        lds_byte* const sbuf = lds + J * T::kStageBytes;
+        bf16x8 fa[2][TA][TM], fb[2][TN];
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+#pragma unroll
+            for (int x = 0; x < TA; ++x)
+#pragma unroll
+                for (int i = 0; i < TM; ++i) fa[s][x][i] = sa.read(sbuf + x * 64 * T::BM, i, s);
+#pragma unroll
+            for (int j = 0; j < TN; ++j) fb[s][j] = sb.read(sbuf + TA * 64 * T::BM, j, s);
+        }
+        if (st + 2 < nst) issue(st + 2, (J + 2) % 3);
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        auto products = [&]() {
+#pragma unroll
+            for (int s = 0; s < 2; ++s)
+#pragma unroll
+                for (int x = 0; x < TA; ++x)
+#pragma unroll
+                    for (int i = 0; i < TM; ++i)
+#pragma unroll
+                        for (int j = 0; j < TN; ++j)
+                            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[s][x][i], fb[s][j], acc[i][j], 0, 0, 0);
+        };
+        if (PING) {
+            if (behind) wait_stage<kLoads>(st + 2 < nst);
+            stage_barrier();
+            products();
+            if (!behind) wait_stage<kLoads>(st + 2 < nst);
+            stage_barrier();
+        } else {
+            products();
+            wait_stage<kLoads>(st + 2 < nst);
+            stage_barrier();
+        }
+    };
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j) acc[i][j] = f32x16{};
+    if (nst <= 0) return;
+    issue(0, 0);
+    if (nst > 1) issue(1, 1);
+    wait_stage<kLoads>(nst > 1);
+    stage_barrier();
+    if (behind) stage_barrier();
+    for (int st = 0; st < nst; st += 3) {
+        stage(st, std::integral_constant<int, 0>{});
+        if (st + 1 < nst) stage(st + 1, std::integral_constant<int, 1>{});
+        if (st + 2 < nst) stage(st + 2, std::integral_constant<int, 2>{});
+    }
+    if (PING && !behind) stage_barrier();
 }
 
 // --------------------------------------------------------------- epilogues
@@ -188,27 +287,24 @@ __device__ __forceinline__ void pipe_wait(int64_t st, int64_t nst) {
 // register 4q + r, element (row 8q + 4h + r, column l % 32).
 
 // Yneg = -acc (the reference product of the loss).
-struct EpiStoreNeg {
-    float* out;
-    int64_t M, N, ld;
-    static constexpr bool kGram = false;
-    __device__ void tile(const f32x16 (&acc)[2][2], int64_t m0, int64_t n0, int64_t, int wm, int wn, int lane,
-                         f32x16 (&)[2], double&) const {
-        const int h = lane >> 5, l32 = lane & 31;
+template <int WM, int WN, int TM, int TN>
+__device__ __forceinline__ void store_neg(const f32x16 (&acc)[TM][TN], float* out, int64_t M, int64_t N, int64_t m0,
+                                          int64_t n0) {
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int wm = wave / WN, wn = wave % WN, h = lane >> 5, l32 = lane & 31;
 #pragma unroll
-        for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < TM; ++i)
 #pragma unroll
-            for (int jj = 0; jj < 2; ++jj) {
-                const int64_t col = n0 + wn * 64 + 32 * jj + l32;
-                if (col >= N) continue;
+        for (int j = 0; j < TN; ++j) {
+            const int64_t col = n0 + 32 * (wn * TN + j) + l32;
+            if (col >= N) continue;
 #pragma unroll
-                for (int e = 0; e < 16; ++e) {
-                    const int64_t row = m0 + wm * 64 + 32 * i + 8 * (e / 4) + 4 * h + (e % 4);
-                    if (row < M) out[row * ld + col] = -acc[i][jj][e];
-                }
+            for (int e = 0; e < 16; ++e) {
+                const int64_t row = m0 + 32 * (wm * TM + i) + 8 * (e / 4) + 4 * h + (e % 4);
+                if (row < M) out[row * N + col] = -acc[i][j][e];
             }
-    }
-};
+        }
+}
 
 // Gradient epilogue.  acc holds a tile of  P = dL_out/dQ * (R o) / 2  for the
 // quantized operand Q [M, d] (exact up to the split of K, which is linear).
@@ -220,33 +316,46 @@ struct EpiStoreNeg {
 // transform, bf16) run on the matrix cores with the rows as the K index,
 // taking g straight from the accumulator registers.  [ks == 0] tiles also add
 // (Q - y)^2 to the regulariser sum.
-struct EpiGram {
+struct Side {
+    Opnd A[2], B;           // the product: residual terms, dequantized operand
     const uint16_t* left;   // [M, d] bf16
     const float* y;         // [M, d]
     const uint8_t* codes;   // [M, d / 2]
     const uint8_t* scales;  // [M, d / 32]
-    int64_t M, d;
-    float c1;
-    const float* lambdas;
+    int64_t M;
     int lam_index;
     float c2_unit;          // 2 / (rows d); c2 = lambda * c2_unit
-    float* partial;         // [chunks, d / 32, 32, 32]
-    double* sq_partial;     // [chunks, ntn]
-    static constexpr bool kGram = true;
-    __device__ void tile(const f32x16 (&acc)[2][2], int64_t m0, int64_t n0, int64_t ks, int wm, int wn, int lane,
-                         f32x16 (&gram)[2], double& sq) const {
-        const int h = lane >> 5, l32 = lane & 31;
-        const float c2 = lambdas[lam_index] * c2_unit;
-        const int64_t nb = d / 32;
+    float* partial;         // [chunks * ks, d / 32, 32, 32]
+    double* sq_partial;     // [m_tiles, ntn]
+    int64_t K, kchunk;      // K (a multiple of 32) in ks parts of kchunk
+    int ks;
+    int64_t m_tiles, chunks;  // workgroup row c takes the m tiles c, c + chunks, ...
+    int64_t works;            // chunks * ks * ntn
+};
+
+template <int WM, int WN, int TM, int TN>
+__device__ __forceinline__ void gram_tile(const f32x16 (&acc)[TM][TN], const Side& s, uint8_t* lds, int64_t d, float c1,
+                                          const float* lambdas, int64_t slot, bool add, int64_t ntn, int64_t m0,
+                                          int64_t n0, bool first) {
+    constexpr int WAVES = WM * WN;
+    int t = threadIdx.x;
+    asm volatile("" : "+v"(t));  // nor the epilogue's through the product
+    const int wave = __builtin_amdgcn_readfirstlane(t >> 6), lane = t & 63;
+    const int wm = wave / WN, wn = wave % WN, h = lane >> 5, l32 = lane & 31;
+    const float c2 = lambdas[s.lam_index] * s.c2_unit;
+    const int64_t nb = d / 32;
+    double sq = 0.0;
+    float* const sums = reinterpret_cast<float*>(lds);  // [wm][block of the tile][32][32]
 #pragma unroll
-        for (int jj = 0; jj < 2; ++jj) {
-            const int64_t blk = (n0 + wn * 64 + 32 * jj) / 32;
-            if (blk >= nb) continue;
+    for (int j = 0; j < TN; ++j) {
+        const int64_t blk = n0 / 32 + wn * TN + j;
+        f32x16 gram = {};
+        if (blk < nb) {
             const int64_t col = blk * 32 + l32;
 #pragma unroll
-            for (int i = 0; i < 2; ++i) {
-                const int64_t rbase = m0 + wm * 64 + 32 * i;
-                if (rbase >= M) continue;
+            for (int i = 0; i < TM; ++i) {
+                const int64_t rbase = m0 + 32 * (wm * TM + i);
+                if (rbase >= s.M) continue;
                 // per half of the 16 rows: all loads first (rows past M read row M - 1 and are
                 // masked), then the arithmetic
                 f32x16 g;
@@ -258,20 +367,20 @@ struct EpiGram {
 #pragma unroll
                     for (int u = 0; u < 8; ++u) {
                         const int e = 8 * half + u;
-                        const int64_t row = min(rbase + 8 * (e / 4) + 4 * h + (e % 4), M - 1);
-                        yv[u] = y[row * d + col];
-                        byte[u] = codes[row * (d / 2) + col / 2];
-                        sbyte[u] = scales[row * nb + blk];
-                        lraw[u] = left[row * d + col];
+                        const int64_t row = min(rbase + 8 * (e / 4) + 4 * h + (e % 4), s.M - 1);
+                        yv[u] = s.y[row * d + col];
+                        byte[u] = s.codes[row * (d / 2) + col / 2];
+                        sbyte[u] = s.scales[row * nb + blk];
+                        lraw[u] = s.left[row * d + col];
                     }
 #pragma unroll
                     for (int u = 0; u < 8; ++u) {
                         const int e = 8 * half + u;
-                        const bool valid = rbase + 8 * (e / 4) + 4 * h + (e % 4) < M;
+                        const bool valid = rbase + 8 * (e / 4) + 4 * h + (e % 4) < s.M;
                         const float qv = mx_value((col & 1) ? byte[u] >> 4 : byte[u], sbyte[u]);
                         const bool pass = fabsf(yv[u]) <= 6.0f * scale_value(sbyte[u]);
-                        float gv = pass ? c1 * acc[i][jj][e] : 0.f;
-                        if (ks == 0) {
+                        float gv = pass ? c1 * acc[i][j][e] : 0.f;
+                        if (first) {
                             const float diff = qv - yv[u];
                             if (!pass) gv -= c2 * diff;
                             if (valid) sq += double(diff) * double(diff);
@@ -281,251 +390,139 @@ struct EpiGram {
                     }
                 }
 #pragma unroll
-                for (int e = 0; e < 16; ++e) gram[jj] = mfma32(lv[e], g[e], gram[jj]);
+                for (int e = 0; e < 16; ++e) gram = mfma32(lv[e], g[e], gram);
             }
         }
-    }
-};
-
-struct GemmGrid {
-    int64_t M, N, K;
-    int64_t m_tiles, ks, kchunk, chunks;
-    int xcd;  // 1: the column tiles of one chunk on one XCD (see calib_gemm_kernel)
-};
-
-template <int TA, class EPI>
-struct GemmArgs {
-    Opnd A[TA];
-    Opnd B;
-    EPI epi;
-    GemmGrid g;
-};
-
-// C tile = sum_k A[m][k] B[n][k] over the work items (m tile, K split) of
-// this workgroup, each handed to the epilogue; A has TA bf16 terms.  Three
-// stage buffers, two stages in flight.
-template <int TA, int WN, class EPI>
-__global__ __launch_bounds__(128 * WN) void calib_gemm_kernel(const GemmArgs<TA, EPI> args) {
-    __shared__ StageBuf<TA, WN> sb0, sb1, sb2;
-    __shared__ double sq_lds[2 * WN];
-    const GemmGrid& g = args.g;
-    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-    const int wm = wave / WN, wn = wave % WN;
-    const int h = lane >> 5, l32 = lane & 31;
-    // work (chunk c, column tile tn).  xcd: workgroup L of the dispatch order
-    // runs on XCD L % 8, and each XCD takes a contiguous range of the works
-    // (column tile fastest), so the column tiles of a chunk, which read the
-    // same A rows at the same pace, share one L2
-    int64_t tn = blockIdx.x, c = blockIdx.y;
-    if (g.xcd) {
-        const int64_t G = int64_t(gridDim.x) * gridDim.y, L = blockIdx.x + int64_t(gridDim.x) * blockIdx.y;
-        const int64_t q = G >> 3, r = G & 7, x = L & 7;
-        const int64_t wk = x * q + (x < r ? x : r) + (L >> 3);
-        tn = wk % gridDim.x;
-        c = wk / gridDim.x;
-    }
-    const int64_t n0 = tn * (64 * WN);
-
-    f32x16 gram[2];
-    gram[0] = f32x16{};
-    gram[1] = f32x16{};
-    double sq = 0.0;
-
-    for (int64_t it = c; it < g.m_tiles * g.ks; it += g.chunks) {
-        const int64_t mt = it / g.ks, ks = it % g.ks;
-        const int64_t m0 = mt * CT;
-        const int64_t k_lo = ks * g.kchunk, k_hi = std::min(g.K, k_lo + g.kchunk);
-        f32x16 acc[2][2];
+        float* const dst = sums + ((wm * WN + wn) * TN + j) * 1024;
 #pragma unroll
-        for (int i = 0; i < 2; ++i)
+        for (int e = 0; e < 16; ++e) dst[(8 * (e / 4) + 4 * h + (e % 4)) * 32 + l32] = gram[e];
+    }
+    __syncthreads();
+    // the WM row groups of a block, in order, and one write per block
+    for (int k = 4 * t; k < WN * TN * 1024; k += 4 * 64 * WAVES) {
+        const int64_t blk = n0 / 32 + k / 1024;
+        if (blk >= nb) continue;
+        float4 v = *reinterpret_cast<const float4*>(sums + k);
 #pragma unroll
-            for (int j = 0; j < 2; ++j) acc[i][j] = f32x16{};
-        const int64_t nst = k_hi > k_lo ? (k_hi - k_lo) / BK : 0;
-        if (nst > 0) {
-            // every wave is done with the buffers (and its earlier memory operations) before they refill
-            __builtin_amdgcn_s_waitcnt((7 << 4) | (15 << 8));
-            __syncthreads();
-            stage_issue<TA, WN>(args.A, args.B, sb0, wave, lane, m0, n0, k_lo);
-            if (nst > 1) stage_issue<TA, WN>(args.A, args.B, sb1, wave, lane, m0, n0, k_lo + BK);
-            Frags<TA> f;
-            for (int64_t st = 0; st < nst; st += 3) {
-                pipe_wait<TA, WN>(st, nst);
-                stage_frags<TA, WN>(sb0, h, wm, wn, l32, f);
-                if (st + 2 < nst) stage_issue<TA, WN>(args.A, args.B, sb2, wave, lane, m0, n0, k_lo + (st + 2) * BK);
-                stage_mfma<TA>(f, acc);
-                if (st + 1 < nst) {
-                    pipe_wait<TA, WN>(st + 1, nst);
-                    stage_frags<TA, WN>(sb1, h, wm, wn, l32, f);
-                    if (st + 3 < nst) stage_issue<TA, WN>(args.A, args.B, sb0, wave, lane, m0, n0, k_lo + (st + 3) * BK);
-                    stage_mfma<TA>(f, acc);
-                }
-                if (st + 2 < nst) {
-                    pipe_wait<TA, WN>(st + 2, nst);
-                    stage_frags<TA, WN>(sb2, h, wm, wn, l32, f);
-                    if (st + 4 < nst) stage_issue<TA, WN>(args.A, args.B, sb1, wave, lane, m0, n0, k_lo + (st + 4) * BK);
-                    stage_mfma<TA>(f, acc);
-                }
-            }
+        for (int w = 1; w < WM; ++w) {
+            const float4 o = *reinterpret_cast<const float4*>(sums + w * (WN * TN * 1024) + k);
+            v = make_float4(v.x + o.x, v.y + o.y, v.z + o.z, v.w + o.w);
         }
-        args.epi.tile(acc, m0, n0, ks, wm, wn, lane, gram, sq);
+        float4* const dst = reinterpret_cast<float4*>(s.partial + (slot * nb + blk) * 1024 + k % 1024);
+        if (add) {  // this workgroup's earlier m tiles
+            const float4 o = *dst;
+            v = make_float4(o.x + v.x, o.y + v.y, o.z + v.z, o.w + v.w);
+        }
+        *dst = v;
     }
-
-    if constexpr (EPI::kGram) {
-        // rows 64..127 of the tile (wm = 1) join rows 0..63, then one write per block
+    if (first) {
         __syncthreads();
-        float* red = reinterpret_cast<float*>(&sb0);
-        if (wm == 1) {
-#pragma unroll
-            for (int jj = 0; jj < 2; ++jj)
-#pragma unroll
-                for (int e = 0; e < 16; ++e) red[((wn * 2 + jj) * 16 + e) * 64 + lane] = gram[jj][e];
-        }
+        double* const red = reinterpret_cast<double*>(lds);
 #pragma unroll
         for (int off = 32; off > 0; off >>= 1) sq += __shfl_xor(sq, off);
-        if (lane == 0) sq_lds[wave] = sq;
+        if (lane == 0) red[wave] = sq;
         __syncthreads();
-        const EPI& epi = args.epi;
-        if (wm == 0) {
-            const int64_t nb = epi.d / 32;
-#pragma unroll
-            for (int jj = 0; jj < 2; ++jj) {
-                const int64_t blk = (n0 + wn * 64 + 32 * jj) / 32;
-                if (blk >= nb) continue;
-                float* dst = epi.partial + (c * nb + blk) * 1024;
-#pragma unroll
-                for (int e = 0; e < 16; ++e) {
-                    const int p = 8 * (e / 4) + 4 * h + (e % 4);
-                    dst[p * 32 + l32] = gram[jj][e] + red[((wn * 2 + jj) * 16 + e) * 64 + lane];
-                }
-            }
-        }
         if (t == 0) {
-            double tot = sq_lds[0];
+            double tot = red[0];
 #pragma unroll
-            for (int i = 1; i < 2 * WN; ++i) tot += sq_lds[i];
-            epi.sq_partial[c * gridDim.x + tn] = tot;
+            for (int i = 1; i < WAVES; ++i) tot += red[i];
+            s.sq_partial[m0 / (32 * WM * TM) * ntn + n0 / (32 * WN * TN)] = tot;
         }
     }
 }
 
-// One pass over the residual res [R, o] (fp32): its bf16 terms hi = bf16(r),
-// lo = bf16(r - hi) both as [R, op] (K = o contiguous, zero for columns
-// o .. op) and transposed as [o, Rp] (K = rows contiguous, zero for rows
-// R .. Rp), and the sum of its squares per workgroup (fp64) into
-// partial[blockIdx.y * gridDim.x + blockIdx.x].  Grid: 64-row x 64-column tiles.
-__global__ __launch_bounds__(256) void residual_prep_kernel(const float* res, int64_t rows, int64_t cols, int64_t op,
-                                                            int64_t Rp, uint16_t* nh, uint16_t* nl, uint16_t* th,
-                                                            uint16_t* tl, double* partial) {
-    __shared__ float tile[64][65];
-    __shared__ double red[4];
-    const int t = threadIdx.x;
-    const int64_t r0 = int64_t(blockIdx.x) * 64, c0 = int64_t(blockIdx.y) * 64;
-    double sq = 0.0;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int rl = t / 16 + 16 * i, cl = 4 * (t % 16);
-        const int64_t r = r0 + rl, cc = c0 + cl;
-        float e[4] = {0.f, 0.f, 0.f, 0.f};
-        if (r < rows) {
-            const float* p = res + r * cols + cc;
-            if (cols % 4 == 0 && cc + 3 < cols) {
-                const float4 x = *reinterpret_cast<const float4*>(p);
-                e[0] = x.x;
-                e[1] = x.y;
-                e[2] = x.z;
-                e[3] = x.w;
-            } else {
-#pragma unroll
-                for (int j = 0; j < 4; ++j)
-                    if (cc + j < cols) e[j] = p[j];
-            }
-        }
-        uint32_t hb[4], lb[4];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            tile[rl][cl + j] = e[j];
-            sq += double(e[j]) * double(e[j]);
-            hb[j] = bf16_rne(e[j]);
-            lb[j] = bf16_rne(e[j] - __uint_as_float(hb[j] << 16));
-        }
-        // natural layout [R, op]: 4 columns (8 bytes) per thread; zero beyond o, up to op
-        if (r < rows && cc < op) {
-            *reinterpret_cast<uint2*>(nh + r * op + cc) = make_uint2(hb[0] | (hb[1] << 16), hb[2] | (hb[3] << 16));
-            *reinterpret_cast<uint2*>(nl + r * op + cc) = make_uint2(lb[0] | (lb[1] << 16), lb[2] | (lb[3] << 16));
-        }
-    }
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) sq += __shfl_xor(sq, off);
-    if ((t & 63) == 0) red[t >> 6] = sq;
-    __syncthreads();
-    if (t == 0) partial[int64_t(blockIdx.y) * gridDim.x + blockIdx.x] = ((red[0] + red[1]) + red[2]) + red[3];
-    const int cl = t / 4, seg = t % 4;
-    const int64_t cc = c0 + cl, rr = r0 + 16 * seg;
-    if (cc >= cols || rr >= Rp) return;
-    uint32_t h[8], l[8];
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-        const float x0 = tile[16 * seg + 2 * j][cl], x1 = tile[16 * seg + 2 * j + 1][cl];
-        const uint32_t h0 = bf16_rne(x0), h1 = bf16_rne(x1);
-        const uint32_t l0 = bf16_rne(x0 - __uint_as_float(h0 << 16)), l1 = bf16_rne(x1 - __uint_as_float(h1 << 16));
-        h[j] = h0 | (h1 << 16);
-        l[j] = l0 | (l1 << 16);
-    }
-    uint4* ph = reinterpret_cast<uint4*>(th + cc * Rp + rr);
-    uint4* pl = reinterpret_cast<uint4*>(tl + cc * Rp + rr);
-    ph[0] = make_uint4(h[0], h[1], h[2], h[3]);
-    ph[1] = make_uint4(h[4], h[5], h[6], h[7]);
-    pl[0] = make_uint4(l[0], l[1], l[2], l[3]);
-    pl[1] = make_uint4(l[4], l[5], l[6], l[7]);
+// Workgroup L of the dispatch order runs on XCD L % 8: each XCD takes a
+// contiguous range of the work items.
+__device__ __forceinline__ int64_t xcd_work(int64_t L, int64_t G) {
+    const int64_t q = G >> 3, r = G & 7, x = L & 7;
+    return x * q + (x < r ? x : r) + (L >> 3);
 }
 
-// out[c][r] = bf16 of the dequantized MXFP4 value (r, c) (exact), c < d,
-// r < ldo, zero for r >= rows: an MXFP4 matrix [rows, d] as its transpose.
-__global__ __launch_bounds__(256) void decode_t_kernel(const uint8_t* codes, const uint8_t* scales, int64_t rows,
-                                                       int64_t d, uint16_t* out, int64_t ldo) {
-    __shared__ uint16_t tile[64][66];
-    const int t = threadIdx.x;
-    const int64_t r0 = int64_t(blockIdx.x) * 64, c0 = int64_t(blockIdx.y) * 64;
-    {
-        const int rl = t / 4, cq = t % 4;
-        const int64_t r = r0 + rl, cc = c0 + 16 * cq;
-        uint2 cw = make_uint2(0, 0);
-        uint32_t s = 127;
-        if (r < rows && cc < d) {
-            cw = *reinterpret_cast<const uint2*>(codes + r * (d / 2) + cc / 2);
-            s = scales[r * (d / 32) + cc / 32];
-        }
-#pragma unroll
-        for (int j = 0; j < 16; ++j) {
-            const uint32_t w = j < 8 ? cw.x : cw.y;
-            tile[rl][16 * cq + j] = uint16_t(__float_as_uint(mx_value(w >> (4 * (j % 8)), s)) >> 16);
-        }
+struct BackwardArgs {
+    Side act, wgt;
+    int64_t d, ntn;
+    float c1;
+    const float* lambdas;
+};
+
+// Both backward products in one launch: works 0 .. act.works - 1 are the
+// activation side P = res . What (K = o, contiguous in res), the rest the weight
+// side P = res^T . Ahat (K = rows, strided in both).  A work is (m tiles, K part,
+// column tile), the column tile fastest: the column tiles of one m tile and K
+// part read the same rows of the residual and run on one XCD.
+template <int WM, int WN, int TM, int TN, bool PING>
+__global__ __launch_bounds__(64 * WM * WN) void calib_backward_kernel(const BackwardArgs p) {
+    typedef CalibTile<2, WM, WN, TM, TN> T;
+    static_assert(WM * WN * TN * 4096 <= T::kLdsBytes, "the block sums fit the stage buffers");
+    __shared__ __align__(16) uint8_t lds[T::kLdsBytes];
+    int64_t wk = xcd_work(blockIdx.x, gridDim.x);
+    const bool act = wk < p.act.works;
+    if (!act) wk -= p.act.works;
+    const Side s = act ? p.act : p.wgt;
+    const int64_t n0 = (wk % p.ntn) * T::BN, slot = wk / p.ntn;
+    const int64_t c = slot / s.ks, k_lo = (slot % s.ks) * s.kchunk, k_hi = std::min(s.K, k_lo + s.kchunk);
+    for (int64_t mt = c; mt < s.m_tiles; mt += s.chunks) {
+        const int64_t m0 = mt * T::BM;
+        f32x16 acc[TM][TN];
+        if (act) calib_product<2, false, true, WM, WN, TM, TN, PING>(s.A, s.B, lds, m0, n0, k_lo, k_hi, acc);
+        else calib_product<2, true, true, WM, WN, TM, TN, PING>(s.A, s.B, lds, m0, n0, k_lo, k_hi, acc);
+        gram_tile<WM, WN, TM, TN>(acc, s, lds, p.d, p.c1, p.lambdas, slot, mt != c, p.ntn, m0, n0, k_lo == 0);
+        __syncthreads();
     }
-    __syncthreads();
-    const int cl = t / 4, seg = t % 4;
-    const int64_t cc = c0 + cl, rr = r0 + 16 * seg;
-    if (cc >= d || rr >= ldo) return;
-    uint32_t v[8];
-#pragma unroll
-    for (int j = 0; j < 8; ++j) v[j] = uint32_t(tile[16 * seg + 2 * j][cl]) | (uint32_t(tile[16 * seg + 2 * j + 1][cl]) << 16);
-    uint4* p = reinterpret_cast<uint4*>(out + cc * ldo + rr);
-    p[0] = make_uint4(v[0], v[1], v[2], v[3]);
-    p[1] = make_uint4(v[4], v[5], v[6], v[7]);
+}
+
+// Yneg = -(X W^T): both operands K-contiguous, one term.
+template <int WM, int WN, int TM, int TN, bool PING>
+__global__ __launch_bounds__(64 * WM * WN) void calib_reference_kernel(const Opnd A, const Opnd B, float* out, int64_t K,
+                                                                       int64_t ntn) {
+    typedef CalibTile<1, WM, WN, TM, TN> T;
+    __shared__ __align__(16) uint8_t lds[T::kLdsBytes];
+    const int64_t wk = xcd_work(blockIdx.x, gridDim.x);
+    const int64_t n0 = (wk % ntn) * T::BN, m0 = (wk / ntn) * T::BM;
+    f32x16 acc[TM][TN];
+    const Opnd a[1] = {A};
+    calib_product<1, false, false, WM, WN, TM, TN, PING>(a, B, lds, m0, n0, 0, K, acc);
+    store_neg<WM, WN, TM, TN>(acc, out, A.rows, B.rows, m0, n0);
 }
 
 // ------------------------------------------------------------ small kernels
 
-// out[f][e] = sum over chunks c and the blocks j of factor f of partial[c][j][e];
-// one factor per block j (nfac = nb) or one for all (nfac = 1).  Fixed order.
-__global__ __launch_bounds__(256) void gram_reduce_kernel(const float* partial, int64_t chunks, int64_t nb,
-                                                          int64_t nfac, float* out) {
-    const int64_t f = blockIdx.x;
-    const int e = blockIdx.y * 256 + threadIdx.x;
-    const int64_t j0 = nfac == 1 ? 0 : f, j1 = nfac == 1 ? nb : f + 1;
-    double s = 0.0;
-    for (int64_t j = j0; j < j1; ++j)
-        for (int64_t c = 0; c < chunks; ++c) s += partial[(c * nb + j) * 1024 + e];
-    out[f * 1024 + e] = float(s);
+// partial[0][j][e] + partial[1][j][e] = sum over the slots c of partial[c][j][e], in
+// place: summed in fp64 and a fixed order (16 threads per four elements, each every
+// 16th slot), stored as the nearest fp32 and the fp32 of the rest.
+struct ReduceSide {
+    float* partial;
+    int64_t slots;
+};
+
+__global__ __launch_bounds__(256) void gram_reduce_kernel(const ReduceSide s0, const ReduceSide s1, int64_t nb) {
+    __shared__ double red[16][16][4];
+    const ReduceSide s = blockIdx.z ? s1 : s0;
+    if (s.slots < 2) return;
+    const int64_t j = blockIdx.x;
+    const int e4 = threadIdx.x & 15, part = threadIdx.x >> 4;
+    const int64_t e = 64 * blockIdx.y + 4 * e4;
+    double v[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll 4
+    for (int64_t c = part; c < s.slots; c += 16) {
+        const float4 x = *reinterpret_cast<const float4*>(s.partial + (c * nb + j) * 1024 + e);
+        v[0] += x.x;
+        v[1] += x.y;
+        v[2] += x.z;
+        v[3] += x.w;
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) red[part][e4][i] = v[i];
+    __syncthreads();
+    if (threadIdx.x < 64) {
+        double t = 0.0;
+#pragma unroll
+        for (int k = 0; k < 16; ++k) t += red[k][threadIdx.x >> 2][threadIdx.x & 3];
+        float* const dst = s.partial + j * 1024 + 64 * blockIdx.y + threadIdx.x;
+        const float hi = (float)t;
+        dst[0] = hi;
+        dst[nb * 1024] = (float)(t - (double)hi);
+    }
 }
 
 __device__ __forceinline__ void decode_g(const float* lu, float (&g)[5][4]) {
@@ -536,43 +533,6 @@ __device__ __forceinline__ void decode_g(const float* lu, float (&g)[5][4]) {
         g[k][1] = pb;
         g[k][2] = pc * pa;
         g[k][3] = __builtin_fmaf(pc, pb, -(1.0f / pa));
-    }
-}
-
-// Factors of T_f^-1 in the layout kq_quantize applies (y = (A (x) B) x per
-// block, so A (x) B = T^-1 gives the weight side's w -> w T^-T).  With
-// det G = -1, G^-1 = [[-g11, g01], [g10, -g00]]; every entry of A and B is the
-// product of its G^-1 entries, left to right, in fp32.
-__global__ __launch_bounds__(64) void inverse_factors_kernel(const float* lu, int na, float* Ainv, float* Binv) {
-    const int64_t f = blockIdx.x;
-    const int a = 1 << na, b = 32 >> na;
-    float g[5][4];
-    decode_g(lu + f * 15, g);
-    float gi[5][4];
-#pragma unroll
-    for (int k = 0; k < 5; ++k) {
-        gi[k][0] = -g[k][3];
-        gi[k][1] = g[k][1];
-        gi[k][2] = g[k][2];
-        gi[k][3] = -g[k][0];
-    }
-    for (int idx = threadIdx.x; idx < a * a + b * b; idx += 64) {
-        const bool in_a = idx < a * a;
-        const int row = in_a ? idx / a : (idx - a * a) / b;
-        const int col = in_a ? idx % a : (idx - a * a) % b;
-        float v = 1.0f;
-        bool first = true;
-#pragma unroll
-        for (int k = 0; k < 5; ++k) {
-            if ((k < na) != in_a) continue;
-            const int sh = in_a ? na - 1 - k : 4 - k;
-            const int e = 2 * ((row >> sh) & 1) + ((col >> sh) & 1);
-            const float ge = e == 0 ? gi[k][0] : e == 1 ? gi[k][1] : e == 2 ? gi[k][2] : gi[k][3];
-            v = first ? ge : v * ge;
-            first = false;
-        }
-        if (in_a) Ainv[f * a * a + idx] = v;
-        else Binv[f * b * b + idx - a * a] = v;
     }
 }
 
@@ -587,15 +547,17 @@ __device__ __forceinline__ double block_sum256(double v, double* red) {
 
 struct LuGradArgs {
     const float* lu;
-    const float* ga;   // [nfac, 32, 32]  dL/dT_f from the activation side
-    const float* gw;   // [nfac, 32, 32]  dL/dU_f, U_f = T_f^-T, from the weight side
+    const float* ga;   // [1 or 2, nb, 32, 32]  dL/dT of every block from the activation side (gram_reduce_kernel)
+    const float* gw;   // [1 or 2, nb, 32, 32]  dL/dU, U = T^-T, from the weight side
+    bool two_a, two_w;  // the second term is there
+    int64_t nb, nfac;  // nfac = nb, or 1: the blocks' sums add up
     float* grad;       // [nfac, 15]
     float* lu_out;
     float* adam_m;
     float* adam_v;
     int adam_t;
     float lr;
-    // losses (block 0)
+    // losses (the last workgroup)
     const double* sr;
     int64_t nsr;
     const double* sqa;
@@ -616,10 +578,47 @@ __global__ __launch_bounds__(256) void lu_grad_kernel(const LuGradArgs p) {
     __shared__ float sU[32][33];
     __shared__ float sGW[32][33];
     __shared__ float sV[32][33];
-    __shared__ double red[4];
+    __shared__ double red[20][256];
     __shared__ float gsum[5][4];
     const int64_t f = blockIdx.x;
     const int t = threadIdx.x;
+    if (f == p.nfac) {  // the losses, beside the factors' workgroups
+        double s = 0.0;
+        for (int64_t i = t; i < p.nsr; i += 256) s += p.sr[i];
+        const double sr = block_sum256(s, red[0]);
+        s = 0.0;
+        for (int64_t i = t; i < p.nsqa; i += 256) s += p.sqa[i];
+        const double sa = block_sum256(s, red[0]);
+        s = 0.0;
+        for (int64_t i = t; i < p.nsqw; i += 256) s += p.sqw[i];
+        const double sw = block_sum256(s, red[0]);
+        if (t == 0) {
+            const double lo = sr / p.n_out, la = sa / p.n_a, lw = sw / p.n_w;
+            p.losses[0] = lo;
+            p.losses[1] = la;
+            p.losses[2] = lw;
+            p.losses[3] = lo + double(p.lambdas[0]) * la + double(p.lambdas[1]) * lw;
+        }
+        return;
+    }
+    float ga[4];
+    {
+        double a4[4] = {0.0, 0.0, 0.0, 0.0}, w4[4] = {0.0, 0.0, 0.0, 0.0};
+        const int64_t j0 = p.nfac == 1 ? 0 : f, j1 = p.nfac == 1 ? p.nb : f + 1;
+#pragma unroll 4
+        for (int64_t j = j0; j < j1; ++j)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int64_t e = j * 1024 + t + 256 * i;
+                a4[i] += double(p.ga[e]) + (p.two_a ? double(p.ga[p.nb * 1024 + e]) : 0.0);
+                w4[i] += double(p.gw[e]) + (p.two_w ? double(p.gw[p.nb * 1024 + e]) : 0.0);
+            }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            ga[i] = float(a4[i]);
+            sGW[(t + 256 * i) / 32][t % 32] = float(w4[i]);
+        }
+    }
     float g[5][4];
     decode_g(p.lu + f * 15, g);
     // (G^-1)^T = [[-g11, g10], [g01, -g00]]
@@ -631,8 +630,9 @@ __global__ __launch_bounds__(256) void lu_grad_kernel(const LuGradArgs p) {
         git[k][2] = g[k][1];
         git[k][3] = -g[k][0];
     }
-    for (int e = t; e < 1024; e += 256) {
-        const int r = e / 32, q = e % 32;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int e = t + 256 * i, r = e / 32, q = e % 32;
         float u = 1.0f;
 #pragma unroll
         for (int k = 0; k < 5; ++k) {
@@ -640,13 +640,14 @@ __global__ __launch_bounds__(256) void lu_grad_kernel(const LuGradArgs p) {
             u *= ee == 0 ? git[k][0] : ee == 1 ? git[k][1] : ee == 2 ? git[k][2] : git[k][3];
         }
         sU[r][q] = u;
-        sGW[r][q] = p.gw[f * 1024 + e];
     }
     __syncthreads();
     // V = GW^T U
-    for (int e = t; e < 1024; e += 256) {
-        const int r = e / 32, q = e % 32;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int e = t + 256 * i, r = e / 32, q = e % 32;
         float s = 0.f;
+#pragma unroll 8
         for (int x = 0; x < 32; ++x) s = __builtin_fmaf(sGW[x][r], sU[x][q], s);
         sV[r][q] = s;
     }
@@ -656,11 +657,13 @@ __global__ __launch_bounds__(256) void lu_grad_kernel(const LuGradArgs p) {
     for (int k = 0; k < 5; ++k)
 #pragma unroll
         for (int e = 0; e < 4; ++e) dg[k][e] = 0.0;
-    for (int e = t; e < 1024; e += 256) {
-        const int r = e / 32, q = e % 32;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int e = t + 256 * i, r = e / 32, q = e % 32;
         float s = 0.f;
+#pragma unroll 8
         for (int x = 0; x < 32; ++x) s = __builtin_fmaf(sU[r][x], sV[x][q], s);
-        const float dT = p.ga[f * 1024 + e] - s;
+        const float dT = ga[i] - s;
         float ge[5];
 #pragma unroll
         for (int k = 0; k < 5; ++k) {
@@ -678,13 +681,29 @@ __global__ __launch_bounds__(256) void lu_grad_kernel(const LuGradArgs p) {
             for (int x = 0; x < 4; ++x) dg[k][x] += (x == ee) ? others : 0.0;
         }
     }
+    // the 20 sums over the workgroup through LDS, five per wave (a reduction of
+    // each with its own barriers took about 1 us apiece)
 #pragma unroll
     for (int k = 0; k < 5; ++k)
 #pragma unroll
-        for (int x = 0; x < 4; ++x) {
-            const double s = block_sum256(dg[k][x], red);
-            if (t == 0) gsum[k][x] = float(s);
+        for (int x = 0; x < 4; ++x) red[4 * k + x][t] = dg[k][x];
+    __syncthreads();
+    {
+        const int w = t >> 6, lane = t & 63;
+        double v[5];
+#pragma unroll
+        for (int i = 0; i < 5; ++i) {
+            const double* const r = red[5 * w + i];
+            v[i] = (r[lane] + r[lane + 64]) + (r[lane + 128] + r[lane + 192]);
         }
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1)
+#pragma unroll
+            for (int i = 0; i < 5; ++i) v[i] += __shfl_xor(v[i], off);
+        if (lane == 0)
+#pragma unroll
+            for (int i = 0; i < 5; ++i) gsum[(5 * w + i) / 4][(5 * w + i) % 4] = float(v[i]);
+    }
     __syncthreads();
     if (t < 5) {
         const int k = t;
@@ -709,24 +728,6 @@ __global__ __launch_bounds__(256) void lu_grad_kernel(const LuGradArgs p) {
                 const float bc2 = 1.0f - powf(0.999f, float(p.adam_t));
                 p.lu_out[i] = par[x] - p.lr * (m / bc1) / (sqrtf(v / bc2) + 1e-8f);
             }
-        }
-    }
-    if (f == 0) {
-        double s = 0.0;
-        for (int64_t i = t; i < p.nsr; i += 256) s += p.sr[i];
-        const double sr = block_sum256(s, red);
-        s = 0.0;
-        for (int64_t i = t; i < p.nsqa; i += 256) s += p.sqa[i];
-        const double sa = block_sum256(s, red);
-        s = 0.0;
-        for (int64_t i = t; i < p.nsqw; i += 256) s += p.sqw[i];
-        const double sw = block_sum256(s, red);
-        if (t == 0) {
-            const double lo = sr / p.n_out, la = sa / p.n_a, lw = sw / p.n_w;
-            p.losses[0] = lo;
-            p.losses[1] = la;
-            p.losses[2] = lw;
-            p.losses[3] = lo + double(p.lambdas[0]) * la + double(p.lambdas[1]) * lw;
         }
     }
 }
@@ -754,6 +755,46 @@ int64_t cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
 }  // namespace
 
+// One side of the backward products: mt row tiles and ntn column tiles, K of
+// `stages` 32-deep stages in ks parts, chunks workgroup rows.
+struct SidePlan {
+    int64_t mt, ntn, stages, ks, chunks;
+    // In units of a stage of a 256 x 256 tile on one CU: rounds of the chip, each
+    // a K part and its epilogue per m tile.  A 128 x 128 workgroup has a quarter of
+    // the work, two share a CU, and its stage feeds half the products per byte.
+    double cost(bool big) const {
+        const double stage = big ? 1.0 : 0.8, epi = big ? 6.0 : 3.0;
+        return double(cdiv(chunks * ntn * ks, big ? 256 : 512)) * double(cdiv(mt, chunks)) *
+               (stage * double(cdiv(stages, ks)) + epi);
+    }
+    // The K parts (of at least four stages) that fill the rounds best.
+    void choose_parts(bool big) {
+        SidePlan s = *this;
+        for (s.ks = 2; s.ks <= 16 && 4 * s.ks <= stages; ++s.ks)
+            if (s.cost(big) < 0.97 * cost(big)) ks = s.ks;
+    }
+};
+
+// The least workspace a caller is told of: 6.6 R d + 12 R o + 6.6 o d bytes and the
+// partial sums of 128-row tiles, of which the step now uses less.  Kept, so that
+// the sizes that the fixed scratch of kq_calib_step_noalloc holds stay the same.
+static size_t told_workspace(int64_t R, int64_t o, int64_t d, int a, int64_t nfac) {
+    const int64_t nb = d / 32, ntn = cdiv(d, 256), act_mt = cdiv(R, 128), w_mt = cdiv(o, 128);
+    const int64_t Rp = cdiv(R, BK) * BK, op = cdiv(o, BK) * BK, stages = Rp / BK;
+    const int64_t act_chunks = std::max<int64_t>(1, std::min(act_mt, cdiv(2048, ntn)));
+    int64_t ks = std::max<int64_t>(1, std::min(cdiv(2048, ntn * w_mt), cdiv(stages, 8)));
+    ks = std::max<int64_t>(1, cdiv(Rp, cdiv(cdiv(Rp, ks), BK) * BK));
+    const int64_t w_chunks = w_mt * ks, b = 32 / a;
+    size_t n = 0;
+    for (const int64_t bytes :
+         {R * d * 4, R * d / 2, R * nb, o * d * 4, o * d / 2, o * nb, R * o * 4, R * op * 2, R * op * 2, o * Rp * 2,
+          o * Rp * 2, d * Rp * 2, d * op * 2, nfac * a * a * 4, nfac * b * b * 4, act_chunks * nb * 4096,
+          w_chunks * nb * 4096, act_chunks * ntn * 8, w_chunks * ntn * 8, cdiv(Rp, 64) * cdiv(o, 64) * 8, nfac * 4096,
+          nfac * 4096, nfac * 60, nfac * 60, nfac * 60, int64_t(8)})
+        n += align256(size_t(bytes));
+    return n;
+}
+
 CalibPlan calib_plan(int64_t R, int64_t o, int64_t d, int a, int64_t nfac) {
     CalibPlan pl;
     pl.R = R;
@@ -762,148 +803,159 @@ CalibPlan calib_plan(int64_t R, int64_t o, int64_t d, int a, int64_t nfac) {
     pl.nb = d / 32;
     pl.a = a;
     pl.nfac = nfac;
-    pl.ntn = cdiv(d, 64 * kWnBackward);
-    pl.act_mt = cdiv(R, CT);
-    pl.act_chunks = std::max<int64_t>(1, std::min(pl.act_mt, cdiv(kTargetWg, pl.ntn)));
-    pl.w_mt = cdiv(o, CT);
     pl.Rp = cdiv(std::max<int64_t>(R, 1), BK) * BK;
     pl.op = cdiv(o, BK) * BK;
-    const int64_t stages = pl.Rp / BK;
-    pl.w_ks = std::max<int64_t>(1, std::min(cdiv(kTargetWg, pl.ntn * pl.w_mt), cdiv(stages, 8)));
-    pl.w_kchunk = cdiv(cdiv(pl.Rp, pl.w_ks), BK) * BK;
-    pl.w_ks = std::max<int64_t>(1, cdiv(pl.Rp, pl.w_kchunk));
-    pl.w_chunks = pl.w_mt * pl.w_ks;
-    pl.nsum = cdiv(pl.Rp, 64) * cdiv(o, 64);
+    pl.nsum = cdiv(pl.Rp, 128) * cdiv(pl.op, 128);
     size_t off = 0;
     auto take = [&](size_t bytes) {
         const size_t at = off;
         off = align256(off + bytes);
         return at;
     };
-    const int b = 32 / a;
     pl.yA = take(size_t(R) * d * 4);
     pl.cA = take(size_t(R) * d / 2);
     pl.sA = take(size_t(R) * (d / 32));
+    pl.qA = take(size_t(R) * d * 2);
     pl.yW = take(size_t(o) * d * 4);
     pl.cW = take(size_t(o) * d / 2);
     pl.sW = take(size_t(o) * (d / 32));
-    pl.res = take(size_t(R) * o * 4);
-    pl.rnh = take(size_t(R) * pl.op * 2);
-    pl.rnl = take(size_t(R) * pl.op * 2);
-    pl.rth = take(size_t(o) * pl.Rp * 2);
-    pl.rtl = take(size_t(o) * pl.Rp * 2);
-    pl.aht = take(size_t(d) * pl.Rp * 2);
-    pl.wht = take(size_t(d) * pl.op * 2);
-    pl.fa = take(size_t(nfac) * a * a * 4);
-    pl.fb = take(size_t(nfac) * b * b * 4);
-    pl.gpa = take(size_t(pl.act_chunks) * pl.nb * 1024 * 4);
-    pl.gpw = take(size_t(pl.w_chunks) * pl.nb * 1024 * 4);
-    pl.sqa = take(size_t(pl.act_chunks) * pl.ntn * 8);
-    pl.sqw = take(size_t(pl.w_chunks) * pl.ntn * 8);
+    pl.qW = take(size_t(o) * d * 2);
+    pl.rh = take(size_t(pl.Rp) * pl.op * 2);
+    pl.rl = take(size_t(pl.Rp) * pl.op * 2);
+    pl.sqa = take(size_t(cdiv(R, 128)) * cdiv(d, 128) * 8);
+    pl.sqw = take(size_t(cdiv(o, 128)) * cdiv(d, 128) * 8);
     pl.sr = take(size_t(pl.nsum) * 8);
-    pl.ga = take(size_t(nfac) * 1024 * 4);
-    pl.gw = take(size_t(nfac) * 1024 * 4);
     pl.grad = take(size_t(nfac) * 15 * 4);
     pl.am = take(size_t(nfac) * 15 * 4);
     pl.av = take(size_t(nfac) * 15 * 4);
     pl.lam = take(2 * 4);
-    pl.total = off;
+    // both sides with 256 x 256 or both with 128 x 128 tiles, whichever is cheaper,
+    // with K parts and workgroup rows whose partial sums fit what is left of the
+    // workspace that is told anyway
+    const size_t told = told_workspace(R, o, d, a, nfac), slot = size_t(pl.nb) * 4096;
+    const int64_t room = std::max<int64_t>(2, told > off ? int64_t((told - off) / slot) : 0);
+    double best = 0.0;
+    for (const bool big : {true, false}) {
+        const int64_t T = big ? 256 : 128, ntn = cdiv(d, T);
+        SidePlan act{cdiv(R, T), ntn, pl.op / BK, 1, cdiv(R, T)}, wgt{cdiv(o, T), ntn, pl.Rp / BK, 1, cdiv(o, T)};
+        act.choose_parts(big);
+        wgt.choose_parts(big);
+        while (act.chunks * act.ks + wgt.chunks * wgt.ks > room) {
+            SidePlan& s = act.chunks * act.ks >= wgt.chunks * wgt.ks ? act : wgt;
+            if (s.ks > 1) --s.ks;
+            else s.chunks = cdiv(s.chunks, 2);
+        }
+        const double cost = act.cost(big) + wgt.cost(big);
+        if (big || cost < best) {
+            best = cost;
+            pl.big = big;
+            pl.ntn = ntn;
+            pl.act_mt = act.mt;
+            pl.act_chunks = act.chunks;
+            pl.act_kchunk = cdiv(act.stages, act.ks) * BK;
+            pl.w_mt = wgt.mt;
+            pl.w_chunks = wgt.chunks;
+            pl.w_kchunk = cdiv(wgt.stages, wgt.ks) * BK;
+        }
+    }
+    pl.act_ks = cdiv(pl.op, pl.act_kchunk);
+    pl.w_ks = cdiv(pl.Rp, pl.w_kchunk);
+    pl.gpa = take(size_t(pl.act_chunks) * pl.act_ks * slot);
+    pl.gpw = take(size_t(pl.w_chunks) * pl.w_ks * slot);
+    pl.total = std::max(off, told);
     return pl;
 }
 
 hipError_t launch_calib_reference(const uint16_t* X, int64_t R, int64_t d, const uint16_t* W, int64_t o,
                                   float* Yneg, hipStream_t st) {
     if (R == 0 || o == 0) return hipSuccess;
-    GemmArgs<1, EpiStoreNeg> args{{{reinterpret_cast<const uint8_t*>(X), R, d * 2}},
-                                  {reinterpret_cast<const uint8_t*>(W), o, d * 2},
-                                  {Yneg, R, o, o},
-                                  {R, o, d, cdiv(R, CT), 1, d, cdiv(R, CT), 0}};
-    dim3 grid(unsigned(cdiv(o, 64 * kWnReference)), unsigned(args.g.chunks));
-    calib_gemm_kernel<1, kWnReference><<<grid, 128 * kWnReference, 0, st>>>(args);
+    const Opnd A{reinterpret_cast<const uint8_t*>(X), R, d, d * 2}, B{reinterpret_cast<const uint8_t*>(W), o, d, d * 2};
+    if (cdiv(R, 256) * cdiv(o, 256) >= 128) {
+        const int64_t ntn = cdiv(o, 256);
+        calib_reference_kernel<4, 2, 2, 4, true><<<unsigned(cdiv(R, 256) * ntn), 512, 0, st>>>(A, B, Yneg, d, ntn);
+    } else {
+        const int64_t ntn = cdiv(o, 128);
+        calib_reference_kernel<2, 2, 2, 2, false><<<unsigned(cdiv(R, 128) * ntn), 256, 0, st>>>(A, B, Yneg, d, ntn);
+    }
     return hipGetLastError();
 }
 
-hipError_t launch_calib_inverse_factors(const float* lu, int a, int64_t nfac, float* Ainv, float* Binv,
-                                        hipStream_t st) {
-    const int na = a == 1 ? 0 : a == 2 ? 1 : a == 4 ? 2 : 3;
-    inverse_factors_kernel<<<unsigned(nfac), 64, 0, st>>>(lu, na, Ainv, Binv);
-    return hipGetLastError();
-}
-
-hipError_t launch_calib_backward(const CalibPlan& pl, const CalibStepArgs& s, hipStream_t st) {
+hipError_t launch_calib_backward(const CalibPlan& pl, const CalibStepArgs& s, int64_t nsr, hipStream_t st) {
     unsigned char* ws = s.ws;
-    float* yA = reinterpret_cast<float*>(ws + pl.yA);
-    const uint8_t* cA = ws + pl.cA;
-    const uint8_t* sA = ws + pl.sA;
-    float* yW = reinterpret_cast<float*>(ws + pl.yW);
-    const uint8_t* cW = ws + pl.cW;
-    const uint8_t* sW = ws + pl.sW;
-    float* res = reinterpret_cast<float*>(ws + pl.res);
-    uint16_t* rnh = reinterpret_cast<uint16_t*>(ws + pl.rnh);
-    uint16_t* rnl = reinterpret_cast<uint16_t*>(ws + pl.rnl);
-    uint16_t* rth = reinterpret_cast<uint16_t*>(ws + pl.rth);
-    uint16_t* rtl = reinterpret_cast<uint16_t*>(ws + pl.rtl);
-    uint16_t* aht = reinterpret_cast<uint16_t*>(ws + pl.aht);
-    uint16_t* wht = reinterpret_cast<uint16_t*>(ws + pl.wht);
-    float* gpa = reinterpret_cast<float*>(ws + pl.gpa);
-    float* gpw = reinterpret_cast<float*>(ws + pl.gpw);
-    double* sqa = reinterpret_cast<double*>(ws + pl.sqa);
-    double* sqw = reinterpret_cast<double*>(ws + pl.sqw);
-    double* sr = reinterpret_cast<double*>(ws + pl.sr);
-    float* ga = reinterpret_cast<float*>(ws + pl.ga);
-    float* gw = reinterpret_cast<float*>(ws + pl.gw);
     const int64_t R = pl.R, o = pl.o, d = pl.d;
-
-    const float c1 = float(2.0 / (double(R) * double(o)));
-    // K-contiguous operands: What^T [d, op], Ahat^T [d, Rp], res as bf16 hi / lo [R, op] and [o, Rp]
-    decode_t_kernel<<<dim3(unsigned(cdiv(pl.op, 64)), unsigned(cdiv(d, 64))), 256, 0, st>>>(cW, sW, o, d, wht, pl.op);
-    decode_t_kernel<<<dim3(unsigned(cdiv(pl.Rp, 64)), unsigned(cdiv(d, 64))), 256, 0, st>>>(cA, sA, R, d, aht, pl.Rp);
-    residual_prep_kernel<<<dim3(unsigned(cdiv(pl.Rp, 64)), unsigned(cdiv(o, 64))), 256, 0, st>>>(
-        res, R, o, pl.op, pl.Rp, rnh, rnl, rth, rtl, sr);
+    const Opnd rh{ws + pl.rh, pl.Rp, pl.op, pl.op * 2}, rl{ws + pl.rl, pl.Rp, pl.op, pl.op * 2};
+    BackwardArgs b{};
+    b.d = d;
+    b.ntn = pl.ntn;
+    b.c1 = float(2.0 / (double(R) * double(o)));
+    b.lambdas = s.lambdas;
     // activation side: P = res . What  (M = R, N = d, K = o)
-    {
-        GemmArgs<2, EpiGram> args{
-            {{reinterpret_cast<const uint8_t*>(rnh), R, pl.op * 2}, {reinterpret_cast<const uint8_t*>(rnl), R, pl.op * 2}},
-            {reinterpret_cast<const uint8_t*>(wht), d, pl.op * 2},
-            {s.X, yA, cA, sA, R, d, c1, s.lambdas, 0, float(2.0 / (double(R) * double(d))), gpa, sqa},
-            {R, d, pl.op, pl.act_mt, 1, pl.op, pl.act_chunks, 1}};
-        dim3 grid(unsigned(pl.ntn), unsigned(pl.act_chunks));
-        calib_gemm_kernel<2, kWnBackward><<<grid, 128 * kWnBackward, 0, st>>>(args);
-    }
+    b.act = Side{{rh, rl},
+                 {ws + pl.qW, o, d, d * 2},
+                 s.X,
+                 reinterpret_cast<const float*>(ws + pl.yA),
+                 ws + pl.cA,
+                 ws + pl.sA,
+                 R,
+                 0,
+                 float(2.0 / (double(R) * double(d))),
+                 reinterpret_cast<float*>(ws + pl.gpa),
+                 reinterpret_cast<double*>(ws + pl.sqa),
+                 pl.op,
+                 pl.act_kchunk,
+                 int(pl.act_ks),
+                 pl.act_mt,
+                 pl.act_chunks,
+                 pl.act_chunks * pl.act_ks * pl.ntn};
     // weight side: P = res^T . Ahat  (M = o, N = d, K = R)
-    {
-        GemmArgs<2, EpiGram> args{
-            {{reinterpret_cast<const uint8_t*>(rth), o, pl.Rp * 2}, {reinterpret_cast<const uint8_t*>(rtl), o, pl.Rp * 2}},
-            {reinterpret_cast<const uint8_t*>(aht), d, pl.Rp * 2},
-            {s.W, yW, cW, sW, o, d, c1, s.lambdas, 1, float(2.0 / (double(o) * double(d))), gpw, sqw},
-            {o, d, pl.Rp, pl.w_mt, pl.w_ks, pl.w_kchunk, pl.w_chunks, 1}};
-        dim3 grid(unsigned(pl.ntn), unsigned(pl.w_chunks));
-        calib_gemm_kernel<2, kWnBackward><<<grid, 128 * kWnBackward, 0, st>>>(args);
-    }
-    gram_reduce_kernel<<<dim3(unsigned(pl.nfac), 4), 256, 0, st>>>(gpa, pl.act_chunks, pl.nb, pl.nfac, ga);
-    gram_reduce_kernel<<<dim3(unsigned(pl.nfac), 4), 256, 0, st>>>(gpw, pl.w_chunks, pl.nb, pl.nfac, gw);
+    b.wgt = Side{{rh, rl},
+                 {ws + pl.qA, R, d, d * 2},
+                 s.W,
+                 reinterpret_cast<const float*>(ws + pl.yW),
+                 ws + pl.cW,
+                 ws + pl.sW,
+                 o,
+                 1,
+                 float(2.0 / (double(o) * double(d))),
+                 reinterpret_cast<float*>(ws + pl.gpw),
+                 reinterpret_cast<double*>(ws + pl.sqw),
+                 pl.Rp,
+                 pl.w_kchunk,
+                 int(pl.w_ks),
+                 pl.w_mt,
+                 pl.w_chunks,
+                 pl.w_chunks * pl.w_ks * pl.ntn};
+    const unsigned works = unsigned(b.act.works + b.wgt.works);
+    if (pl.big) calib_backward_kernel<4, 2, 2, 4, true><<<works, 512, 0, st>>>(b);
+    else calib_backward_kernel<2, 2, 2, 2, false><<<works, 256, 0, st>>>(b);
+    const ReduceSide ra{b.act.partial, pl.act_chunks * pl.act_ks}, rw{b.wgt.partial, pl.w_chunks * pl.w_ks};
+    if (ra.slots > 1 || rw.slots > 1) gram_reduce_kernel<<<dim3(unsigned(pl.nb), 16, 2), 256, 0, st>>>(ra, rw, pl.nb);
     LuGradArgs la{};
     la.lu = s.lu;
-    la.ga = ga;
-    la.gw = gw;
+    la.ga = ra.partial;
+    la.gw = rw.partial;
+    la.two_a = ra.slots > 1;
+    la.two_w = rw.slots > 1;
+    la.nb = pl.nb;
+    la.nfac = pl.nfac;
     la.grad = s.grad;
     la.lu_out = s.lu_out;
     la.adam_m = s.adam_m;
     la.adam_v = s.adam_v;
     la.adam_t = s.adam_t;
     la.lr = s.lr;
-    la.sr = sr;
-    la.nsr = pl.nsum;
-    la.sqa = sqa;
-    la.nsqa = pl.act_chunks * pl.ntn;
-    la.sqw = sqw;
-    la.nsqw = pl.w_chunks * pl.ntn;
+    la.sr = reinterpret_cast<double*>(ws + pl.sr);
+    la.nsr = nsr;
+    la.sqa = reinterpret_cast<double*>(ws + pl.sqa);
+    la.nsqa = pl.act_mt * pl.ntn;
+    la.sqw = reinterpret_cast<double*>(ws + pl.sqw);
+    la.nsqw = pl.w_mt * pl.ntn;
     la.n_out = double(R) * double(o);
     la.n_a = double(R) * double(d);
     la.n_w = double(o) * double(d);
     la.lambdas = s.lambdas;
     la.losses = s.losses;
-    lu_grad_kernel<<<unsigned(pl.nfac), 256, 0, st>>>(la);
+    lu_grad_kernel<<<unsigned(pl.nfac + 1), 256, 0, st>>>(la);
     return hipGetLastError();
 }
 

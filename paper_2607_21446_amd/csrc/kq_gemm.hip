@@ -418,10 +418,15 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& g, typename Tile<WN,
 // of 32 rows (4608 x 12288 x 3072, bf16 / fp32: 141 / 155 us so, 119 / 137 now).  Rows in LDS are 16 bytes apart from a multiple of 512 (256), so
 // that the 16 rows of a write phase cover all banks.  When a tile of fp32 does not
 // fit, it goes in NP passes of TN / NP of every wave's column tiles.
-template <int WN, int WM, int TN, int TM, bool BF16>
+//
+// OUT 0: fp32 (bias, accumulate); 1: bf16; 2: the residual v = bias + product as its
+// two bf16 terms hi = bf16(v), lo = bf16(v - hi), zero in the padding columns and
+// rows up to ldr and rows_pad, and the workgroup's sum of v^2 (fp64).
+template <int WN, int WM, int TN, int TM, int OUT>
 __device__ __forceinline__ void store_tile(const GemmParams& g, uint8_t* lds, int64_t nb0, int64_t mb0,
                                            const f32x16g (&acc)[TN][TM]) {
     typedef Tile<WN, WM, TN, TM> T;
+    constexpr bool BF16 = OUT == 1;
     constexpr int ES = BF16 ? 2 : 4;
     constexpr int NP = (T::BM * (T::BN * ES + 16) <= (int)sizeof(typename T::Lds)) ? 1 : 2;
     constexpr int TP = TN / NP;                    // column tiles per wave and pass
@@ -431,6 +436,8 @@ __device__ __forceinline__ void store_tile(const GemmParams& g, uint8_t* lds, in
     const int t = threadIdx.x;
     const int wave = t >> 6, lane = t & 63;
     const int r = lane & 31, h = lane >> 5, wn = wave / WM, wm = wave % WM;
+    const int64_t mend = OUT == 2 ? g.rows_pad : g.M, nend = OUT == 2 ? g.ldr : g.N;
+    double sq = 0.0;
 #pragma unroll
     for (int p = 0; p < NP; ++p) {
         if (p > 0) __syncthreads();
@@ -460,7 +467,7 @@ __device__ __forceinline__ void store_tile(const GemmParams& g, uint8_t* lds, in
             // column of the chunk: the pass holds TP tiles of each of the WN waves' column ranges
             const int cl = ch * EPC, seg = cl / (32 * TP);
             const int64_t m = mb0 + row, n = nb0 + seg * 32 * TN + 32 * p * TP + (cl - seg * 32 * TP);
-            if (m >= g.M || n >= g.N) continue;
+            if (m >= mend || n >= nend) continue;
             const uint4 v = *reinterpret_cast<const uint4*>(lds + row * RS + 16 * ch);
             if (BF16) {
                 uint16_t* const c = g.C16 + m * g.ldc_out + n;
@@ -472,10 +479,49 @@ __device__ __forceinline__ void store_tile(const GemmParams& g, uint8_t* lds, in
                     for (int e = 0; e < 8; ++e)
                         if (n + e < g.N) c[e] = (uint16_t)(w[e / 2] >> (16 * (e & 1)));
                 }
+            } else if (OUT == 0) {
+                store_c4(g, m, n, __builtin_bit_cast(float4, v));
             } else {
-                const float4 f = __builtin_bit_cast(float4, v);
-                store_c4(g, m, n, f);
+                const float4 c = __builtin_bit_cast(float4, v);
+                float f[4] = {c.x, c.y, c.z, c.w};
+                const float* const b = g.bias + m * g.ldc_out + n;
+                if (m < g.M && g.vec_ok && n + 3 < g.N) {
+                    const float4 o = *reinterpret_cast<const float4*>(b);
+                    f[0] = o.x + f[0];
+                    f[1] = o.y + f[1];
+                    f[2] = o.z + f[2];
+                    f[3] = o.w + f[3];
+                } else {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) f[e] = (m < g.M && n + e < g.N) ? b[e] + f[e] : 0.0f;
+                }
+                uint32_t hi[2], lo[2];
+#pragma unroll
+                for (int e = 0; e < 4; e += 2) {
+                    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+                    const bf16x2 h2 = {(__bf16)f[e], (__bf16)f[e + 1]};
+                    const bf16x2 l2 = {(__bf16)(f[e] - (float)h2[0]), (__bf16)(f[e + 1] - (float)h2[1])};
+                    hi[e / 2] = __builtin_bit_cast(uint32_t, h2);
+                    lo[e / 2] = __builtin_bit_cast(uint32_t, l2);
+                    sq += (double)f[e] * (double)f[e] + (double)f[e + 1] * (double)f[e + 1];
+                }
+                *reinterpret_cast<uint2*>(g.rh + m * g.ldr + n) = make_uint2(hi[0], hi[1]);
+                *reinterpret_cast<uint2*>(g.rl + m * g.ldr + n) = make_uint2(lo[0], lo[1]);
             }
+        }
+    }
+    if (OUT == 2) {
+        __syncthreads();
+        double* const red = reinterpret_cast<double*>(lds);
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) sq += __shfl_xor(sq, off);
+        if (lane == 0) red[wave] = sq;
+        __syncthreads();
+        if (t == 0) {
+            double tot = red[0];
+#pragma unroll
+            for (int i = 1; i < T::WAVES; ++i) tot += red[i];
+            g.sq_part[(int64_t)blockIdx.y * gridDim.x + blockIdx.x] = tot;
         }
     }
 }
@@ -508,8 +554,9 @@ __global__ __launch_bounds__(64 * WN * WM) void mxfp4_gemm_pipe_kernel(const Gem
     f32x16g acc[TN][TM];
     gemm_tile<WN, WM, TN, TM, PING, DMA_SCALES>(g, lds, tn * T::BN, tm * T::BM, acc);
     uint8_t* const stage = reinterpret_cast<uint8_t*>(&lds);
-    if (g.C16) store_tile<WN, WM, TN, TM, true>(g, stage, tn * T::BN, tm * T::BM, acc);
-    else store_tile<WN, WM, TN, TM, false>(g, stage, tn * T::BN, tm * T::BM, acc);
+    if (g.C16) store_tile<WN, WM, TN, TM, 1>(g, stage, tn * T::BN, tm * T::BM, acc);
+    else if (g.rh) store_tile<WN, WM, TN, TM, 2>(g, stage, tn * T::BN, tm * T::BM, acc);
+    else store_tile<WN, WM, TN, TM, 0>(g, stage, tn * T::BN, tm * T::BM, acc);
 }
 
 constexpr int64_t kBigTileMin = 96;  // 256 x 256 tiles needed before that kernel is chosen
@@ -528,13 +575,19 @@ static void launch_pipe(const GemmParams& g, hipStream_t st) {
 // The pipelined kernels index a tile's 256 rows with 32-bit byte offsets.
 constexpr int64_t kPipeMaxK = int64_t(1) << 24;
 
+static bool big_tiles(const GemmParams& g) { return ((g.N + 255) / 256) * ((g.M + 255) / 256) >= kBigTileMin; }
+
+int64_t mxfp4_gemm_workgroups(const GemmParams& g) {
+    const int64_t t = big_tiles(g) ? 256 : 128;
+    return ((g.N + t - 1) / t) * ((g.M + t - 1) / t);
+}
+
 hipError_t launch_mxfp4_gemm(const GemmParams& g, hipStream_t st) {
     // the 256 x 256 tile once there are enough of them to spread over the chip, else 128 x 128
     // (16-byte code and scale loads per row: any K; us before, with K % 128 != 0 on the direct
     // kernel, and now: 4096 x 5600 x 2240 151 and 49, 4608 x 3072 x 3072 41.1 and 34.3,
     // 4608 x 3072 x 12288 124 and 98, 1000 x 3456 x 1152 12.0 and 8.1)
-    const int64_t big_tiles = ((g.N + 255) / 256) * ((g.M + 255) / 256);
-    if (g.K <= kPipeMaxK && big_tiles >= kBigTileMin) {
+    if (g.K <= kPipeMaxK && big_tiles(g)) {
         launch_pipe<2, 4, 4, 2, true>(g, st);
     } else if (g.K <= kPipeMaxK) {
         launch_pipe<2, 2, 2, 2, false>(g, st);

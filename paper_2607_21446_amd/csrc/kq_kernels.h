@@ -28,6 +28,8 @@ struct Params {
     const uint8_t* kpack;  // [nfac, kPackBytes] materialised K terms, or null
     const float* lu;       // [nfac, 5, 3] LU parameters of G_1..G_5 (KronLU), or null
     uint16_t* y16;         // [M, d] bf16 of the transformed values, or null (KronLU)
+    uint16_t* q16;         // [M, d] bf16 of the dequantized codes (calibration)
+    int inverse;           // 1: the LU parameters' inverse blocks (calibration)
     int64_t units;       // wave units, filled in by the launcher
 };
 
@@ -53,12 +55,22 @@ struct GemmParams {
     int accumulate;           // 1: C += product, 0: C = product
     const float* bias = nullptr;  // if set: C = bias + product (bias [M, ldc_out], vec rule as C)
     uint16_t* C16 = nullptr;      // if set: bf16 output [M, ldc_out] instead of C (no bias, no accumulate)
+    // if rh is set: no C; v = bias + product goes out as the bf16 terms of v, [rows_pad, ldr]
+    // (zero beyond M and N), and every workgroup's sum of v^2 (K at most 2^24)
+    uint16_t* rh = nullptr;
+    uint16_t* rl = nullptr;
+    int64_t ldr = 0, rows_pad = 0;
+    double* sq_part = nullptr;    // [mxfp4_gemm_workgroups]
     int vec_ok;               // C 16-byte aligned and ldc_out a multiple of 4 (C16: 16-byte and 8)
     int scales_aligned;       // both scale arrays 4-byte aligned
 };
 
 hipError_t launch(Kind kind, int a, const Params& p, Mapping map, hipStream_t st);
 hipError_t launch_mxfp4_gemm(const GemmParams& g, hipStream_t st);
+int64_t mxfp4_gemm_workgroups(const GemmParams& g);  // of the call, for K up to 2^24
+// The calibration step's two operands in one launch: px with the factors of its LU
+// parameters, pw with those of the inverse blocks; y, codes, scales and q16 of both.
+hipError_t launch_calib_quant(int a, const Params& px, const Params& pw, hipStream_t st);
 hipError_t launch_pack(int a, const float* A, const float* B, int64_t nfac, uint8_t* kpack, hipStream_t st);
 hipError_t launch_e2m1(const float* v, int64_t npairs, uint32_t s, uint8_t* codes, hipStream_t st);
 hipError_t launch_fwht(const Params& p, hipStream_t st);  // d a power of two, 32 .. 16384

@@ -53,6 +53,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "kq_kernels.h"
 
 namespace kq {
@@ -85,6 +87,14 @@ __device__ __forceinline__ float ld_uniform(const float* base, int64_t idx) {
 __device__ __forceinline__ uint32_t e8m0_byte(float amax) {
     const uint32_t e = __float_as_uint(amax) >> 23;
     return e > 2u ? e - 2u : 0u;
+}
+
+// Value of an E2M1 code at E8M0 scale byte s (OCP MX v1.0), exact in fp32 (and in bf16).
+__device__ __forceinline__ float e2m1_value(uint32_t nib, uint32_t s) {
+    const uint32_t m = nib & 7u;
+    const uint32_t bits = m >= 2 ? (((126u + (m >> 1)) << 23) | ((m & 1u) << 22)) : (m == 1 ? (126u << 23) : 0u);
+    const float v = __uint_as_float(bits) * __uint_as_float(s ? s << 23 : 0x00400000u);
+    return (nib & 8u) ? -v : v;
 }
 
 // Encode 32 fp32 values: returns the scale byte, writes 4 dwords of packed codes.
@@ -493,7 +503,7 @@ __global__ __launch_bounds__(64) void smooth_stationary_kernel(const Params p) {
 //   Y[o][i] = A[o][0]*Z[0][i] then fma(A[o][p], Z[p][i], .), p = 1..a-1.
 // Called with all 64 lanes active; the blocks lie in this wave's LDS unit
 // (GX: the inputs are read from X at the output blocks, unit_lds unused).
-template <int NA, int NB, bool GX = false>
+template <int NA, int NB, bool GX = false, bool Q16 = false>
 __device__ __forceinline__ void exact_blocks_coop(const uint4* unit_lds, int blk0, int blk1, const float* Af,
                                                   const float* Bf, const Params& p, int64_t out0, int64_t out1) {
     const int h = (threadIdx.x >> 5) & 1;  // half of this wave (workgroups may hold several waves)
@@ -528,12 +538,13 @@ __device__ __forceinline__ void exact_blocks_coop(const uint4* unit_lds, int blk
         }
         if (p.y) p.y[out_blk * 32 + n] = acc;
         if (p.y16) p.y16[out_blk * 32 + n] = (uint16_t)(bf16_pair(acc, 0.0f) & 0xFFFFu);
+        if (Q16) p.q16[out_blk * 32 + n] = (uint16_t)(__float_as_uint(e2m1_value(c, sb)) >> 16);
     }
 }
 
 // all blocks flagged in `edges` (bit b = block b of the unit), two at a time
 // (GX: their inputs read from X instead of the unit in LDS)
-template <int NA, int NB, bool GX = false>
+template <int NA, int NB, bool GX = false, bool Q16 = false>
 __device__ __forceinline__ void exact_flagged(uint64_t edges, const uint4* unit_lds, int64_t first, uint32_t bstride,
                                               const float* Af, const float* Bf, const Params& p) {
     while (edges) {
@@ -544,7 +555,7 @@ __device__ __forceinline__ void exact_flagged(uint64_t edges, const uint4* unit_
             b1 = __builtin_ctzll(edges);
             edges &= edges - 1;
         }
-        exact_blocks_coop<NA, NB, GX>(unit_lds, b0, b1, Af, Bf, p, first + (int64_t)b0 * bstride,
+        exact_blocks_coop<NA, NB, GX, Q16>(unit_lds, b0, b1, Af, Bf, p, first + (int64_t)b0 * bstride,
                                       first + (int64_t)(b1 < 0 ? 0 : b1) * bstride);
     }
 }
@@ -570,6 +581,19 @@ __device__ __forceinline__ void lu_g(const float (&pv)[15], float (&g)[5][4]) {
         g[k][1] = pb;
         g[k][2] = pc * pa;
         g[k][3] = __builtin_fmaf(pc, pb, -(1.0f / pa));
+    }
+}
+
+// The transposes of the inverse factors: det G = -1, so G^-1 = [[-g3, g1], [g2, -g0]],
+// and A (x) B built from them is T^-1 instead of T^T.
+__device__ __forceinline__ void lu_g_inverse(float (&g)[5][4]) {
+#pragma unroll
+    for (int k = 0; k < 5; ++k) {
+        const float g0 = g[k][0], g1 = g[k][1];
+        g[k][0] = -g[k][3];
+        g[k][1] = g[k][2];
+        g[k][2] = g1;
+        g[k][3] = -g0;
     }
 }
 
@@ -668,7 +692,8 @@ struct TileSink {
     uint64_t* edges;
 };
 
-template <Mapping MAP, int NA, int NB, bool ILV, bool WY, bool WY16, bool FULL, bool PACKED, bool TILE = false>
+template <Mapping MAP, int NA, int NB, bool ILV, bool WY, bool WY16, bool FULL, bool PACKED, bool TILE = false,
+          bool WQ16 = false>
 __device__ __forceinline__ void unit_compute(const Params& p, uint4* lds, int64_t first, int nvalid_rt,
                                              uint32_t bstride, const uint4 (&v)[4], const KSlices& ks, bool zero_ok,
                                              EdgeTest et, const float* Af, const float* Bf, TileSink ts = {}) {
@@ -770,6 +795,20 @@ __device__ __forceinline__ void unit_compute(const Params& p, uint4* lds, int64_
             for (int q = 0; q < 2; ++q)
                 yb[q] = make_uint4(bf16_pair(acc[8 * q], acc[8 * q + 1]), bf16_pair(acc[8 * q + 2], acc[8 * q + 3]),
                                    bf16_pair(acc[8 * q + 4], acc[8 * q + 5]), bf16_pair(acc[8 * q + 6], acc[8 * q + 7]));
+        }
+        if (WQ16 && o.store) {
+            // the codes' values (a stored block's scale byte is at least 2, or its codes are 0:
+            // the smallest value, 0.5 * 2^(s - 127), is a normal bf16)
+            uint4* qb = reinterpret_cast<uint4*>(p.q16 + first * 32 + ((uint32_t)bt * bstride * 32u + 16u * h));
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                const uint32_t c = q ? o.codes.y : o.codes.x;
+                auto two = [&](auto sel) {
+                    return __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(c, sc, decltype(sel)::value));
+                };
+                qb[q] = make_uint4(two(std::integral_constant<int, 0>{}), two(std::integral_constant<int, 1>{}),
+                                   two(std::integral_constant<int, 2>{}), two(std::integral_constant<int, 3>{}));
+            }
         }
         edges |= (__builtin_amdgcn_ballot_w64(near) & 0xFFFFFFFFull) << (32 * t);
         return o;
@@ -1098,8 +1137,11 @@ constexpr int kTileSlots = 260;
 constexpr int kCodeSlots = 68;  // 64 blocks x 16 code bytes, then 64 scale bytes
 constexpr int kTileMaxSteps = 8;
 
-template <int NA, int NB, bool LU, bool WY, bool WY16, bool PW = false>
-__global__ __launch_bounds__(64 * kTileCols) void kron_tile_kernel(const Params p, int rg) {
+//
+// CAL: the calibration step's form, with the dequantized values as a third
+// output and, for its weight side, the factors of the inverse blocks.
+template <int NA, int NB, bool LU, bool WY, bool WY16, bool PW, bool CAL>
+__device__ __forceinline__ void kron_tile(const Params& p, int rg, int64_t wg, int64_t nwg) {
     constexpr int NF = NA * NA + NB * NB;
     constexpr int FPL = (NF + 63) / 64;  // factor entries per lane
     __shared__ uint4 lds_x[kTileCols * kTileSlots];
@@ -1110,7 +1152,7 @@ __global__ __launch_bounds__(64 * kTileCols) void kron_tile_kernel(const Params 
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int64_t ntc = (p.nb + kTileCols - 1) / kTileCols;
     const int64_t nrb = (p.M + 63) / 64;
-    const int64_t g = xcd_order(blockIdx.x, gridDim.x);
+    const int64_t g = xcd_order(wg, nwg);
     const int64_t jt = g % ntc, rb0 = (g / ntc) * rg;
     const int nsteps = (int)min<int64_t>(rg, nrb - rb0);
     const int ncols = (int)min<int64_t>(kTileCols, p.nb - kTileCols * jt);
@@ -1162,6 +1204,7 @@ __global__ __launch_bounds__(64 * kTileCols) void kron_tile_kernel(const Params 
             float pv[15];
             lu_load(p.lu + f * 15, pv);
             lu_g(pv, gm);
+            if (CAL && p.inverse) lu_g_inverse(gm);
 #pragma unroll
             for (int q2 = 0; q2 < FPL; ++q2) {
                 const int i = lane + 64 * q2;
@@ -1228,7 +1271,7 @@ __global__ __launch_bounds__(64 * kTileCols) void kron_tile_kernel(const Params 
         __builtin_amdgcn_s_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
         if (active)
-            unit_compute<Mapping::Column, NA, NB, false, WY, WY16, false, PW, true>(
+            unit_compute<Mapping::Column, NA, NB, false, WY, WY16, false, PW, true, CAL>(
                 p, lds_x + kTileSlots * w, row0 * p.nb + jc, nrows, (uint32_t)p.nb, v, ks, zero_ok, et, Af, Bf,
                 TileSink{lds_c + kCodeSlots * w, &stmask[w], &sedges[w][it]});
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
@@ -1253,9 +1296,29 @@ __global__ __launch_bounds__(64 * kTileCols) void kron_tile_kernel(const Params 
             const uint64_t se = sedges[w][it];
             const uint64_t e = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)se) |
                                ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)(se >> 32)) << 32);
-            if (e) exact_flagged<NA, NB, true>(e, nullptr, (rb0 + it) * 64 * p.nb + jc, (uint32_t)p.nb, Af, Bf, p);
+            if (e) exact_flagged<NA, NB, true, CAL>(e, nullptr, (rb0 + it) * 64 * p.nb + jc, (uint32_t)p.nb, Af, Bf, p);
         }
     }
+}
+
+template <int NA, int NB, bool LU, bool WY, bool WY16, bool PW = false>
+__global__ __launch_bounds__(64 * kTileCols) void kron_tile_kernel(const Params p, int rg) {
+    kron_tile<NA, NB, LU, WY, WY16, PW, false>(p, rg, blockIdx.x, gridDim.x);
+}
+
+// Both operands of a calibration step: workgroups 0 .. nx - 1 take px, the rest pw.
+struct CalibQuant {
+    Params p[2];
+    int rg[2];
+    uint32_t nx;
+};
+
+template <int NA, int NB>
+__global__ __launch_bounds__(64 * kTileCols) void kron_tile_calib_kernel(const CalibQuant c) {
+    const bool w = blockIdx.x >= c.nx;
+    const Params p = w ? c.p[1] : c.p[0];
+    kron_tile<NA, NB, true, true, false, false, true>(p, w ? c.rg[1] : c.rg[0], w ? blockIdx.x - c.nx : blockIdx.x,
+                                                      w ? gridDim.x - c.nx : c.nx);
 }
 
 // Materialise and split K = A (x) B for every factor pair, in the lane layout
@@ -1628,6 +1691,23 @@ static int tile_rows(const Params& p) {
     const int64_t tiles = ((p.M + 63) / 64) * ((p.nb + kTileCols - 1) / kTileCols);
     const int64_t rg = tiles / 1728;
     return rg < 1 ? 1 : rg > kTileMaxSteps ? kTileMaxSteps : (int)rg;
+}
+
+hipError_t launch_calib_quant(int a, const Params& px, const Params& pw, hipStream_t st) {
+    auto groups = [](const Params& p, int rg) {
+        return (((p.M + 63) / 64 + rg - 1) / rg) * ((p.nb + kTileCols - 1) / kTileCols);
+    };
+    CalibQuant c{{px, pw}, {tile_rows(px), tile_rows(pw)}, 0u};
+    c.nx = (uint32_t)groups(px, c.rg[0]);
+    const dim3 g(c.nx + (unsigned)groups(pw, c.rg[1])), b(64 * kTileCols);
+    switch (a) {
+        case 4: hipLaunchKernelGGL((kron_tile_calib_kernel<4, 8>), g, b, 0, st, c); break;
+        case 2: hipLaunchKernelGGL((kron_tile_calib_kernel<2, 16>), g, b, 0, st, c); break;
+        case 8: hipLaunchKernelGGL((kron_tile_calib_kernel<8, 4>), g, b, 0, st, c); break;
+        case 1: hipLaunchKernelGGL((kron_tile_calib_kernel<1, 32>), g, b, 0, st, c); break;
+        default: return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
 }
 
 // The on-chip-K unit kernel: four units per workgroup (one factor pair each).
