@@ -521,17 +521,21 @@ kq_status kq_calib_reference(const uint16_t* X, int64_t R, int64_t d, const uint
 static kq_status calib_step_impl(const kq::CalibPlan& pl, const uint16_t* X, const uint16_t* W, const float* Yneg,
                                  float* lu, const float* lambdas, float* grad, double* losses, float* adam_m,
                                  float* adam_v, int adam_t, float lr, unsigned char* ws, hipStream_t s) {
-    auto operand = [&](const uint16_t* M, int64_t rows, size_t c, size_t sc, size_t y, size_t q, int inverse) {
-        kq::Params p = make_params(M, rows, pl.d, ws + c, ws + sc, reinterpret_cast<float*>(ws + y));
+    auto operand = [&](const uint16_t* M, int64_t rows, size_t c, size_t sc, size_t q, size_t m, size_t dp, size_t sq,
+                       int inverse) {
+        kq::Params p = make_params(M, rows, pl.d, ws + c, ws + sc, nullptr);
         p.nfac = pl.nfac;
         p.lu = lu;
-        p.q16 = reinterpret_cast<uint16_t*>(ws + q);
         p.inverse = inverse;
+        p.q16 = reinterpret_cast<uint16_t*>(ws + q);
+        p.clipped = reinterpret_cast<uint32_t*>(ws + m);
+        p.dpart = reinterpret_cast<float*>(ws + dp);
+        p.sqpart = reinterpret_cast<double*>(ws + sq);
         return p;
     };
-    // Q(X T) and Q(W T^-T), their fp32 and dequantized values
-    hipError_t e = kq::launch_calib_quant(pl.a, operand(X, pl.R, pl.cA, pl.sA, pl.yA, pl.qA, 0),
-                                          operand(W, pl.o, pl.cW, pl.sW, pl.yW, pl.qW, 1), s);
+    // Q(X T) and Q(W T^-T) and what the gradient needs of their rounding
+    hipError_t e = kq::launch_calib_quant(pl.a, operand(X, pl.R, pl.cA, pl.sA, pl.qA, pl.mA, pl.dA, pl.sqa, 0),
+                                          operand(W, pl.o, pl.cW, pl.sW, pl.qW, pl.mW, pl.dW, pl.sqw, 1), s);
     if (e != hipSuccess) return from_hip(e, "kq_calib_step (quantize)");
     // residual Q(X T) Q(W T^-T)^T - X W^T on the W4A4 GEMM with Yneg as its bias, as two bf16 terms
     kq::GemmParams g =

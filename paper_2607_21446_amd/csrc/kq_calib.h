@@ -13,13 +13,15 @@ struct CalibPlan {
     int a = 4;
     bool big = true;                      // 256 x 256 tiles of the backward products, else 128 x 128
     int64_t ntn = 0;                      // column tiles of the d axis
-    // activation side: row tiles, workgroup rows that share them, K parts and their length; weight side
-    int64_t act_mt = 0, act_chunks = 0, act_ks = 0, act_kchunk = 0;
-    int64_t w_mt = 0, w_chunks = 0, w_ks = 0, w_kchunk = 0;
+    int64_t act_mt = 0, act_ks = 0, act_kchunk = 0;  // activation side: row tiles, K parts and their length
+    int64_t w_mt = 0, w_ks = 0, w_kchunk = 0;        // weight side
     int64_t nsum = 0;                     // room for the partial sums of the residual's squares
     int64_t Rp = 0, op = 0;               // R and o rounded up to the 32-deep K stage
     // byte offsets into the workspace (each 256-byte aligned)
-    size_t yA = 0, cA = 0, sA = 0, qA = 0, yW = 0, cW = 0, sW = 0, qW = 0;  // y, codes, scales, dequantized bf16
+    // of X and W: codes, scales, dequantized bf16, clipped-element words, the quantizer's
+    // per-strip sums over clipped elements (strips_*) and sums of squares (nsq*)
+    size_t cA = 0, sA = 0, qA = 0, mA = 0, dA = 0, cW = 0, sW = 0, qW = 0, mW = 0, dW = 0;
+    int64_t strips_a = 0, strips_w = 0, nsqa = 0, nsqw = 0;
     size_t rh = 0, rl = 0;                // the residual's two bf16 terms [Rp, op]
     size_t gpa = 0, gpw = 0, sqa = 0, sqw = 0, sr = 0;
     size_t grad = 0, am = 0, av = 0, lam = 0;
@@ -47,9 +49,8 @@ struct CalibStepArgs {
     unsigned char* ws;      // workspace laid out by the plan
 };
 
-// Backward and update part of a step; the forward products (quantized operands,
-// their fp32 and dequantized values, the residual's terms and the nsr partial
-// sums of its squares) must already be in the workspace.
+// Backward and update part of a step; the quantizer's outputs, the residual's terms and
+// the nsr partial sums of its squares must already be in the workspace.
 hipError_t launch_calib_backward(const CalibPlan& pl, const CalibStepArgs& s, int64_t nsr, hipStream_t st);
 
 // Small helpers of the calibration loop.

@@ -36,6 +36,7 @@
 #include <type_traits>
 
 #include "kq_calib.h"
+#include "kq_kernels.h"
 
 namespace kq {
 namespace {
@@ -44,25 +45,6 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
 constexpr int BK = 32;  // K per LDS stage (bf16 elements)
-
-__device__ __forceinline__ float bf16f(uint16_t v) { return __uint_as_float(uint32_t(v) << 16); }
-
-// Value of an E2M1 code at E8M0 scale byte s (OCP MX v1.0), exact in fp32 (and in bf16).
-__device__ __forceinline__ float mx_value(uint32_t nib, uint32_t s) {
-    const uint32_t m = nib & 7u;
-    const uint32_t bits = m >= 2 ? (((126u + (m >> 1)) << 23) | ((m & 1u) << 22)) : (m == 1 ? (126u << 23) : 0u);
-    const float scale = s ? __uint_as_float(s << 23) : __uint_as_float(0x00400000u);
-    const float v = __uint_as_float(bits) * scale;
-    return (nib & 8u) ? -v : v;
-}
-
-__device__ __forceinline__ float scale_value(uint32_t s) {
-    return s ? __uint_as_float(s << 23) : __uint_as_float(0x00400000u);
-}
-
-__device__ __forceinline__ f32x16 mfma32(float a, float b, f32x16 c) {
-    return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0);
-}
 
 // ---------------------------------------------------------------- operands
 // A GEMM operand, bf16, rows 16-byte aligned, columns a multiple of 8:
@@ -306,96 +288,112 @@ __device__ __forceinline__ void store_neg(const f32x16 (&acc)[TM][TN], float* ou
         }
 }
 
-// Gradient epilogue.  acc holds a tile of  P = dL_out/dQ * (R o) / 2  for the
-// quantized operand Q [M, d] (exact up to the split of K, which is linear).
-// With y the operand before quantization (fp32 from the quantizer) and
-// m = [|y| <= 6 * scale] the straight-through mask,
-//   g = c1 * P * m + [ks == 0] * c2 * (Q - y) * (m - 1)
-// is the tile of dL/dy (c1 = 2 / (R o), c2 = lambda * 2 / (rows d)); the
-// per-block sums  S_j += left_j^T g_j  (left = the operand before the
-// transform, bf16) run on the matrix cores with the rows as the K index,
-// taking g straight from the accumulator registers.  [ks == 0] tiles also add
-// (Q - y)^2 to the regulariser sum.
+// One side of the backward pass.  The product's tile holds  P = dL_out/dQ * (R o) / 2
+// for the quantized operand Q [M, d] (exact up to the split of K, which is linear).
+// With y the operand before quantization and m = [|y| <= 6 * scale] the
+// straight-through mask, the gradient is
+//   dL/dy = c1 * P * m + c2 * (Q - y) * (m - 1),
+// c1 = 2 / (R o), c2 = lambda * 2 / (rows d), and the block transforms take the
+// per-block sums  S_j = left_j^T dL/dy_j  (left = the operand before the transform).
+// The second term's sums come from the quantizer; this epilogue makes the first's,
+// without c1.
 struct Side {
-    Opnd A[2], B;           // the product: residual terms, dequantized operand
-    const uint16_t* left;   // [M, d] bf16
-    const float* y;         // [M, d]
-    const uint8_t* codes;   // [M, d / 2]
-    const uint8_t* scales;  // [M, d / 32]
-    int64_t M;
-    int lam_index;
-    float c2_unit;          // 2 / (rows d); c2 = lambda * c2_unit
-    float* partial;         // [chunks * ks, d / 32, 32, 32]
-    double* sq_partial;     // [m_tiles, ntn]
-    int64_t K, kchunk;      // K (a multiple of 32) in ks parts of kchunk
-    int ks;
-    int64_t m_tiles, chunks;  // workgroup row c takes the m tiles c, c + chunks, ...
-    int64_t works;            // chunks * ks * ntn
+    Opnd A[2], B;             // the product: residual terms, dequantized operand
+    Opnd left;                // [M, d] bf16
+    const uint32_t* clipped;  // [ceil(M / 32), d]: bit r of word (g, c) = not m of row 32 g + r
+    float* partial;           // [m_tiles * ks, d / 32, 32, 32]
+    int64_t K, kchunk;        // K (a multiple of 32) in ks parts of kchunk
+    int64_t ks, works;        // works = m_tiles * ks * ntn
 };
 
+// The Gram sums of a tile: left^T (P m) per 32-column block, on the matrix cores with
+// the rows as the K index.  P comes straight from the accumulators as three bf16
+// terms (hi + mid + lo, exact): six instructions of 32 cycles per 32 x 32, where fp32
+// ones took 16 of 64.  `left` is staged in the free stage buffers (one round of loads
+// for the whole tile; loading it, y, codes and scales from the lanes took a chain of
+// 16 memory latencies) and read transposed, its K index in the order the
+// accumulators have: k-step s, lane half h holds rows 16 s + 4 h + 0..3, 16 s + 8 + 4 h + 0..3.
+// 18432 x 3072 x 3072, both sides: 335 us before, of 1250.
 template <int WM, int WN, int TM, int TN>
-__device__ __forceinline__ void gram_tile(const f32x16 (&acc)[TM][TN], const Side& s, uint8_t* lds, int64_t d, float c1,
-                                          const float* lambdas, int64_t slot, bool add, int64_t ntn, int64_t m0,
-                                          int64_t n0, bool first) {
-    constexpr int WAVES = WM * WN;
+__device__ __forceinline__ void gram_tile(const f32x16 (&acc)[TM][TN], const Side& s, uint8_t* lds_generic, int64_t slot,
+                                          int64_t m0, int64_t n0) {
+    constexpr int WAVES = WM * WN, BM = 32 * WM * TM, BN = 32 * WN * TN;
+    constexpr int RPI = 512 / BN, LPR = 64 / RPI, LOADS = 2 * BM * BN / 1024 / WAVES;
+    lds_byte* const lds = (lds_byte*)lds_generic;
     int t = threadIdx.x;
-    asm volatile("" : "+v"(t));  // nor the epilogue's through the product
+    asm volatile("" : "+v"(t));  // the lane's addresses are not kept in registers through the product
     const int wave = __builtin_amdgcn_readfirstlane(t >> 6), lane = t & 63;
     const int wm = wave / WN, wn = wave % WN, h = lane >> 5, l32 = lane & 31;
-    const float c2 = lambdas[s.lam_index] * s.c2_unit;
-    const int64_t nb = d / 32;
-    double sq = 0.0;
-    float* const sums = reinterpret_cast<float*>(lds);  // [wm][block of the tile][32][32]
+    const int64_t d = s.left.cols, M = s.left.rows, nb = d / 32;
+    {
+        const uint8_t* const base = s.left.p + m0 * s.left.ld + 2 * n0;
+        const uint32_t last = (uint32_t)min<int64_t>(BM - 1, M - 1 - m0);
+        const uint32_t lds0 = (uint32_t)(uintptr_t)lds;
+#pragma unroll
+        for (int i = 0; i < LOADS; ++i) {
+            const uint32_t row = RPI * (LOADS * wave + i) + lane / LPR;
+            const int c = (lane % LPR) ^ ((row & 3) << 2);
+            const uint32_t col = 2u * (uint32_t)min<int64_t>(8 * c, d - 8 - n0);
+            lds_dma16(lds0 + 1024u * (LOADS * wave + i), min(row, last) * (uint32_t)s.left.ld + col, base);
+        }
+    }
+    // bit r of pass[i][j]: row r of the tile exists and passes the gradient at this lane's column
+    uint32_t pass[TM][TN];
+#pragma unroll
+    for (int i = 0; i < TM; ++i) {
+        const int64_t r0 = m0 + 32 * (wm * TM + i);
+        const uint32_t rows = r0 >= M ? 0u : M - r0 >= 32 ? ~0u : (1u << (M - r0)) - 1u;
+#pragma unroll
+        for (int j = 0; j < TN; ++j) {
+            const int64_t col = n0 + 32 * (wn * TN + j) + l32;
+            pass[i][j] = rows;
+            if (rows && col < d) pass[i][j] = rows & ~s.clipped[(r0 >> 5) * d + col];
+        }
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    stage_barrier();
+    f32x16 gram[TN];
+    const int jr = (lane >> 2) & 3;
 #pragma unroll
     for (int j = 0; j < TN; ++j) {
-        const int64_t blk = n0 / 32 + wn * TN + j;
-        f32x16 gram = {};
-        if (blk < nb) {
-            const int64_t col = blk * 32 + l32;
+        gram[j] = f32x16{};
+        const int c = (4 * (wn * TN + j) + 2 * ((lane >> 4) & 1) + ((lane & 3) >> 1)) ^ (jr << 2);
+        lds_byte* const lb = lds + (32 * wm * TM + 4 * h + jr) * (2 * BN) + 16 * c + 8 * (lane & 1);
 #pragma unroll
-            for (int i = 0; i < TM; ++i) {
-                const int64_t rbase = m0 + 32 * (wm * TM + i);
-                if (rbase >= s.M) continue;
-                // per half of the 16 rows: all loads first (rows past M read row M - 1 and are
-                // masked), then the arithmetic
-                f32x16 g;
-                float lv[16];
+        for (int i = 0; i < TM; ++i) {
+            const uint32_t bits = pass[i][j] >> (4 * h);
 #pragma unroll
-                for (int half = 0; half < 2; ++half) {
-                    float yv[8];
-                    uint32_t byte[8], sbyte[8], lraw[8];
+            for (int k = 0; k < 2; ++k) {
+                lds_byte* const p = lb + (32 * i + 16 * k) * (2 * BN);
+                const s16x4 lo4 = __builtin_amdgcn_ds_read_tr16_b64_v4i16(reinterpret_cast<lds_s16x4*>(p));
+                const s16x4 hi4 = __builtin_amdgcn_ds_read_tr16_b64_v4i16(reinterpret_cast<lds_s16x4*>(p + 8 * (2 * BN)));
+                typedef short s16x8 __attribute__((ext_vector_type(8)));
+                const bf16x8 lf = __builtin_bit_cast(bf16x8, s16x8{lo4.x, lo4.y, lo4.z, lo4.w, hi4.x, hi4.y, hi4.z, hi4.w});
+                bf16x8 g[3];
 #pragma unroll
-                    for (int u = 0; u < 8; ++u) {
-                        const int e = 8 * half + u;
-                        const int64_t row = min(rbase + 8 * (e / 4) + 4 * h + (e % 4), s.M - 1);
-                        yv[u] = s.y[row * d + col];
-                        byte[u] = s.codes[row * (d / 2) + col / 2];
-                        sbyte[u] = s.scales[row * nb + blk];
-                        lraw[u] = s.left[row * d + col];
-                    }
-#pragma unroll
-                    for (int u = 0; u < 8; ++u) {
-                        const int e = 8 * half + u;
-                        const bool valid = rbase + 8 * (e / 4) + 4 * h + (e % 4) < s.M;
-                        const float qv = mx_value((col & 1) ? byte[u] >> 4 : byte[u], sbyte[u]);
-                        const bool pass = fabsf(yv[u]) <= 6.0f * scale_value(sbyte[u]);
-                        float gv = pass ? c1 * acc[i][j][e] : 0.f;
-                        if (first) {
-                            const float diff = qv - yv[u];
-                            if (!pass) gv -= c2 * diff;
-                            if (valid) sq += double(diff) * double(diff);
-                        }
-                        g[e] = valid ? gv : 0.f;
-                        lv[e] = valid ? bf16f(uint16_t(lraw[u])) : 0.f;
-                    }
+                for (int u = 0; u < 8; ++u) {
+                    // accumulator 8 k + u is row 16 k + 8 (u / 4) + 4 h + u % 4
+                    const int bit = 16 * k + 8 * (u / 4) + (u % 4);
+                    const uint32_t keep = (uint32_t)((int32_t)(bits << (31 - bit)) >> 31);
+                    const float v = __uint_as_float(__float_as_uint(acc[i][j][8 * k + u]) & keep);
+                    g[0][u] = (__bf16)v;
+                    const float r1 = v - (float)g[0][u];  // exact
+                    g[1][u] = (__bf16)r1;
+                    g[2][u] = (__bf16)(r1 - (float)g[1][u]);
                 }
 #pragma unroll
-                for (int e = 0; e < 16; ++e) gram = mfma32(lv[e], g[e], gram);
+                for (int term = 2; term >= 0; --term)
+                    gram[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lf, g[term], gram[j], 0, 0, 0);
             }
         }
+    }
+    __syncthreads();
+    float* const sums = reinterpret_cast<float*>(lds_generic);  // [wm][block of the tile][32][32]
+#pragma unroll
+    for (int j = 0; j < TN; ++j) {
         float* const dst = sums + ((wm * WN + wn) * TN + j) * 1024;
 #pragma unroll
-        for (int e = 0; e < 16; ++e) dst[(8 * (e / 4) + 4 * h + (e % 4)) * 32 + l32] = gram[e];
+        for (int e = 0; e < 16; ++e) dst[(8 * (e / 4) + 4 * h + (e % 4)) * 32 + l32] = gram[j][e];
     }
     __syncthreads();
     // the WM row groups of a block, in order, and one write per block
@@ -408,26 +406,7 @@ __device__ __forceinline__ void gram_tile(const f32x16 (&acc)[TM][TN], const Sid
             const float4 o = *reinterpret_cast<const float4*>(sums + w * (WN * TN * 1024) + k);
             v = make_float4(v.x + o.x, v.y + o.y, v.z + o.z, v.w + o.w);
         }
-        float4* const dst = reinterpret_cast<float4*>(s.partial + (slot * nb + blk) * 1024 + k % 1024);
-        if (add) {  // this workgroup's earlier m tiles
-            const float4 o = *dst;
-            v = make_float4(o.x + v.x, o.y + v.y, o.z + v.z, o.w + v.w);
-        }
-        *dst = v;
-    }
-    if (first) {
-        __syncthreads();
-        double* const red = reinterpret_cast<double*>(lds);
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) sq += __shfl_xor(sq, off);
-        if (lane == 0) red[wave] = sq;
-        __syncthreads();
-        if (t == 0) {
-            double tot = red[0];
-#pragma unroll
-            for (int i = 1; i < WAVES; ++i) tot += red[i];
-            s.sq_partial[m0 / (32 * WM * TM) * ntn + n0 / (32 * WN * TN)] = tot;
-        }
+        *reinterpret_cast<float4*>(s.partial + (slot * nb + blk) * 1024 + k % 1024) = v;
     }
 }
 
@@ -440,35 +419,30 @@ __device__ __forceinline__ int64_t xcd_work(int64_t L, int64_t G) {
 
 struct BackwardArgs {
     Side act, wgt;
-    int64_t d, ntn;
-    float c1;
-    const float* lambdas;
+    int64_t ntn;
 };
 
 // Both backward products in one launch: works 0 .. act.works - 1 are the
 // activation side P = res . What (K = o, contiguous in res), the rest the weight
-// side P = res^T . Ahat (K = rows, strided in both).  A work is (m tiles, K part,
+// side P = res^T . Ahat (K = rows, strided in both).  A work is (m tile, K part,
 // column tile), the column tile fastest: the column tiles of one m tile and K
 // part read the same rows of the residual and run on one XCD.
 template <int WM, int WN, int TM, int TN, bool PING>
 __global__ __launch_bounds__(64 * WM * WN) void calib_backward_kernel(const BackwardArgs p) {
     typedef CalibTile<2, WM, WN, TM, TN> T;
-    static_assert(WM * WN * TN * 4096 <= T::kLdsBytes, "the block sums fit the stage buffers");
+    static_assert(WM * WN * TN * 4096 <= T::kLdsBytes && 2 * T::BM * T::BN <= T::kLdsBytes,
+                  "the block sums and a tile of `left` fit the stage buffers");
     __shared__ __align__(16) uint8_t lds[T::kLdsBytes];
-    int64_t wk = xcd_work(blockIdx.x, gridDim.x);
-    const bool act = wk < p.act.works;
-    if (!act) wk -= p.act.works;
+    const bool act = blockIdx.x < p.act.works;
     const Side s = act ? p.act : p.wgt;
-    const int64_t n0 = (wk % p.ntn) * T::BN, slot = wk / p.ntn;
-    const int64_t c = slot / s.ks, k_lo = (slot % s.ks) * s.kchunk, k_hi = std::min(s.K, k_lo + s.kchunk);
-    for (int64_t mt = c; mt < s.m_tiles; mt += s.chunks) {
-        const int64_t m0 = mt * T::BM;
-        f32x16 acc[TM][TN];
-        if (act) calib_product<2, false, true, WM, WN, TM, TN, PING>(s.A, s.B, lds, m0, n0, k_lo, k_hi, acc);
-        else calib_product<2, true, true, WM, WN, TM, TN, PING>(s.A, s.B, lds, m0, n0, k_lo, k_hi, acc);
-        gram_tile<WM, WN, TM, TN>(acc, s, lds, p.d, p.c1, p.lambdas, slot, mt != c, p.ntn, m0, n0, k_lo == 0);
-        __syncthreads();
-    }
+    // each XCD takes its share of both sides (their works differ in length)
+    const int64_t wk = xcd_work(act ? blockIdx.x : blockIdx.x - p.act.works, s.works);
+    const int64_t n0 = (wk % p.ntn) * T::BN, slot = wk / p.ntn, m0 = slot / s.ks * T::BM;
+    const int64_t k_lo = (slot % s.ks) * s.kchunk, k_hi = std::min(s.K, k_lo + s.kchunk);
+    f32x16 acc[TM][TN];
+    if (act) calib_product<2, false, true, WM, WN, TM, TN, PING>(s.A, s.B, lds, m0, n0, k_lo, k_hi, acc);
+    else calib_product<2, true, true, WM, WN, TM, TN, PING>(s.A, s.B, lds, m0, n0, k_lo, k_hi, acc);
+    gram_tile<WM, WN, TM, TN>(acc, s, lds, slot, m0, n0);
 }
 
 // Yneg = -(X W^T): both operands K-contiguous, one term.
@@ -487,22 +461,25 @@ __global__ __launch_bounds__(64 * WM * WN) void calib_reference_kernel(const Opn
 
 // ------------------------------------------------------------ small kernels
 
-// partial[0][j][e] + partial[1][j][e] = sum over the slots c of partial[c][j][e], in
-// place: summed in fp64 and a fixed order (16 threads per four elements, each every
-// 16th slot), stored as the nearest fp32 and the fp32 of the rest.
+// S = c1 sum over the slots of partial - c2 sum over the quantizer's strips of dpart,
+// summed in fp64 and a fixed order (16 threads per four elements, each every 16th
+// term), in place: partial[0][j][e] the nearest fp32, partial[1][j][e] that of the rest.
 struct ReduceSide {
-    float* partial;
-    int64_t slots;
+    float* partial;      // [slots (room for 2 at least), nb, 1024]
+    const float* dpart;  // [strips, nb, 1024]
+    int64_t slots, strips;
+    double c1, c2_unit;  // c2 = lambda * c2_unit
 };
 
-__global__ __launch_bounds__(256) void gram_reduce_kernel(const ReduceSide s0, const ReduceSide s1, int64_t nb) {
+__global__ __launch_bounds__(256) void gram_reduce_kernel(const ReduceSide s0, const ReduceSide s1, int64_t nb,
+                                                          const float* lambdas) {
     __shared__ double red[16][16][4];
     const ReduceSide s = blockIdx.z ? s1 : s0;
-    if (s.slots < 2) return;
+    const double c2 = -(double)lambdas[blockIdx.z] * s.c2_unit;
     const int64_t j = blockIdx.x;
     const int e4 = threadIdx.x & 15, part = threadIdx.x >> 4;
     const int64_t e = 64 * blockIdx.y + 4 * e4;
-    double v[4] = {0.0, 0.0, 0.0, 0.0};
+    double v[4] = {0.0, 0.0, 0.0, 0.0}, w[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll 4
     for (int64_t c = part; c < s.slots; c += 16) {
         const float4 x = *reinterpret_cast<const float4*>(s.partial + (c * nb + j) * 1024 + e);
@@ -511,8 +488,16 @@ __global__ __launch_bounds__(256) void gram_reduce_kernel(const ReduceSide s0, c
         v[2] += x.z;
         v[3] += x.w;
     }
+#pragma unroll 4
+    for (int64_t c = part; c < s.strips; c += 16) {
+        const float4 x = *reinterpret_cast<const float4*>(s.dpart + (c * nb + j) * 1024 + e);
+        w[0] += x.x;
+        w[1] += x.y;
+        w[2] += x.z;
+        w[3] += x.w;
+    }
 #pragma unroll
-    for (int i = 0; i < 4; ++i) red[part][e4][i] = v[i];
+    for (int i = 0; i < 4; ++i) red[part][e4][i] = s.c1 * v[i] + c2 * w[i];
     __syncthreads();
     if (threadIdx.x < 64) {
         double t = 0.0;
@@ -547,9 +532,8 @@ __device__ __forceinline__ double block_sum256(double v, double* red) {
 
 struct LuGradArgs {
     const float* lu;
-    const float* ga;   // [1 or 2, nb, 32, 32]  dL/dT of every block from the activation side (gram_reduce_kernel)
-    const float* gw;   // [1 or 2, nb, 32, 32]  dL/dU, U = T^-T, from the weight side
-    bool two_a, two_w;  // the second term is there
+    const float* ga;   // [2, nb, 32, 32]  dL/dT of every block from the activation side, in two terms
+    const float* gw;   // [2, nb, 32, 32]  dL/dU, U = T^-T, from the weight side
     int64_t nb, nfac;  // nfac = nb, or 1: the blocks' sums add up
     float* grad;       // [nfac, 15]
     float* lu_out;
@@ -610,8 +594,8 @@ __global__ __launch_bounds__(256) void lu_grad_kernel(const LuGradArgs p) {
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 const int64_t e = j * 1024 + t + 256 * i;
-                a4[i] += double(p.ga[e]) + (p.two_a ? double(p.ga[p.nb * 1024 + e]) : 0.0);
-                w4[i] += double(p.gw[e]) + (p.two_w ? double(p.gw[p.nb * 1024 + e]) : 0.0);
+                a4[i] += double(p.ga[e]) + double(p.ga[p.nb * 1024 + e]);
+                w4[i] += double(p.gw[e]) + double(p.gw[p.nb * 1024 + e]);
             }
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
@@ -755,17 +739,16 @@ int64_t cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
 }  // namespace
 
-// One side of the backward products: mt row tiles and ntn column tiles, K of
-// `stages` 32-deep stages in ks parts, chunks workgroup rows.
+// One side of the backward products: mt x ntn tiles of C, K of `stages` 32-deep
+// stages in ks parts.
 struct SidePlan {
-    int64_t mt, ntn, stages, ks, chunks;
-    // In units of a stage of a 256 x 256 tile on one CU: rounds of the chip, each
-    // a K part and its epilogue per m tile.  A 128 x 128 workgroup has a quarter of
-    // the work, two share a CU, and its stage feeds half the products per byte.
+    int64_t mt, ntn, stages, ks;
+    // In units of a stage of a 256 x 256 tile on one CU: rounds of the chip, each a K
+    // part and its epilogue.  A 128 x 128 workgroup has a quarter of the work, two
+    // share a CU, and its stage feeds half the products per byte.
     double cost(bool big) const {
         const double stage = big ? 1.0 : 0.8, epi = big ? 6.0 : 3.0;
-        return double(cdiv(chunks * ntn * ks, big ? 256 : 512)) * double(cdiv(mt, chunks)) *
-               (stage * double(cdiv(stages, ks)) + epi);
+        return double(cdiv(mt * ntn * ks, big ? 256 : 512)) * (stage * double(cdiv(stages, ks)) + epi);
     }
     // The K parts (of at least four stages) that fill the rounds best.
     void choose_parts(bool big) {
@@ -812,56 +795,56 @@ CalibPlan calib_plan(int64_t R, int64_t o, int64_t d, int a, int64_t nfac) {
         off = align256(off + bytes);
         return at;
     };
-    pl.yA = take(size_t(R) * d * 4);
     pl.cA = take(size_t(R) * d / 2);
     pl.sA = take(size_t(R) * (d / 32));
     pl.qA = take(size_t(R) * d * 2);
-    pl.yW = take(size_t(o) * d * 4);
+    pl.mA = take(size_t(cdiv(R, 32)) * d * 4);
+    pl.strips_a = calib_quant_strips(R, pl.nb);
+    pl.dA = take(size_t(pl.strips_a) * pl.nb * 4096);
     pl.cW = take(size_t(o) * d / 2);
     pl.sW = take(size_t(o) * (d / 32));
     pl.qW = take(size_t(o) * d * 2);
+    pl.mW = take(size_t(cdiv(o, 32)) * d * 4);
+    pl.strips_w = calib_quant_strips(o, pl.nb);
+    pl.dW = take(size_t(pl.strips_w) * pl.nb * 4096);
     pl.rh = take(size_t(pl.Rp) * pl.op * 2);
     pl.rl = take(size_t(pl.Rp) * pl.op * 2);
-    pl.sqa = take(size_t(cdiv(R, 128)) * cdiv(d, 128) * 8);
-    pl.sqw = take(size_t(cdiv(o, 128)) * cdiv(d, 128) * 8);
+    pl.nsqa = pl.strips_a * cdiv(pl.nb, 8);
+    pl.nsqw = pl.strips_w * cdiv(pl.nb, 8);
+    pl.sqa = take(size_t(pl.nsqa) * 8);
+    pl.sqw = take(size_t(pl.nsqw) * 8);
     pl.sr = take(size_t(pl.nsum) * 8);
     pl.grad = take(size_t(nfac) * 15 * 4);
     pl.am = take(size_t(nfac) * 15 * 4);
     pl.av = take(size_t(nfac) * 15 * 4);
     pl.lam = take(2 * 4);
-    // both sides with 256 x 256 or both with 128 x 128 tiles, whichever is cheaper,
-    // with K parts and workgroup rows whose partial sums fit what is left of the
-    // workspace that is told anyway
+    // both sides with 256 x 256 or both with 128 x 128 tiles, whichever is cheaper, with
+    // as many K parts as the partial sums have room for in the workspace that is told anyway
     const size_t told = told_workspace(R, o, d, a, nfac), slot = size_t(pl.nb) * 4096;
-    const int64_t room = std::max<int64_t>(2, told > off ? int64_t((told - off) / slot) : 0);
+    const int64_t room = told > off ? int64_t((told - off) / slot) : 0;
     double best = 0.0;
     for (const bool big : {true, false}) {
         const int64_t T = big ? 256 : 128, ntn = cdiv(d, T);
-        SidePlan act{cdiv(R, T), ntn, pl.op / BK, 1, cdiv(R, T)}, wgt{cdiv(o, T), ntn, pl.Rp / BK, 1, cdiv(o, T)};
+        SidePlan act{cdiv(R, T), ntn, pl.op / BK, 1}, wgt{cdiv(o, T), ntn, pl.Rp / BK, 1};
         act.choose_parts(big);
         wgt.choose_parts(big);
-        while (act.chunks * act.ks + wgt.chunks * wgt.ks > room) {
-            SidePlan& s = act.chunks * act.ks >= wgt.chunks * wgt.ks ? act : wgt;
-            if (s.ks > 1) --s.ks;
-            else s.chunks = cdiv(s.chunks, 2);
-        }
+        while ((act.ks > 1 || wgt.ks > 1) && act.mt * act.ks + wgt.mt * wgt.ks > room)
+            --(wgt.ks == 1 || (act.ks > 1 && act.mt * act.ks >= wgt.mt * wgt.ks) ? act : wgt).ks;
         const double cost = act.cost(big) + wgt.cost(big);
         if (big || cost < best) {
             best = cost;
             pl.big = big;
             pl.ntn = ntn;
             pl.act_mt = act.mt;
-            pl.act_chunks = act.chunks;
             pl.act_kchunk = cdiv(act.stages, act.ks) * BK;
             pl.w_mt = wgt.mt;
-            pl.w_chunks = wgt.chunks;
             pl.w_kchunk = cdiv(wgt.stages, wgt.ks) * BK;
         }
     }
     pl.act_ks = cdiv(pl.op, pl.act_kchunk);
     pl.w_ks = cdiv(pl.Rp, pl.w_kchunk);
-    pl.gpa = take(size_t(pl.act_chunks) * pl.act_ks * slot);
-    pl.gpw = take(size_t(pl.w_chunks) * pl.w_ks * slot);
+    pl.gpa = take(size_t(std::max<int64_t>(2, pl.act_mt * pl.act_ks)) * slot);
+    pl.gpw = take(size_t(std::max<int64_t>(2, pl.w_mt * pl.w_ks)) * slot);
     pl.total = std::max(off, told);
     return pl;
 }
@@ -885,57 +868,40 @@ hipError_t launch_calib_backward(const CalibPlan& pl, const CalibStepArgs& s, in
     const int64_t R = pl.R, o = pl.o, d = pl.d;
     const Opnd rh{ws + pl.rh, pl.Rp, pl.op, pl.op * 2}, rl{ws + pl.rl, pl.Rp, pl.op, pl.op * 2};
     BackwardArgs b{};
-    b.d = d;
     b.ntn = pl.ntn;
-    b.c1 = float(2.0 / (double(R) * double(o)));
-    b.lambdas = s.lambdas;
     // activation side: P = res . What  (M = R, N = d, K = o)
     b.act = Side{{rh, rl},
                  {ws + pl.qW, o, d, d * 2},
-                 s.X,
-                 reinterpret_cast<const float*>(ws + pl.yA),
-                 ws + pl.cA,
-                 ws + pl.sA,
-                 R,
-                 0,
-                 float(2.0 / (double(R) * double(d))),
+                 {reinterpret_cast<const uint8_t*>(s.X), R, d, d * 2},
+                 reinterpret_cast<const uint32_t*>(ws + pl.mA),
                  reinterpret_cast<float*>(ws + pl.gpa),
-                 reinterpret_cast<double*>(ws + pl.sqa),
                  pl.op,
                  pl.act_kchunk,
-                 int(pl.act_ks),
-                 pl.act_mt,
-                 pl.act_chunks,
-                 pl.act_chunks * pl.act_ks * pl.ntn};
+                 pl.act_ks,
+                 pl.act_mt * pl.act_ks * pl.ntn};
     // weight side: P = res^T . Ahat  (M = o, N = d, K = R)
     b.wgt = Side{{rh, rl},
                  {ws + pl.qA, R, d, d * 2},
-                 s.W,
-                 reinterpret_cast<const float*>(ws + pl.yW),
-                 ws + pl.cW,
-                 ws + pl.sW,
-                 o,
-                 1,
-                 float(2.0 / (double(o) * double(d))),
+                 {reinterpret_cast<const uint8_t*>(s.W), o, d, d * 2},
+                 reinterpret_cast<const uint32_t*>(ws + pl.mW),
                  reinterpret_cast<float*>(ws + pl.gpw),
-                 reinterpret_cast<double*>(ws + pl.sqw),
                  pl.Rp,
                  pl.w_kchunk,
-                 int(pl.w_ks),
-                 pl.w_mt,
-                 pl.w_chunks,
-                 pl.w_chunks * pl.w_ks * pl.ntn};
+                 pl.w_ks,
+                 pl.w_mt * pl.w_ks * pl.ntn};
     const unsigned works = unsigned(b.act.works + b.wgt.works);
     if (pl.big) calib_backward_kernel<4, 2, 2, 4, true><<<works, 512, 0, st>>>(b);
     else calib_backward_kernel<2, 2, 2, 2, false><<<works, 256, 0, st>>>(b);
-    const ReduceSide ra{b.act.partial, pl.act_chunks * pl.act_ks}, rw{b.wgt.partial, pl.w_chunks * pl.w_ks};
-    if (ra.slots > 1 || rw.slots > 1) gram_reduce_kernel<<<dim3(unsigned(pl.nb), 16, 2), 256, 0, st>>>(ra, rw, pl.nb);
+    const double c1 = 2.0 / (double(R) * double(o));
+    const ReduceSide ra{b.act.partial, reinterpret_cast<const float*>(ws + pl.dA), pl.act_mt * pl.act_ks, pl.strips_a,
+                        c1, 2.0 / (double(R) * double(d))};
+    const ReduceSide rw{b.wgt.partial, reinterpret_cast<const float*>(ws + pl.dW), pl.w_mt * pl.w_ks, pl.strips_w,
+                        c1, 2.0 / (double(o) * double(d))};
+    gram_reduce_kernel<<<dim3(unsigned(pl.nb), 16, 2), 256, 0, st>>>(ra, rw, pl.nb, s.lambdas);
     LuGradArgs la{};
     la.lu = s.lu;
     la.ga = ra.partial;
     la.gw = rw.partial;
-    la.two_a = ra.slots > 1;
-    la.two_w = rw.slots > 1;
     la.nb = pl.nb;
     la.nfac = pl.nfac;
     la.grad = s.grad;
@@ -947,9 +913,9 @@ hipError_t launch_calib_backward(const CalibPlan& pl, const CalibStepArgs& s, in
     la.sr = reinterpret_cast<double*>(ws + pl.sr);
     la.nsr = nsr;
     la.sqa = reinterpret_cast<double*>(ws + pl.sqa);
-    la.nsqa = pl.act_mt * pl.ntn;
+    la.nsqa = pl.nsqa;
     la.sqw = reinterpret_cast<double*>(ws + pl.sqw);
-    la.nsqw = pl.w_mt * pl.ntn;
+    la.nsqw = pl.nsqw;
     la.n_out = double(R) * double(o);
     la.n_a = double(R) * double(d);
     la.n_w = double(o) * double(d);

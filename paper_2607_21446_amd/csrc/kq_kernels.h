@@ -28,8 +28,12 @@ struct Params {
     const uint8_t* kpack;  // [nfac, kPackBytes] materialised K terms, or null
     const float* lu;       // [nfac, 5, 3] LU parameters of G_1..G_5 (KronLU), or null
     uint16_t* y16;         // [M, d] bf16 of the transformed values, or null (KronLU)
-    uint16_t* q16;         // [M, d] bf16 of the dequantized codes (calibration)
-    int inverse;           // 1: the LU parameters' inverse blocks (calibration)
+    // calibration only
+    int inverse;           // 1: the LU parameters' inverse blocks
+    uint16_t* q16;         // [M, d] bf16 of the dequantized codes
+    uint32_t* clipped;     // [ceil(M / 32), d]: bit r of word (g, c): |y[32 g + r][c]| > 6 * scale
+    float* dpart;          // [strips, d / 32, 32, 32]: per block sum over rows of x^T (Q - y), clipped elements only
+    double* sqpart;        // [workgroups]: sums of (Q - y)^2
     int64_t units;       // wave units, filled in by the launcher
 };
 
@@ -69,7 +73,10 @@ hipError_t launch(Kind kind, int a, const Params& p, Mapping map, hipStream_t st
 hipError_t launch_mxfp4_gemm(const GemmParams& g, hipStream_t st);
 int64_t mxfp4_gemm_workgroups(const GemmParams& g);  // of the call, for K up to 2^24
 // The calibration step's two operands in one launch: px with the factors of its LU
-// parameters, pw with those of the inverse blocks; y, codes, scales and q16 of both.
+// parameters, pw with those of the inverse blocks; codes, scales and the calibration
+// outputs of both.  An operand of M rows and nb blocks takes calib_quant_strips(M, nb)
+// strips of rows, each of ceil(nb / 8) workgroups.
+int64_t calib_quant_strips(int64_t M, int64_t nb);
 hipError_t launch_calib_quant(int a, const Params& px, const Params& pw, hipStream_t st);
 hipError_t launch_pack(int a, const float* A, const float* B, int64_t nfac, uint8_t* kpack, hipStream_t st);
 hipError_t launch_e2m1(const float* v, int64_t npairs, uint32_t s, uint8_t* codes, hipStream_t st);

@@ -495,6 +495,16 @@ __global__ __launch_bounds__(64) void smooth_stationary_kernel(const Params p) {
     }
 }
 
+// A wave's state in the calibration step over its column block.  The sums: d = sum over rows of
+// x^T (Q - y) over clipped elements (|y| > 6 * scale), [p][q] with q = lane % 32 and
+// p = 8 (e / 4) + 4 (lane / 32) + e % 4 in d[e]; sq = this lane's sum of (Q - y)^2.
+struct CalSums {
+    f32x16 d;
+    double sq;
+    uint8_t* lds;       // 2 KiB of this wave's own
+    uint32_t* clipped;  // the words of the unit's first 32 rows
+};
+
 // Exact fixed-order evaluation of up to two blocks by 32 cooperating lanes
 // each: half-wave h takes block blk[h] (skipped if negative); lane n
 // (n = lane % 32) evaluates output y[n] = Y[o][i], n = o*b + i, with the FMA
@@ -503,9 +513,13 @@ __global__ __launch_bounds__(64) void smooth_stationary_kernel(const Params p) {
 //   Y[o][i] = A[o][0]*Z[0][i] then fma(A[o][p], Z[p][i], .), p = 1..a-1.
 // Called with all 64 lanes active; the blocks lie in this wave's LDS unit
 // (GX: the inputs are read from X at the output blocks, unit_lds unused).
-template <int NA, int NB, bool GX = false, bool Q16 = false>
+//
+// CAL (the calibration step): also the dequantized value, and the block's share of
+// the wave's calibration sums (cal), see CalSums.
+template <int NA, int NB, bool GX = false, bool CAL = false>
 __device__ __forceinline__ void exact_blocks_coop(const uint4* unit_lds, int blk0, int blk1, const float* Af,
-                                                  const float* Bf, const Params& p, int64_t out0, int64_t out1) {
+                                                  const float* Bf, const Params& p, int64_t out0, int64_t out1,
+                                                  CalSums* cal = nullptr) {
     const int h = (threadIdx.x >> 5) & 1;  // half of this wave (workgroups may hold several waves)
     const int n = threadIdx.x & 31;
     const int o = n / NB, i = n % NB;
@@ -538,15 +552,34 @@ __device__ __forceinline__ void exact_blocks_coop(const uint4* unit_lds, int blk
         }
         if (p.y) p.y[out_blk * 32 + n] = acc;
         if (p.y16) p.y16[out_blk * 32 + n] = (uint16_t)(bf16_pair(acc, 0.0f) & 0xFFFFu);
-        if (Q16) p.q16[out_blk * 32 + n] = (uint16_t)(__float_as_uint(e2m1_value(c, sb)) >> 16);
+        if (CAL) p.q16[out_blk * 32 + n] = (uint16_t)(__float_as_uint(e2m1_value(c, sb)) >> 16);
+    }
+    if (CAL) {
+        const float diff = e2m1_value(c, sb) - acc;
+        const bool clip = blk >= 0 && fabsf(acc) > 6.0f * __uint_as_float(sb ? sb << 23 : 0x00400000u);
+        if (blk >= 0) cal->sq += (double)diff * (double)diff;
+        const float dv = clip ? diff : 0.0f, dother = other_half(dv);
+        if (clip) {
+            const int64_t row = out_blk / p.nb, j = out_blk % p.nb;
+            atomicOr(p.clipped + (row >> 5) * p.d + 32 * j + n, 1u << (row & 31));
+        }
+        // lane (h, n) holds columns n of rows 8 q + 4 h + r of the sums: both blocks add to all of them
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+            const int p0 = 8 * (e / 4) + (e % 4);
+            const float mine = h ? x[p0 + 4] : x[p0], theirs = other_half(h ? x[p0] : x[p0 + 4]);
+            cal->d[e] = __builtin_fmaf(mine, dv, cal->d[e]);
+            cal->d[e] = __builtin_fmaf(theirs, dother, cal->d[e]);
+        }
     }
 }
 
 // all blocks flagged in `edges` (bit b = block b of the unit), two at a time
 // (GX: their inputs read from X instead of the unit in LDS)
-template <int NA, int NB, bool GX = false, bool Q16 = false>
+template <int NA, int NB, bool GX = false, bool CAL = false>
 __device__ __forceinline__ void exact_flagged(uint64_t edges, const uint4* unit_lds, int64_t first, uint32_t bstride,
-                                              const float* Af, const float* Bf, const Params& p) {
+                                              const float* Af, const float* Bf, const Params& p,
+                                              CalSums* cal = nullptr) {
     while (edges) {
         const int b0 = __builtin_ctzll(edges);
         edges &= edges - 1;
@@ -555,8 +588,8 @@ __device__ __forceinline__ void exact_flagged(uint64_t edges, const uint4* unit_
             b1 = __builtin_ctzll(edges);
             edges &= edges - 1;
         }
-        exact_blocks_coop<NA, NB, GX, Q16>(unit_lds, b0, b1, Af, Bf, p, first + (int64_t)b0 * bstride,
-                                      first + (int64_t)(b1 < 0 ? 0 : b1) * bstride);
+        exact_blocks_coop<NA, NB, GX, CAL>(unit_lds, b0, b1, Af, Bf, p, first + (int64_t)b0 * bstride,
+                                           first + (int64_t)(b1 < 0 ? 0 : b1) * bstride, cal);
     }
 }
 
@@ -692,11 +725,132 @@ struct TileSink {
     uint64_t* edges;
 };
 
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+typedef short s16x8 __attribute__((ext_vector_type(8)));
+
+// Eight K values of this lane's column from two 4-row groups of a row-major bf16 tile
+// in LDS: within 16 lanes, lane l gives the address of row l / 4, columns 4 (l % 4) ..
+// + 3, and gets the four rows of column l.
+__device__ __forceinline__ bf16x8 read_tr(const uint8_t* g0, const uint8_t* g1) {
+    typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
+    const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)g0);
+    const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)g1);
+    return __builtin_bit_cast(bf16x8, s16x8{lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w});
+}
+
+// Lanes I .. I + 3 of v from the low halves of b, lanes 16 + I .. 19 + I from the high
+// halves (two wait states between a VALU write of an SGPR and its read by another).
+template <int I>
+__device__ __forceinline__ uint32_t write_lanes(uint32_t v, const uint64_t (&b)[4]) {
+    asm("s_nop 1\n\t"
+        "v_writelane_b32 %0, %1, %9\n\tv_writelane_b32 %0, %2, %10\n\t"
+        "v_writelane_b32 %0, %3, %11\n\tv_writelane_b32 %0, %4, %12\n\t"
+        "v_writelane_b32 %0, %5, %13\n\tv_writelane_b32 %0, %6, %14\n\t"
+        "v_writelane_b32 %0, %7, %15\n\tv_writelane_b32 %0, %8, %16"
+        : "+v"(v)
+        : "s"((uint32_t)b[0]), "s"((uint32_t)b[1]), "s"((uint32_t)b[2]), "s"((uint32_t)b[3]),
+          "s"((uint32_t)(b[0] >> 32)), "s"((uint32_t)(b[1] >> 32)), "s"((uint32_t)(b[2] >> 32)),
+          "s"((uint32_t)(b[3] >> 32)), "n"(I), "n"(I + 1), "n"(I + 2), "n"(I + 3), "n"(16 + I), "n"(17 + I),
+          "n"(18 + I), "n"(19 + I));
+    return v;
+}
+
+// Calibration outputs of tile t of a unit (32 rows of one column block; lane 32 h + r
+// holds y[16 h + i] of row r in acc[i]): the dequantized values, the words of
+// clipped elements, and the wave's sums.  d takes the clipped elements' Q - y as three
+// bf16 terms (exact) through 2 KiB of LDS, so that both operands have the rows as
+// the K index: six matrix instructions per tile, where the fp32 y written here
+// and read back by the gradient's epilogue took 8 bytes per element.
+__device__ __forceinline__ void calib_block(const Params& p, const uint4* unit_lds, int64_t first,
+                                            uint32_t bstride, int nvalid, int t, const f32x16& acc, uint2 codes, float sc,
+                                            bool store, CalSums& cal) {
+    int lane = threadIdx.x & 63;
+    asm volatile("" : "+v"(lane));  // addresses are made where they are used, not kept through the strip
+    const int h = lane >> 5, jl = lane & 31;
+    uint32_t q[8];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        // (a stored block's scale byte is at least 2, or its codes are 0: the smallest
+        // value, 0.5 * 2^(s - 127), is a normal bf16)
+        const uint32_t c = i ? codes.y : codes.x;
+        auto two = [&](auto sel) {
+            return __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(c, sc, decltype(sel)::value));
+        };
+        q[4 * i + 0] = two(std::integral_constant<int, 0>{});
+        q[4 * i + 1] = two(std::integral_constant<int, 1>{});
+        q[4 * i + 2] = two(std::integral_constant<int, 2>{});
+        q[4 * i + 3] = two(std::integral_constant<int, 3>{});
+    }
+    if (store) {
+        uint4* const qb = reinterpret_cast<uint4*>(p.q16 + first * 32 + ((uint32_t)(32 * t + jl) * bstride * 32u + 16u * h));
+        qb[0] = make_uint4(q[0], q[1], q[2], q[3]);
+        qb[1] = make_uint4(q[4], q[5], q[6], q[7]);
+    }
+    const float lim = 6.0f * sc;
+    float dv[16];
+    double sq = 0.0;
+    uint32_t word = 0u;
+    uint64_t any = 0u;
+    // one 64-bit ballot per element: lanes 0-31 give column i of the block, lanes 32-63
+    // column 16 + i, one bit per row; lane c of `word` collects column c's
+    auto collect = [&](auto ic) {
+        constexpr int I = decltype(ic)::value;
+        uint64_t b[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int i = I + k;
+            const float qv = __uint_as_float(i & 1 ? q[i / 2] & 0xFFFF0000u : q[i / 2] << 16);
+            const float diff = qv - acc[i];
+            sq = __builtin_fma((double)diff, (double)diff, sq);
+            const bool clip = store && fabsf(acc[i]) > lim;
+            dv[i] = clip ? diff : 0.0f;
+            b[k] = __builtin_amdgcn_ballot_w64(clip);
+            any |= b[k];
+        }
+        word = write_lanes<I>(word, b);
+    };
+    collect(std::integral_constant<int, 0>{});
+    collect(std::integral_constant<int, 4>{});
+    collect(std::integral_constant<int, 8>{});
+    collect(std::integral_constant<int, 12>{});
+    if (store) cal.sq += sq;
+    if (32 * t < nvalid && lane < 32) cal.clipped[t * p.d + lane] = word;
+    if (any == 0u) return;
+    // x: row b of the unit at slots 4 b + (m ^ ((b >> 2) & 3)); rows 16 s + 8 h + 4 g + 0..3 of
+    // tile t in group g of k-step s
+    const int jr = (lane >> 2) & 3, c8 = 2 * ((lane >> 4) & 1) + ((lane & 3) >> 1);
+    const uint8_t* const xb = reinterpret_cast<const uint8_t*>(unit_lds) + 64 * (32 * t + 8 * h + jr) + 8 * (lane & 1);
+    const uint8_t* const db = cal.lds + 64 * (8 * h + jr) + 16 * c8 + 8 * (lane & 1);
+    bf16x8 xf[2];
+#pragma unroll
+    for (int s = 0; s < 2; ++s)
+        xf[s] = read_tr(xb + 1024 * s + 16 * (c8 ^ (2 * h)), xb + 1024 * s + 256 + 16 * (c8 ^ (2 * h + 1)));
+    uint4* const drow = reinterpret_cast<uint4*>(cal.lds + 64 * jl + 32 * h);
+#pragma unroll
+    for (int term = 0; term < 3; ++term) {
+        uint32_t w[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            w[i] = bf16_pair(dv[2 * i], dv[2 * i + 1]);
+            dv[2 * i] -= __uint_as_float(w[i] << 16);  // exact
+            dv[2 * i + 1] -= __uint_as_float(w[i] & 0xFFFF0000u);
+        }
+        drow[0] = make_uint4(w[0], w[1], w[2], w[3]);
+        drow[1] = make_uint4(w[4], w[5], w[6], w[7]);
+        wave_lds_sync();
+#pragma unroll
+        for (int s = 0; s < 2; ++s)
+            cal.d = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xf[s], read_tr(db + 1024 * s, db + 1024 * s + 256), cal.d, 0, 0, 0);
+        wave_lds_sync();
+    }
+}
+
 template <Mapping MAP, int NA, int NB, bool ILV, bool WY, bool WY16, bool FULL, bool PACKED, bool TILE = false,
-          bool WQ16 = false>
+          bool CAL = false>
 __device__ __forceinline__ void unit_compute(const Params& p, uint4* lds, int64_t first, int nvalid_rt,
                                              uint32_t bstride, const uint4 (&v)[4], const KSlices& ks, bool zero_ok,
-                                             EdgeTest et, const float* Af, const float* Bf, TileSink ts = {}) {
+                                             EdgeTest et, const float* Af, const float* Bf, TileSink ts = {},
+                                             CalSums* cal = nullptr) {
     const int lane = threadIdx.x & 63;
     const int h = lane >> 5, jl = lane & 31;
     const int nvalid = FULL ? 64 : nvalid_rt;
@@ -727,11 +881,12 @@ __device__ __forceinline__ void unit_compute(const Params& p, uint4* lds, int64_
     const int rslot = 4 * jl + (h ^ ((jl >> 2) & 3));
     if (!TILE) wave_lds_sync();
     uint4 raw[2][2];
-#pragma unroll
-    for (int t = 0; t < 2; ++t) {
+    auto read_raw = [&](int t) {
         raw[t][0] = lds[128 * t + rslot];
         raw[t][1] = lds[128 * t + (rslot ^ 2)];
-    }
+    };
+    read_raw(0);
+    if (!CAL) read_raw(1);
     uint64_t edges = 0;  // blocks of the unit on a binade edge (bit = block index)
     // the three terms, smallest first, of tile t: acc[n][block] += K[n][k-step] . x[block][k-step]
     auto product = [&](const uint4 (&r)[2]) {
@@ -796,20 +951,7 @@ __device__ __forceinline__ void unit_compute(const Params& p, uint4* lds, int64_
                 yb[q] = make_uint4(bf16_pair(acc[8 * q], acc[8 * q + 1]), bf16_pair(acc[8 * q + 2], acc[8 * q + 3]),
                                    bf16_pair(acc[8 * q + 4], acc[8 * q + 5]), bf16_pair(acc[8 * q + 6], acc[8 * q + 7]));
         }
-        if (WQ16 && o.store) {
-            // the codes' values (a stored block's scale byte is at least 2, or its codes are 0:
-            // the smallest value, 0.5 * 2^(s - 127), is a normal bf16)
-            uint4* qb = reinterpret_cast<uint4*>(p.q16 + first * 32 + ((uint32_t)bt * bstride * 32u + 16u * h));
-#pragma unroll
-            for (int q = 0; q < 2; ++q) {
-                const uint32_t c = q ? o.codes.y : o.codes.x;
-                auto two = [&](auto sel) {
-                    return __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(c, sc, decltype(sel)::value));
-                };
-                qb[q] = make_uint4(two(std::integral_constant<int, 0>{}), two(std::integral_constant<int, 1>{}),
-                                   two(std::integral_constant<int, 2>{}), two(std::integral_constant<int, 3>{}));
-            }
-        }
+        if (CAL) calib_block(p, lds, first, bstride, nvalid, t, acc, o.codes, sc, o.store, *cal);
         edges |= (__builtin_amdgcn_ballot_w64(near) & 0xFFFFFFFFull) << (32 * t);
         return o;
     };
@@ -844,6 +986,7 @@ __device__ __forceinline__ void unit_compute(const Params& p, uint4* lds, int64_
         const TileOut o0 = finish(0, product(raw[0]), raw[0]);
         if (TILE) tile_write(0, o0);
         __builtin_amdgcn_sched_barrier(0);
+        if (CAL) read_raw(1);
         const TileOut o1 = finish(1, product(raw[1]), raw[1]);
         if (TILE) tile_write(1, o1);
         __builtin_amdgcn_sched_barrier(0);
@@ -1138,8 +1281,8 @@ constexpr int kCodeSlots = 68;  // 64 blocks x 16 code bytes, then 64 scale byte
 constexpr int kTileMaxSteps = 8;
 
 //
-// CAL: the calibration step's form, with the dequantized values as a third
-// output and, for its weight side, the factors of the inverse blocks.
+// CAL: the calibration step's form, with its own outputs (calib_block) and, for its
+// weight side, the factors of the inverse blocks.
 template <int NA, int NB, bool LU, bool WY, bool WY16, bool PW, bool CAL>
 __device__ __forceinline__ void kron_tile(const Params& p, int rg, int64_t wg, int64_t nwg) {
     constexpr int NF = NA * NA + NB * NB;
@@ -1149,6 +1292,8 @@ __device__ __forceinline__ void kron_tile(const Params& p, int rg, int64_t wg, i
     __shared__ uint64_t stmask[kTileCols];
     __shared__ uint64_t sedges[kTileCols][kTileMaxSteps];
     __shared__ float fac[kTileCols * NF];  // each wave's A then B
+    __shared__ uint4 lds_d[CAL ? kTileCols * 128 : 1];  // CAL: each wave's 32 x 32 bf16 term
+    __shared__ double sq_lds[CAL ? kTileCols : 1];
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int64_t ntc = (p.nb + kTileCols - 1) / kTileCols;
     const int64_t nrb = (p.M + 63) / 64;
@@ -1247,6 +1392,7 @@ __device__ __forceinline__ void kron_tile(const Params& p, int rg, int64_t wg, i
             et.edge_t = __float_as_uint(ld_uniform(hdr, 3));
         }
     }
+    CalSums cal{f32x16{}, 0.0, reinterpret_cast<uint8_t*>(lds_d + (CAL ? 128 * w : 0)), nullptr};
     for (int it = 0; it < nsteps; ++it) {
         const int64_t row0 = (rb0 + it) * 64;
         const int nrows = (int)min<int64_t>(64, p.M - row0);
@@ -1270,15 +1416,18 @@ __device__ __forceinline__ void kron_tile(const Params& p, int rg, int64_t wg, i
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
         __builtin_amdgcn_s_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+        if (CAL) cal.clipped = p.clipped + 2 * (rb0 + it) * p.d + 32 * jc;
         if (active)
             unit_compute<Mapping::Column, NA, NB, false, WY, WY16, false, PW, true, CAL>(
                 p, lds_x + kTileSlots * w, row0 * p.nb + jc, nrows, (uint32_t)p.nb, v, ks, zero_ok, et, Af, Bf,
-                TileSink{lds_c + kCodeSlots * w, &stmask[w], &sedges[w][it]});
+                TileSink{lds_c + kCodeSlots * w, &stmask[w], &sedges[w][it]}, &cal);
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
         __builtin_amdgcn_s_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
         // row stores: thread t takes row t / 8, column block t % 8 of the step
-        const int r = threadIdx.x >> 3, j = threadIdx.x & 7;
+        int tid = threadIdx.x;
+        if (CAL) asm volatile("" : "+v"(tid));
+        const int r = tid >> 3, j = tid & 7;
         const uint32_t mword = reinterpret_cast<const uint32_t*>(stmask)[2 * j + (r >> 5)];
         if (p.codes && r < nrows && j < ncols && ((mword >> (r & 31)) & 1u)) {
             const uint4* const ct = lds_c + kCodeSlots * j;
@@ -1291,12 +1440,30 @@ __device__ __forceinline__ void kron_tile(const Params& p, int rg, int64_t wg, i
     // blocks on a binade edge: the fixed evaluation order decides (this
     // wave's own records, so no barrier is needed)
     if (active) {
+        if (CAL) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the clipped words, before their bits are added to
         for (int it = 0; it < nsteps; ++it) {
             // readfirstlane returns int: widen each half through uint32_t
             const uint64_t se = sedges[w][it];
             const uint64_t e = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)se) |
                                ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)(se >> 32)) << 32);
-            if (e) exact_flagged<NA, NB, true, CAL>(e, nullptr, (rb0 + it) * 64 * p.nb + jc, (uint32_t)p.nb, Af, Bf, p);
+            if (e) exact_flagged<NA, NB, true, CAL>(e, nullptr, (rb0 + it) * 64 * p.nb + jc, (uint32_t)p.nb, Af, Bf, p, &cal);
+        }
+    }
+    if (CAL) {
+        if (active) {
+            float* const dst = p.dpart + ((g / ntc) * p.nb + jc) * 1024;
+#pragma unroll
+            for (int e = 0; e < 16; ++e) dst[(8 * (e / 4) + 4 * (lane >> 5) + (e % 4)) * 32 + (lane & 31)] = cal.d[e];
+        }
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) cal.sq += __shfl_xor(cal.sq, off);
+        if (lane == 0) sq_lds[w] = cal.sq;
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            double s = 0.0;
+#pragma unroll
+            for (int i = 0; i < kTileCols; ++i) s += sq_lds[i];
+            p.sqpart[wg] = s;
         }
     }
 }
@@ -1317,7 +1484,7 @@ template <int NA, int NB>
 __global__ __launch_bounds__(64 * kTileCols) void kron_tile_calib_kernel(const CalibQuant c) {
     const bool w = blockIdx.x >= c.nx;
     const Params p = w ? c.p[1] : c.p[0];
-    kron_tile<NA, NB, true, true, false, false, true>(p, w ? c.rg[1] : c.rg[0], w ? blockIdx.x - c.nx : blockIdx.x,
+    kron_tile<NA, NB, true, false, false, false, true>(p, w ? c.rg[1] : c.rg[0], w ? blockIdx.x - c.nx : blockIdx.x,
                                                       w ? gridDim.x - c.nx : c.nx);
 }
 
@@ -1693,13 +1860,28 @@ static int tile_rows(const Params& p) {
     return rg < 1 ? 1 : rg > kTileMaxSteps ? kTileMaxSteps : (int)rg;
 }
 
+// The same for the calibration step's kernel, one workgroup of which fits a CU: the
+// steps that fill the rounds of 256 best, a strip's factors, block sums and first
+// loads costing about 0.7 of a step.
+static int calib_tile_rows(int64_t M, int64_t nb) {
+    const int64_t nrb = (M + 63) / 64, ntc = (nb + kTileCols - 1) / kTileCols;
+    auto cost = [&](int64_t rg) { return (double)(((nrb + rg - 1) / rg * ntc + 255) / 256) * ((double)rg + 0.7); };
+    int best = 1;
+    for (int rg = 2; rg <= kTileMaxSteps; ++rg)
+        if (cost(rg) < cost(best)) best = rg;
+    return best;
+}
+
+int64_t calib_quant_strips(int64_t M, int64_t nb) {
+    const int rg = calib_tile_rows(M, nb);
+    return ((M + 63) / 64 + rg - 1) / rg;
+}
+
 hipError_t launch_calib_quant(int a, const Params& px, const Params& pw, hipStream_t st) {
-    auto groups = [](const Params& p, int rg) {
-        return (((p.M + 63) / 64 + rg - 1) / rg) * ((p.nb + kTileCols - 1) / kTileCols);
-    };
-    CalibQuant c{{px, pw}, {tile_rows(px), tile_rows(pw)}, 0u};
-    c.nx = (uint32_t)groups(px, c.rg[0]);
-    const dim3 g(c.nx + (unsigned)groups(pw, c.rg[1])), b(64 * kTileCols);
+    auto groups = [](const Params& p) { return calib_quant_strips(p.M, p.nb) * ((p.nb + kTileCols - 1) / kTileCols); };
+    CalibQuant c{{px, pw}, {calib_tile_rows(px.M, px.nb), calib_tile_rows(pw.M, pw.nb)}, 0u};
+    c.nx = (uint32_t)groups(px);
+    const dim3 g(c.nx + (unsigned)groups(pw)), b(64 * kTileCols);
     switch (a) {
         case 4: hipLaunchKernelGGL((kron_tile_calib_kernel<4, 8>), g, b, 0, st, c); break;
         case 2: hipLaunchKernelGGL((kron_tile_calib_kernel<2, 16>), g, b, 0, st, c); break;

@@ -53,6 +53,11 @@ CASES = [
     (129, 130, 256, 8, True, "random"),
     (1, 1, 32, 4, False, "random"),
     (520, 72, 96, 1, True, "hadamard"),
+    # 128 x 128 backward tiles in K parts, ragged rows, features and column tile
+    (700, 1310, 544, 4, True, "random"),
+    # 256 x 256 tiles in K parts; shared factors sum over the blocks
+    (1490, 1510, 1056, 4, True, "random"),
+    (1501, 1480, 1056, 2, False, "random"),
 ]
 
 
