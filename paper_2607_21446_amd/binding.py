@@ -3,6 +3,10 @@
 Argument marshalling only: every step of the quantizer runs in the HIP
 kernels of the library.  torch supplies device memory and the current HIP
 stream.  There is no fallback: if the library is missing the first call raises.
+
+The calls that a loop repeats go through _kqbind (csrc/kq_bind.cpp), which makes
+the library call for plain arguments and returns None for all others; those come
+to the checks here, which name what is wrong.
 """
 from __future__ import annotations
 
@@ -79,6 +83,18 @@ def lib() -> ctypes.CDLL:
     L.kq_version.argtypes = []
     L.kq_version.restype = ctypes.c_int
     return L
+
+
+@lru_cache(maxsize=1)
+def _native():
+    """The binding's native part (built in-tree with the library)."""
+    lib()
+    try:
+        from . import _kqbind
+    except ImportError as e:
+        raise ImportError("_kqbind.so not found or not loadable; build it first "
+                          "(python -m paper_2607_21446_amd._build)") from e
+    return _kqbind
 
 
 def _check(status: int, call: str):
@@ -175,12 +191,18 @@ def quantize(X, A, B, codes=None, scales=None, y=None, want_y=False, stream=None
     """KroQuant quantizer kq_quantize (matrix-core path): X bf16 [M, d];
     A [nfac, a, a] and B [nfac, b, b] fp32 device tensors.
     Returns (codes, scales, y or None)."""
+    r = _native().quantize(X, A, B, codes, scales, y, want_y, stream)
+    if r is not None:
+        return r
     return _kron(lib().kq_quantize, "kq_quantize", X, A, B, codes, scales, y, want_y, stream)
 
 
 def quantize_exact(X, A, B, codes=None, scales=None, y=None, want_y=False, stream=None):
     """kq_quantize_exact: the same quantizer with the fixed-order fp32
     evaluation on the vector ALUs."""
+    r = _native().quantize_exact(X, A, B, codes, scales, y, want_y, stream)
+    if r is not None:
+        return r
     return _kron(lib().kq_quantize_exact, "kq_quantize_exact", X, A, B, codes, scales, y, want_y, stream)
 
 
@@ -203,6 +225,9 @@ def pack_factors(A, B, kpack=None, stream=None):
 
 def quantize_packed(X, A, B, kpack, codes=None, scales=None, y=None, want_y=False, stream=None):
     """kq_quantize_packed: kq_quantize with K read from kpack."""
+    r = _native().quantize_packed(X, A, B, kpack, codes, scales, y, want_y, stream)
+    if r is not None:
+        return r
     _need(X, torch.bfloat16, "X")
     _need(A, torch.float32, "A")
     _need(B, torch.float32, "B")
@@ -221,6 +246,9 @@ def quantize_lu(X, lu, a=4, codes=None, scales=None, y=None, y16=None, want_y=Fa
     """kq_quantize_lu: K2-form factors, lu fp32 [nfac, 5, 3] = (a_k, b_k, c_k)
     of G_1..G_5, decoded on chip; a = number of rows of A (1, 2, 4 or 8).
     Returns (codes, scales, y or None, y16 or None); y16 is bf16 [M, d]."""
+    r = _native().quantize_lu(X, lu, a, codes, scales, y, y16, want_y, want_y16, stream)
+    if r is not None:
+        return r
     _need(X, torch.bfloat16, "X")
     _need(lu, torch.float32, "lu")
     if lu.numel() % 15 or lu.numel() == 0:
@@ -241,6 +269,9 @@ def quantize_lu(X, lu, a=4, codes=None, scales=None, y=None, y16=None, want_y=Fa
 
 def smoothquant(X, mult, codes=None, scales=None, y=None, want_y=False, stream=None):
     """SmoothQuant comparator kq_smoothquant_quantize; mult fp32 [d] = 1/s."""
+    r = _native().smoothquant(X, mult, codes, scales, y, want_y, stream)
+    if r is not None:
+        return r
     _need(X, torch.bfloat16, "X")
     _need(mult, torch.float32, "mult")
     codes, scales, y = _outputs(X, codes, scales, y, want_y)
@@ -253,6 +284,9 @@ def smoothquant(X, mult, codes=None, scales=None, y=None, want_y=False, stream=N
 
 def hadamard32(X, codes=None, scales=None, y=None, want_y=False, stream=None):
     """Hadamard-32 comparator kq_hadamard32_quantize."""
+    r = _native().hadamard32(X, codes, scales, y, want_y, stream)
+    if r is not None:
+        return r
     _need(X, torch.bfloat16, "X")
     codes, scales, y = _outputs(X, codes, scales, y, want_y)
     M, d = X.shape
@@ -263,6 +297,9 @@ def hadamard32(X, codes=None, scales=None, y=None, want_y=False, stream=None):
 
 def fwht(X, codes=None, scales=None, y=None, want_y=False, stream=None):
     """Full-row FWHT comparator kq_fwht_quantize (d a power of two)."""
+    r = _native().fwht(X, codes, scales, y, want_y, stream)
+    if r is not None:
+        return r
     _need(X, torch.bfloat16, "X")
     codes, scales, y = _outputs(X, codes, scales, y, want_y)
     M, d = X.shape
@@ -276,6 +313,9 @@ def mxfp4_gemm(a_codes, a_scales, b_codes, b_scales, C=None, accumulate=False, s
     uint8 [rows, K/2], scales uint8 [rows, K/32]).  Returns C (fp32; with
     out_dtype=torch.bfloat16 or a bf16 C, kq_mxfp4_gemm_bf16: the product
     rounded to bf16, no accumulate)."""
+    r = _native().mxfp4_gemm(a_codes, a_scales, b_codes, b_scales, C, accumulate, stream, out_dtype)
+    if r is not None:
+        return r
     for t, name in ((a_codes, "a_codes"), (a_scales, "a_scales"), (b_codes, "b_codes"), (b_scales, "b_scales")):
         _need(t, torch.uint8, name)
     _matrix(a_codes, "a_codes")
@@ -305,6 +345,9 @@ def mxfp4_gemm(a_codes, a_scales, b_codes, b_scales, C=None, accumulate=False, s
 
 def mxfp4(X, codes=None, scales=None, stream=None):
     """Plain MXFP4 kq_mxfp4_quantize."""
+    r = _native().mxfp4(X, codes, scales, stream)
+    if r is not None:
+        return r
     _need(X, torch.bfloat16, "X")
     codes, scales, _ = _outputs(X, codes, scales, None, False)
     M, d = X.shape
@@ -461,6 +504,10 @@ def calib_step(X, W, Yneg, lu, lambdas, a=4, workspace=None, adam=None, grad=Non
     [nfac, 5, 3]) of the calibration objective at ``lu``; with
     ``adam = (m, v, t, lr)`` (t >= 1) also one Adam update of ``lu`` in place.
     ``lambdas``: device fp32 [2].  Returns (losses, grad)."""
+    if adam is None and workspace is not None:
+        r = _native().calib_step(X, W, Yneg, lu, lambdas, a, workspace, adam, grad, losses, stream)
+        if r is not None:
+            return r
     _need(X, torch.bfloat16, "X")
     _need(W, torch.bfloat16, "W")
     _need(Yneg, torch.float32, "Yneg")

@@ -927,3 +927,67 @@ def test_index_beyond_2_31_elements():
         _assert_mx_close_all(host(c), host(s), cr, sr, X, A, B, f"packed nfac={nfac}")
         del c, s, cr, sr
         torch.cuda.empty_cache()
+
+
+class _NoNative:
+    """Stands for the binding's native part and takes no call."""
+
+    def __getattr__(self, name):
+        return lambda *args: None
+
+
+@pytest.mark.parametrize("given", [False, True])
+def test_native_marshalling_matches_python(monkeypatch, given):
+    """Every call of the binding's native part returns what the checks and the
+    ctypes call in Python return: the same values, kinds and, for buffers that
+    were given, the same objects; an explicit stream and views with an offset
+    are taken, a non-contiguous or subclassed tensor goes to the Python checks."""
+    from paper_2607_21446_amd import binding
+    M, d, N = 70, 128, 96
+    g = torch.Generator(device="cuda")
+    g.manual_seed(3)
+    X = torch.randn((M + 1, d), generator=g, device="cuda").to(torch.bfloat16)[1:]
+    W = torch.randn((N, d), generator=g, device="cuda").to(torch.bfloat16)
+    A, B = (torch.from_numpy(t).cuda() for t in synth.factors(4, 8, 1, seed=1))
+    lu = torch.from_numpy(synth.lu_params(1, seed=2)).cuda()
+    mult = torch.rand(d, generator=g, device="cuda") + 0.5
+    kpack = kq.pack_factors(A, B)
+    wc, ws = kq.mxfp4(W)
+    lam = torch.tensor([0.5, 0.25], device="cuda")
+    Y = kq.calib_reference(X, W)
+    work = kq.calib_workspace(M, N, d, 4, 1)
+    bufs = lambda: dict(codes=torch.empty((M, d // 2), dtype=torch.uint8, device="cuda"),
+                        scales=torch.empty((M, d // 32), dtype=torch.uint8, device="cuda")) if given else {}
+    yb = lambda: dict(y=torch.empty((M, d), device="cuda")) if given else {}
+    st = torch.cuda.current_stream().cuda_stream if given else None
+    calls = [
+        lambda k: kq.quantize(X, A, B, want_y=True, stream=st, **k, **yb()),
+        lambda k: kq.quantize_exact(X, A, B, stream=st, **k),
+        lambda k: kq.quantize_packed(X, A, B, kpack, stream=st, **k, **yb()),
+        lambda k: kq.quantize_lu(X, lu, 4, want_y16=True, stream=st, **k),
+        lambda k: kq.smoothquant(X, mult, want_y=True, stream=st, **k),
+        lambda k: kq.hadamard32(X, stream=st, **k),
+        lambda k: kq.fwht(X, want_y=True, stream=st, **k),
+        lambda k: kq.mxfp4(X, stream=st, **k),
+        lambda k: (kq.mxfp4_gemm(*kq.mxfp4(X), wc, ws, stream=st, out_dtype=torch.bfloat16),),
+        lambda k: (kq.mxfp4_gemm(*kq.mxfp4(X), wc, ws, C=torch.ones((M, N), device="cuda"), accumulate=True, stream=st),),
+        lambda k: kq.calib_step(X, W, Y, lu, lam, a=4, workspace=work, stream=st),
+    ]
+    native = binding._native()
+    for i, call in enumerate(calls):
+        k = bufs()
+        monkeypatch.setattr(binding, "_native", lambda: native)
+        got = call(k)
+        if given and i < 8:
+            assert got[0] is k["codes"] and got[1] is k["scales"], i
+        monkeypatch.setattr(binding, "_native", _NoNative)
+        want = call(bufs())
+        assert type(got) is type(want) and len(got) == len(want), i
+        for a, b in zip(got, want):
+            assert (a is None) == (b is None), i
+            if a is not None:
+                assert a.dtype == b.dtype and a.shape == b.shape and torch.equal(a, b), i
+    assert native.mxfp4(X.t(), None, None, None) is None
+    assert native.mxfp4(X, torch.empty((M, d // 2 + 1), dtype=torch.uint8, device="cuda"), None, None) is None
+    assert native.mxfp4(X.as_subclass(type("Sub", (torch.Tensor,), {})), None, None, None) is None
+    assert native.quantize_lu(X, lu, 3, None, None, None, None, False, False, None) is None  # the library refuses it

@@ -317,3 +317,18 @@ def test_calib_step_noalloc_refuses_before_any_hip_call():
     assert L.kq_calib_step_noalloc(FAKE, 0, 64, FAKE, 8, FAKE, FAKE, 4, 1, FAKE, FAKE, FAKE, None, None, 0, 0.0,
                                    None) == INVALID
     assert kq.CALIB_NOALLOC_MAX_BYTES == 64 << 20
+
+
+def test_native_marshalling_leaves_other_arguments_to_python():
+    """The binding's native part takes plain device tensors only: everything
+    else comes back as None and meets the checks in Python."""
+    from paper_2607_21446_amd import binding
+    native = binding._native()
+    x = torch.zeros((2, 32), dtype=torch.bfloat16)
+    assert native.mxfp4(x, None, None, None) is None
+    assert native.mxfp4(None, None, None, None) is None
+    assert native.mxfp4(x) is None
+    assert native.quantize(x, x, x, None, None, None, False, None) is None
+    assert native.mxfp4_gemm(x, x, x, x, None, False, None, None) is None
+    with pytest.raises(TypeError, match="X must be a device tensor"):
+        kq.mxfp4(x)
