@@ -788,7 +788,7 @@ CalibPlan calib_plan(int64_t R, int64_t o, int64_t d, int a, int64_t nfac) {
     pl.nfac = nfac;
     pl.Rp = cdiv(std::max<int64_t>(R, 1), BK) * BK;
     pl.op = cdiv(o, BK) * BK;
-    pl.nsum = cdiv(pl.Rp, 128) * cdiv(pl.op, 128);
+    pl.nsum = std::max<int64_t>(256, cdiv(pl.Rp, 128) * cdiv(pl.op, 128));  // one per workgroup of the GEMM
     size_t off = 0;
     auto take = [&](size_t bytes) {
         const size_t at = off;

@@ -13,9 +13,9 @@
 // values times the two scales are exact in fp32; the sum over K is
 // accumulated in fp32 (order not specified).
 //
-// Kernels: the pipelined kernel below on a 256 x 256 (eight waves) or 128 x 128
-// (four waves) tile of C, for any K up to 2^24; a plain direct-load kernel for
-// longer rows, whose tile offsets pass 32 bits.
+// Kernels: a pipelined one on a 256 x 256 (eight waves) or 128 x 128 (four waves)
+// tile of C, for K up to 2^24 (32-bit offsets within a tile), and one whose waves
+// split K, on tiles of 32 x 32 to 64 x 64, for few tiles (and any K).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -36,19 +36,6 @@ struct Frag {
     uint4 codes;
     uint32_t scale;
 };
-
-__device__ __forceinline__ Frag load_frag(const uint8_t* __restrict__ codes, const uint8_t* __restrict__ scales,
-                                          int64_t row, int64_t nrows, int64_t kb, int64_t nkb, int64_t row_bytes) {
-    Frag f;
-    if (row < nrows && kb < nkb) {
-        f.codes = *reinterpret_cast<const uint4*>(codes + row * row_bytes + kb * 16);
-        f.scale = scales[row * nkb + kb];
-    } else {
-        f.codes = make_uint4(0u, 0u, 0u, 0u);  // zero codes contribute 0 whatever the scale
-        f.scale = 127u;
-    }
-    return f;
-}
 
 __device__ __forceinline__ i32x8 operand(const Frag& f) {
     i32x8 v = {(int)f.codes.x, (int)f.codes.y, (int)f.codes.z, (int)f.codes.w, 0, 0, 0, 0};
@@ -73,73 +60,66 @@ __device__ __forceinline__ void store_c4(const GemmParams& g, int64_t m, int64_t
     }
 }
 
-}  // namespace
-
-// K above kPipeMaxK: a 256-thread workgroup owns a 128 x 128 tile of C, its four
-// waves 64 x 64 quadrants; fragments straight from global memory, the next K
-// step's in flight while the current step's four instructions run.
-__global__ __launch_bounds__(256) void mxfp4_gemm_kernel(const GemmParams g) {
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int r = lane & 31, h = lane >> 5;
-    const int64_t m0 = (int64_t)blockIdx.y * 128 + (wave >> 1) * 64;
-    const int64_t n0 = (int64_t)blockIdx.x * 128 + (wave & 1) * 64;
-    const int64_t nkb = g.K / 32;                // 32-element blocks along K
-    const int64_t row_bytes = g.K / 2;           // code bytes per row
-    const int64_t nsteps = (nkb + 1) / 2;        // 64-wide K steps
-    f32x16g acc[2][2];
+// Four consecutive bf16 C values (8-byte stores where C allows 16-byte ones).
+__device__ __forceinline__ void store_b4(const GemmParams& g, int64_t m, int64_t n, float4 v) {
+    typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+    const bf16x4 b = {(__bf16)v.x, (__bf16)v.y, (__bf16)v.z, (__bf16)v.w};
+    const uint2 w = __builtin_bit_cast(uint2, b);
+    uint16_t* const c = g.C16 + m * g.ldc_out + n;
+    if (g.vec_ok && n + 3 < g.N) {
+        *reinterpret_cast<uint2*>(c) = w;
+    } else {
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j) acc[i][j] = f32x16g{};
-    Frag fa[2], fb[2];
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-        fa[i] = load_frag(g.a_codes, g.a_scales, m0 + 32 * i + r, g.M, h, nkb, row_bytes);
-        fb[i] = load_frag(g.b_codes, g.b_scales, n0 + 32 * i + r, g.N, h, nkb, row_bytes);
+        for (int e = 0; e < 4; ++e)
+            if (n + e < g.N) c[e] = (uint16_t)((e < 2 ? w.x : w.y) >> (16 * (e & 1)));
     }
-    for (int64_t s = 0; s < nsteps; ++s) {
-        Frag na[2], nbf[2];
-        const int64_t kb = 2 * (s + 1) + h;
-#pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            na[i] = load_frag(g.a_codes, g.a_scales, m0 + 32 * i + r, g.M, kb, nkb, row_bytes);
-            nbf[i] = load_frag(g.b_codes, g.b_scales, n0 + 32 * i + r, g.N, kb, nkb, row_bytes);
-        }
-#pragma unroll
-        for (int i = 0; i < 2; ++i)
-#pragma unroll
-            for (int j = 0; j < 2; ++j)
-                acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(
-                    operand(fa[i]), operand(fb[j]), acc[i][j], 4, 4, 0, (int)fa[i].scale, 0, (int)fb[j].scale);
-#pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            fa[i] = na[i];
-            fb[i] = nbf[i];
-        }
-    }
-    // acc[i][j][4q + e] = C[m0 + 32 i + 8 q + 4 h + e][n0 + 32 j + r]
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j) {
-            const int64_t col = n0 + 32 * j + r;
-            if (col >= g.N) continue;
-#pragma unroll
-            for (int q = 0; q < 4; ++q)
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const int64_t row = m0 + 32 * i + 8 * q + 4 * h + e;
-                    if (row >= g.M) continue;
-                    if (g.C16) {
-                        g.C16[row * g.ldc_out + col] = __builtin_bit_cast(uint16_t, (__bf16)acc[i][j][4 * q + e]);
-                        continue;
-                    }
-                    float* dst = g.C + row * g.ldc_out + col;
-                    const float base = g.bias ? g.bias[row * g.ldc_out + col] : g.accumulate ? *dst : 0.0f;
-                    *dst = (g.bias || g.accumulate) ? base + acc[i][j][4 * q + e] : acc[i][j][4 * q + e];
-                }
-        }
 }
+
+// Four consecutive values of the residual f = bias + product as two bf16 terms (zero
+// past M and N, up to rows_pad and ldr); their squares are added to sq.
+__device__ __forceinline__ void store_r4(const GemmParams& g, int64_t m, int64_t n, float4 v, double& sq) {
+    float f[4] = {v.x, v.y, v.z, v.w};
+    const float* const b = g.bias + m * g.ldc_out + n;
+    if (m < g.M && g.vec_ok && n + 3 < g.N) {
+        const float4 o = *reinterpret_cast<const float4*>(b);
+        f[0] = o.x + f[0];
+        f[1] = o.y + f[1];
+        f[2] = o.z + f[2];
+        f[3] = o.w + f[3];
+    } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) f[e] = (m < g.M && n + e < g.N) ? b[e] + f[e] : 0.0f;
+    }
+    uint32_t hi[2], lo[2];
+#pragma unroll
+    for (int e = 0; e < 4; e += 2) {
+        typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+        const bf16x2 h2 = {(__bf16)f[e], (__bf16)f[e + 1]};
+        const bf16x2 l2 = {(__bf16)(f[e] - (float)h2[0]), (__bf16)(f[e + 1] - (float)h2[1])};
+        hi[e / 2] = __builtin_bit_cast(uint32_t, h2);
+        lo[e / 2] = __builtin_bit_cast(uint32_t, l2);
+        sq += (double)f[e] * (double)f[e] + (double)f[e + 1] * (double)f[e + 1];
+    }
+    *reinterpret_cast<uint2*>(g.rh + m * g.ldr + n) = make_uint2(hi[0], hi[1]);
+    *reinterpret_cast<uint2*>(g.rl + m * g.ldr + n) = make_uint2(lo[0], lo[1]);
+}
+
+// The workgroup's sum of sq to its place (red: one entry per wave).
+template <int WAVES>
+__device__ __forceinline__ void block_squares(double sq, double* red, const GemmParams& g) {
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) sq += __shfl_xor(sq, off);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = sq;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        double tot = red[0];
+#pragma unroll
+        for (int i = 1; i < WAVES; ++i) tot += red[i];
+        g.sq_part[blockIdx.x] = tot;
+    }
+}
+
+}  // namespace
 
 // ------------------------------------------------------------------ pipelined kernels
 // K advances 128 (four 32-blocks) per stage.  Codes and scales go from global
@@ -482,51 +462,17 @@ __device__ __forceinline__ void store_tile(const GemmParams& g, uint8_t* lds, in
             } else if (OUT == 0) {
                 store_c4(g, m, n, __builtin_bit_cast(float4, v));
             } else {
-                const float4 c = __builtin_bit_cast(float4, v);
-                float f[4] = {c.x, c.y, c.z, c.w};
-                const float* const b = g.bias + m * g.ldc_out + n;
-                if (m < g.M && g.vec_ok && n + 3 < g.N) {
-                    const float4 o = *reinterpret_cast<const float4*>(b);
-                    f[0] = o.x + f[0];
-                    f[1] = o.y + f[1];
-                    f[2] = o.z + f[2];
-                    f[3] = o.w + f[3];
-                } else {
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) f[e] = (m < g.M && n + e < g.N) ? b[e] + f[e] : 0.0f;
-                }
-                uint32_t hi[2], lo[2];
-#pragma unroll
-                for (int e = 0; e < 4; e += 2) {
-                    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-                    const bf16x2 h2 = {(__bf16)f[e], (__bf16)f[e + 1]};
-                    const bf16x2 l2 = {(__bf16)(f[e] - (float)h2[0]), (__bf16)(f[e + 1] - (float)h2[1])};
-                    hi[e / 2] = __builtin_bit_cast(uint32_t, h2);
-                    lo[e / 2] = __builtin_bit_cast(uint32_t, l2);
-                    sq += (double)f[e] * (double)f[e] + (double)f[e + 1] * (double)f[e + 1];
-                }
-                *reinterpret_cast<uint2*>(g.rh + m * g.ldr + n) = make_uint2(hi[0], hi[1]);
-                *reinterpret_cast<uint2*>(g.rl + m * g.ldr + n) = make_uint2(lo[0], lo[1]);
+                store_r4(g, m, n, __builtin_bit_cast(float4, v), sq);
             }
         }
     }
     if (OUT == 2) {
         __syncthreads();
-        double* const red = reinterpret_cast<double*>(lds);
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) sq += __shfl_xor(sq, off);
-        if (lane == 0) red[wave] = sq;
-        __syncthreads();
-        if (t == 0) {
-            double tot = red[0];
-#pragma unroll
-            for (int i = 1; i < T::WAVES; ++i) tot += red[i];
-            g.sq_part[(int64_t)blockIdx.y * gridDim.x + blockIdx.x] = tot;
-        }
+        block_squares<T::WAVES>(sq, reinterpret_cast<double*>(lds), g);
     }
 }
 
-// Tile of workgroup (blockIdx.x, blockIdx.y) of a gx x gy grid.  Workgroups
+// Tile of workgroup blockIdx.x of gx x gy tiles.  Workgroups
 // are dealt to the 8 XCDs round-robin by linear id, so XCD k runs ids
 // k, k + 8, ...; those get consecutive logical ids (a bijection for any
 // count), and logical ids walk the tiles in groups of 4 M rows (N fastest
@@ -534,7 +480,7 @@ __device__ __forceinline__ void store_tile(const GemmParams& g, uint8_t* lds, in
 // block of about 4 x (T / 32) tiles instead of every M row.
 __device__ __forceinline__ void xcd_tile(int64_t gx, int64_t gy, int64_t& tn, int64_t& tm) {
     const int64_t T = gx * gy;
-    const int64_t i = (int64_t)blockIdx.y * gx + blockIdx.x;
+    const int64_t i = blockIdx.x;
     const int64_t k = i % 8, j = i / 8;
     const int64_t L = k * (T / 8) + (k < T % 8 ? k : T % 8) + j;
     constexpr int64_t GM = 4;
@@ -545,12 +491,156 @@ __device__ __forceinline__ void xcd_tile(int64_t gx, int64_t gy, int64_t& tn, in
     tn = (L % gsize) / gm;
 }
 
+// Few tiles: W waves share one tile of 32 TM (M) x 32 TN (N), each taking every W-th
+// 128-wide chunk of K with fragments straight from global memory (D chunks in flight),
+// and their sums meet in LDS in wave order.  With fewer tiles than CUs the pipelined
+// kernels walk K alone, a memory latency or more per few stages; here K is as wide as
+// the workgroup.
+template <int TN, int TM, int W, int D>
+__global__ __launch_bounds__(64 * W) void mxfp4_gemm_split_kernel(const GemmParams g, int64_t gx, int64_t gy) {
+    constexpr int BN = 32 * TN, BM = 32 * TM, RS = BN + 4;  // LDS row in floats
+    __shared__ float sums[W * BM * RS];
+    const int t = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(t >> 6), lane = t & 63;
+    const int r = lane & 31, h = lane >> 5;
+    int64_t tn, tm;
+    xcd_tile(gx, gy, tn, tm);
+    const int64_t nb0 = tn * BN, mb0 = tm * BM, nkb = g.K / 32, row_bytes = g.K / 2;
+    const int nch = (int)((nkb + 3) / 4), tb = (int)(nkb & 3);
+    // rows past N or M read the last row (their sums are never stored)
+    const uint8_t *cw[TN], *cx[TM], *sw[TN], *sx[TM];
+#pragma unroll
+    for (int i = 0; i < TN; ++i) {
+        const int64_t n = min(nb0 + 32 * i + r, g.N - 1);
+        cw[i] = g.b_codes + n * row_bytes;
+        sw[i] = g.b_scales + n * nkb;
+    }
+#pragma unroll
+    for (int j = 0; j < TM; ++j) {
+        const int64_t m = min(mb0 + 32 * j + r, g.M - 1);
+        cx[j] = g.a_codes + m * row_bytes;
+        sx[j] = g.a_scales + m * nkb;
+    }
+    struct Chunk {
+        uint4 w[2][TN], x[2][TM];
+        uint32_t sw[TN], sx[TM];
+    };
+    auto scales4 = [&](const uint8_t* p, int valid) {
+        typedef uint32_t u32u __attribute__((aligned(1)));
+        if (valid >= 4) return *reinterpret_cast<const u32u*>(p);
+        uint32_t v = p[0];
+        if (valid > 1) v |= (uint32_t)p[1] << 8;
+        if (valid > 2) v |= (uint32_t)p[2] << 16;
+        return v;
+    };
+    auto load = [&](int c, Chunk& f) {
+        const int valid = (tb && c == nch - 1) ? tb : 4;  // blocks of the chunk; those past K read its last block
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+            const int64_t at = 16 * (4 * (int64_t)c + min(2 * s + h, valid - 1));
+#pragma unroll
+            for (int i = 0; i < TN; ++i) f.w[s][i] = *reinterpret_cast<const uint4*>(cw[i] + at);
+#pragma unroll
+            for (int j = 0; j < TM; ++j) f.x[s][j] = *reinterpret_cast<const uint4*>(cx[j] + at);
+        }
+#pragma unroll
+        for (int i = 0; i < TN; ++i) f.sw[i] = scales4(sw[i] + 4 * (int64_t)c, valid);
+#pragma unroll
+        for (int j = 0; j < TM; ++j) f.sx[j] = scales4(sx[j] + 4 * (int64_t)c, valid);
+    };
+    const uint32_t psel = h ? 0x0c0c0301u : 0x0c0c0200u;
+    f32x16g acc[TN][TM];
+#pragma unroll
+    for (int i = 0; i < TN; ++i)
+#pragma unroll
+        for (int j = 0; j < TM; ++j) acc[i][j] = f32x16g{};
+    auto multiply = [&](int c, Chunk& f) {
+#pragma unroll
+        for (int i = 0; i < TN; ++i) f.sw[i] = __builtin_amdgcn_perm(0u, f.sw[i], psel);
+#pragma unroll
+        for (int j = 0; j < TM; ++j) f.sx[j] = __builtin_amdgcn_perm(0u, f.sx[j], psel);
+        if (tb && c == nch - 1) {  // blocks past K: zero codes, scale 1
+#pragma unroll
+            for (int s = 0; s < 2; ++s) {
+                const bool past = 2 * s + h >= tb;
+                const uint32_t keep = past ? 0u : ~0u, one = past ? 127u << (8 * s) : 0u, sm = past ? ~(255u << (8 * s)) : ~0u;
+#pragma unroll
+                for (int i = 0; i < TN; ++i) {
+                    f.w[s][i] = make_uint4(f.w[s][i].x & keep, f.w[s][i].y & keep, f.w[s][i].z & keep, f.w[s][i].w & keep);
+                    f.sw[i] = (f.sw[i] & sm) | one;
+                }
+#pragma unroll
+                for (int j = 0; j < TM; ++j) f.sx[j] = (f.sx[j] & sm) | one;
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < TN; ++i)
+#pragma unroll
+            for (int j = 0; j < TM; ++j)
+                acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(operand(Frag{f.w[0][i], 0u}),
+                                                                             operand(Frag{f.x[0][j], 0u}), acc[i][j], 4, 4,
+                                                                             0, (int)f.sw[i], 0, (int)f.sx[j]);
+#pragma unroll
+        for (int i = 0; i < TN; ++i)
+#pragma unroll
+            for (int j = 0; j < TM; ++j)
+                acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(operand(Frag{f.w[1][i], 0u}),
+                                                                             operand(Frag{f.x[1][j], 0u}), acc[i][j], 4, 4,
+                                                                             1, (int)f.sw[i], 1, (int)f.sx[j]);
+    };
+    Chunk f[D];
+#pragma unroll
+    for (int u = 0; u < D; ++u)
+        if (wave + u * W < nch) load(wave + u * W, f[u]);
+    for (int c = wave; c < nch; c += D * W) {
+#pragma unroll
+        for (int u = 0; u < D; ++u) {
+            const int cu = c + u * W;
+            if (cu < nch) {
+                multiply(cu, f[u]);
+                if (cu + D * W < nch) load(cu + D * W, f[u]);
+            }
+        }
+    }
+    // acc[i][j][4q + e] = (row 32 j + r, column 32 i + 8 q + 4 h + e)
+    const int active = min(W, nch);
+    if (wave < active) {
+#pragma unroll
+        for (int j = 0; j < TM; ++j)
+#pragma unroll
+            for (int i = 0; i < TN; ++i)
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    *reinterpret_cast<float4*>(sums + (wave * BM + 32 * j + r) * RS + 32 * i + 8 * q + 4 * h) =
+                        make_float4(acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]);
+    }
+    __syncthreads();
+    const int64_t mend = g.rh ? g.rows_pad : g.M, nend = g.rh ? g.ldr : g.N;
+    double sq = 0.0;
+    for (int k = t; k < BM * BN / 4; k += 64 * W) {
+        const int row = k / (BN / 4), col = 4 * (k % (BN / 4));
+        const int64_t m = mb0 + row, n = nb0 + col;
+        if (m >= mend || n >= nend) continue;
+        float4 v = *reinterpret_cast<const float4*>(sums + row * RS + col);
+        for (int w = 1; w < active; ++w) {
+            const float4 o = *reinterpret_cast<const float4*>(sums + (w * BM + row) * RS + col);
+            v = make_float4(v.x + o.x, v.y + o.y, v.z + o.z, v.w + o.w);
+        }
+        if (g.C16) store_b4(g, m, n, v);
+        else if (g.rh) store_r4(g, m, n, v, sq);
+        else store_c4(g, m, n, v);
+    }
+    if (g.rh) {
+        __shared__ double red[W];
+        block_squares<W>(sq, red, g);
+    }
+}
+
 template <int WN, int WM, int TN, int TM, bool PING, bool DMA_SCALES>
-__global__ __launch_bounds__(64 * WN * WM) void mxfp4_gemm_pipe_kernel(const GemmParams g) {
+__global__ __launch_bounds__(64 * WN * WM) void mxfp4_gemm_pipe_kernel(const GemmParams g, int64_t gx, int64_t gy) {
     typedef Tile<WN, WM, TN, TM> T;
     __shared__ typename T::Lds lds;
     int64_t tn, tm;
-    xcd_tile(gridDim.x, gridDim.y, tn, tm);
+    xcd_tile(gx, gy, tn, tm);
     f32x16g acc[TN][TM];
     gemm_tile<WN, WM, TN, TM, PING, DMA_SCALES>(g, lds, tn * T::BN, tm * T::BM, acc);
     uint8_t* const stage = reinterpret_cast<uint8_t*>(&lds);
@@ -559,41 +649,64 @@ __global__ __launch_bounds__(64 * WN * WM) void mxfp4_gemm_pipe_kernel(const Gem
     else store_tile<WN, WM, TN, TM, 0>(g, stage, tn * T::BN, tm * T::BM, acc);
 }
 
-constexpr int64_t kBigTileMin = 96;  // 256 x 256 tiles needed before that kernel is chosen
+// The pipelined kernels index a tile's 256 rows with 32-bit byte offsets.
+constexpr int64_t kPipeMaxK = int64_t(1) << 24;
+
+// Tile of a call.  Measured, us (bf16 C, K 512 / 1152 / 3072 / 9600):
+//   32 x 32 split (8 waves)     128 x  512: 3.3 / 3.7 /  6.9 / 10.9; 128 x 128 5.1 / 7.0 / 12.1 / 30.7
+//   32 (M) x 64 (N) split       256 x 1152: 3.9 / 4.3 /  9.4 / 18.6; 32 x 32 3.9 / 4.5 / 11.0 / 22.0
+//   64 x 64 split               512 x 2048: 4.9 / 6.1 / 12.8 / 25.9; 128 x 128 5.4 / 7.3 / 13.1 / 32.4
+//   128 x 128 pipelined         512 x 4096: 5.7 / 7.8 / 13.8 / 32.8; 64 x 64 8.4 / 10.8 / 24.0 / 47.9
+//                              4096 x 2048: 9.5 / 13.5 / 24.3 / 63.8; 256 x 256 11.7 / 16.7 / 27.1 / 64.6
+//   256 x 256 pipelined        3000 x 3000: 12.3 / 16.5 / 26.3 / 64.8; 128 x 128 12.5 / 17.6 / 31.0 / 84.8
+// So the smallest split tile that still gives a CU no more than one workgroup, and
+// past 256 tiles of 64 x 64 the pipelined tile that needs fewer rounds (two 128 x
+// 128 workgroups share a CU and take as long as one of 256 x 256).
+enum class GemmTile { Split32, Split32x64, Split64, Pipe128, Pipe256 };
+
+static GemmTile gemm_tile_of(const GemmParams& g) {
+    auto tiles = [&](int64_t tm, int64_t tn) { return ((g.M + tm - 1) / tm) * ((g.N + tn - 1) / tn); };
+    if (tiles(32, 32) <= 256) return GemmTile::Split32;
+    if (tiles(32, 64) <= 256) return GemmTile::Split32x64;
+    if (tiles(64, 64) <= 256 || g.K > kPipeMaxK) return GemmTile::Split64;
+    return (tiles(128, 128) + 511) / 512 <= (tiles(256, 256) + 255) / 256 ? GemmTile::Pipe128 : GemmTile::Pipe256;
+}
+
+int64_t mxfp4_gemm_workgroups(const GemmParams& g) {
+    auto tiles = [&](int64_t tm, int64_t tn) { return ((g.M + tm - 1) / tm) * ((g.N + tn - 1) / tn); };
+    switch (gemm_tile_of(g)) {
+        case GemmTile::Split32: return tiles(32, 32);
+        case GemmTile::Split32x64: return tiles(32, 64);
+        case GemmTile::Split64: return tiles(64, 64);
+        case GemmTile::Pipe128: return tiles(128, 128);
+        default: return tiles(256, 256);
+    }
+}
+
+template <int TN, int TM, int W, int D>
+static void launch_split(const GemmParams& g, hipStream_t st) {
+    const int64_t gx = (g.N + 32 * TN - 1) / (32 * TN), gy = (g.M + 32 * TM - 1) / (32 * TM);
+    hipLaunchKernelGGL((mxfp4_gemm_split_kernel<TN, TM, W, D>), dim3((unsigned)(gx * gy)), dim3(64 * W), 0, st, g, gx, gy);
+}
 
 template <int WN, int WM, int TN, int TM, bool PING>
 static void launch_pipe(const GemmParams& g, hipStream_t st) {
     typedef Tile<WN, WM, TN, TM> T;
-    const int64_t nkb = g.K / 32;
-    const dim3 grid((unsigned)((g.N + T::BN - 1) / T::BN), (unsigned)((g.M + T::BM - 1) / T::BM)), b(64 * T::WAVES);
+    const int64_t nkb = g.K / 32, gx = (g.N + T::BN - 1) / T::BN, gy = (g.M + T::BM - 1) / T::BM;
+    const dim3 grid((unsigned)(gx * gy)), b(64 * T::WAVES);
     if (nkb % 4 == 0 && nkb >= 16 && g.scales_aligned)
-        hipLaunchKernelGGL((mxfp4_gemm_pipe_kernel<WN, WM, TN, TM, PING, true>), grid, b, 0, st, g);
+        hipLaunchKernelGGL((mxfp4_gemm_pipe_kernel<WN, WM, TN, TM, PING, true>), grid, b, 0, st, g, gx, gy);
     else
-        hipLaunchKernelGGL((mxfp4_gemm_pipe_kernel<WN, WM, TN, TM, PING, false>), grid, b, 0, st, g);
-}
-
-// The pipelined kernels index a tile's 256 rows with 32-bit byte offsets.
-constexpr int64_t kPipeMaxK = int64_t(1) << 24;
-
-static bool big_tiles(const GemmParams& g) { return ((g.N + 255) / 256) * ((g.M + 255) / 256) >= kBigTileMin; }
-
-int64_t mxfp4_gemm_workgroups(const GemmParams& g) {
-    const int64_t t = big_tiles(g) ? 256 : 128;
-    return ((g.N + t - 1) / t) * ((g.M + t - 1) / t);
+        hipLaunchKernelGGL((mxfp4_gemm_pipe_kernel<WN, WM, TN, TM, PING, false>), grid, b, 0, st, g, gx, gy);
 }
 
 hipError_t launch_mxfp4_gemm(const GemmParams& g, hipStream_t st) {
-    // the 256 x 256 tile once there are enough of them to spread over the chip, else 128 x 128
-    // (16-byte code and scale loads per row: any K; us before, with K % 128 != 0 on the direct
-    // kernel, and now: 4096 x 5600 x 2240 151 and 49, 4608 x 3072 x 3072 41.1 and 34.3,
-    // 4608 x 3072 x 12288 124 and 98, 1000 x 3456 x 1152 12.0 and 8.1)
-    if (g.K <= kPipeMaxK && big_tiles(g)) {
-        launch_pipe<2, 4, 4, 2, true>(g, st);
-    } else if (g.K <= kPipeMaxK) {
-        launch_pipe<2, 2, 2, 2, false>(g, st);
-    } else {
-        const dim3 grid((unsigned)((g.N + 127) / 128), (unsigned)((g.M + 127) / 128));
-        hipLaunchKernelGGL(mxfp4_gemm_kernel, grid, dim3(256), 0, st, g);
+    switch (gemm_tile_of(g)) {
+        case GemmTile::Split32: launch_split<1, 1, 8, 4>(g, st); break;
+        case GemmTile::Split32x64: launch_split<2, 1, 8, 3>(g, st); break;
+        case GemmTile::Split64: launch_split<2, 2, 8, 2>(g, st); break;
+        case GemmTile::Pipe128: launch_pipe<2, 2, 2, 2, false>(g, st); break;
+        case GemmTile::Pipe256: launch_pipe<2, 4, 4, 2, true>(g, st); break;
     }
     return hipGetLastError();
 }

@@ -60,7 +60,7 @@ struct GemmParams {
     const float* bias = nullptr;  // if set: C = bias + product (bias [M, ldc_out], vec rule as C)
     uint16_t* C16 = nullptr;      // if set: bf16 output [M, ldc_out] instead of C (no bias, no accumulate)
     // if rh is set: no C; v = bias + product goes out as the bf16 terms of v, [rows_pad, ldr]
-    // (zero beyond M and N), and every workgroup's sum of v^2 (K at most 2^24)
+    // (zero beyond M and N; both less than 32 past them), and every workgroup's sum of v^2
     uint16_t* rh = nullptr;
     uint16_t* rl = nullptr;
     int64_t ldr = 0, rows_pad = 0;
@@ -71,7 +71,7 @@ struct GemmParams {
 
 hipError_t launch(Kind kind, int a, const Params& p, Mapping map, hipStream_t st);
 hipError_t launch_mxfp4_gemm(const GemmParams& g, hipStream_t st);
-int64_t mxfp4_gemm_workgroups(const GemmParams& g);  // of the call, for K up to 2^24
+int64_t mxfp4_gemm_workgroups(const GemmParams& g);  // of the call: at most max(256, 128 x 128 tiles)
 // The calibration step's two operands in one launch: px with the factors of its LU
 // parameters, pw with those of the inverse blocks; codes, scales and the calibration
 // outputs of both.  An operand of M rows and nb blocks takes calib_quant_strips(M, nb)

@@ -629,16 +629,21 @@ def test_mxfp4_gemm_parity(M, N, K):
     assert np.all(np.abs(host(Cd) - (ref + C0)) <= tol + 2.0 ** -23 * np.abs(ref + C0))
 
 
-@pytest.mark.parametrize("M,N,K", [(1, 1, 64), (129, 257, 96), (127, 130, 160), (129, 127, 480), (129, 129, 512),
-                                   (130, 1, 544), (129, 200, 640), (200, 129, 672), (129, 65, 1920), (2500, 2470, 672),
-                                   (2305, 2561, 640), (2500, 2470, 1152), (3, 2, (1 << 24) + 32)])
+@pytest.mark.parametrize("M,N,K", [
+    # 32 x 32, 32 x 64 and 64 x 64 tiles whose waves split K: one chunk, fewer chunks than waves, several rounds
+    (1, 1, 32), (33, 65, 160), (129, 257, 96), (3, 2, (1 << 24) + 32), (256, 1030, 1120), (250, 1250, 5280),
+    (1000, 1000, 480), (1030, 990, 4192),
+    # 128 x 128
+    (1025, 1153, 96), (1025, 1153, 512), (2050, 1150, 544), (1000, 1300, 640), (1500, 1409, 672), (2500, 2470, 1920),
+    # 256 x 256
+    (3000, 3001, 160), (3001, 2900, 512), (2950, 3100, 640), (3000, 2999, 672)])
 @pytest.mark.parametrize("off", [0, 1])
 def test_mxfp4_gemm_k_tails(M, N, K, off):
     """Every form of the last K stage and of the scale rows: 1 to 4 blocks in
     the last stage, rows of scales that are and are not a multiple of 4 and of
     16 bytes, fewer than 16 of them, scales that start at an odd address, tiles
-    that end past the last row, both tile sizes, and the kernel for rows beyond
-    the pipelined kernels' 32-bit offsets."""
+    that end past the last row, and every tile of the dispatch; fp32, added to
+    C, and bf16."""
     ac, as_ = _rand_mx(M, K, seed=M + K)
     bc, bs = _rand_mx(N, K, seed=N + 2 * K)
     ref = oracle.mxfp4_gemm(ac, as_, bc, bs)
@@ -649,8 +654,13 @@ def test_mxfp4_gemm_k_tails(M, N, K, off):
         buf[o:] = torch.from_numpy(a).cuda().reshape(-1)
         return buf[o:].view(a.shape)
 
-    C = host(kq.mxfp4_gemm(t(ac), t(as_, off), t(bc), t(bs, off)))
+    ops = (t(ac), t(as_, off), t(bc), t(bs, off))
+    C = host(kq.mxfp4_gemm(*ops))
     assert np.all(np.abs(C - ref) <= tol), np.max(np.abs(C - ref) - tol)
+    one = torch.ones((M, N), device="cuda")
+    assert np.array_equal(host(kq.mxfp4_gemm(*ops, C=one, accumulate=True)), np.float32(1.0) + C)
+    c16 = host(kq.mxfp4_gemm(*ops, out_dtype=torch.bfloat16).view(torch.int16)).view(np.uint16)
+    assert np.array_equal(c16, oracle.f32_to_bf16(C))
 
 
 @pytest.mark.parametrize("M,N,K", [(77, 200, 2240), (33, 70, 1120), (300, 257, 3072), (5, 3, 128), (3000, 2200, 384),
