@@ -743,20 +743,31 @@ int64_t cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }
 // stages in ks parts.
 struct SidePlan {
     int64_t mt, ntn, stages, ks;
-    // In units of a stage of a 256 x 256 tile on one CU: rounds of the chip, each a K
-    // part and its epilogue.  A 128 x 128 workgroup has a quarter of the work, two
-    // share a CU, and its stage feeds half the products per byte.
-    double cost(bool big) const {
-        const double stage = big ? 1.0 : 0.8, epi = big ? 6.0 : 3.0;
-        return double(cdiv(mt * ntn * ks, big ? 256 : 512)) * (stage * double(cdiv(stages, ks)) + epi);
-    }
-    // The K parts (of at least four stages) that fill the rounds best.
-    void choose_parts(bool big) {
-        SidePlan s = *this;
-        for (s.ks = 2; s.ks <= 16 && 4 * s.ks <= stages; ++s.ks)
-            if (s.cost(big) < 0.97 * cost(big)) ks = s.ks;
-    }
+    double works() const { return double(mt * ntn * ks); }
+    // A work's length in stages of a 256 x 256 tile: its K part and its epilogue.  A 128 x
+    // 128 workgroup has a quarter of the products, two share a CU, and its stage feeds
+    // half the products per byte.
+    double length(bool big) const { return (big ? 1.0 : 0.65) * double(cdiv(stages, ks)) + (big ? 12.0 : 5.0); }
 };
+
+// Cost of the launch, `act` works first and `wgt` works into the slots as they come
+// free: the time of the last one plus the mean load of a slot (idle slots leave the
+// others clock and bandwidth).  2048 x 1152 x 1152, step in us: parts 1 and 4 72.4,
+// 1 and 1 84.4, 3 and 6 76.8; 4096 x 1152 x 4608: 1 and 2 247, 2 and 5 296, 1 and 1 292.
+static double backward_cost(const SidePlan& act, const SidePlan& wgt, bool big) {
+    const double S = big ? 256.0 : 512.0, n1 = act.works(), l1 = act.length(big), n2 = wgt.works(), l2 = wgt.length(big);
+    const double q = std::floor(n1 / S), busy = n1 - q * S;    // slots that take a last act work
+    const double early = q * l1, late = busy > 0 ? early + l1 : early;
+    // works that end by t: slots free at `early` and slots free at `late`
+    auto done = [&](double t) {
+        return (S - busy) * std::floor((t - early) / l2 + 1e-9) + busy * std::max(0.0, std::floor((t - late) / l2 + 1e-9));
+    };
+    const double k = std::floor(n2 / S);
+    double end = std::max(late, early + (k + 2.0) * l2);
+    for (const double t : {early + k * l2, early + (k + 1.0) * l2, late + k * l2, late + (k > 0 ? k - 1.0 : 0.0) * l2})
+        if (t >= late && t < end && done(t) >= n2) end = t;
+    return end + (n1 * l1 + n2 * l2) / S;
+}
 
 // The least workspace a caller is told of: 6.6 R d + 12 R o + 6.6 o d bytes and the
 // partial sums of 128-row tiles, of which the step now uses less.  Kept, so that
@@ -822,24 +833,28 @@ CalibPlan calib_plan(int64_t R, int64_t o, int64_t d, int a, int64_t nfac) {
     // as many K parts as the partial sums have room for in the workspace that is told anyway
     const size_t told = told_workspace(R, o, d, a, nfac), slot = size_t(pl.nb) * 4096;
     const int64_t room = told > off ? int64_t((told - off) / slot) : 0;
-    double best = 0.0;
+    double best = HUGE_VAL;
     for (const bool big : {true, false}) {
         const int64_t T = big ? 256 : 128, ntn = cdiv(d, T);
         SidePlan act{cdiv(R, T), ntn, pl.op / BK, 1}, wgt{cdiv(o, T), ntn, pl.Rp / BK, 1};
-        act.choose_parts(big);
-        wgt.choose_parts(big);
-        while ((act.ks > 1 || wgt.ks > 1) && act.mt * act.ks + wgt.mt * wgt.ks > room)
-            --(wgt.ks == 1 || (act.ks > 1 && act.mt * act.ks >= wgt.mt * wgt.ks) ? act : wgt).ks;
-        const double cost = act.cost(big) + wgt.cost(big);
-        if (big || cost < best) {
-            best = cost;
-            pl.big = big;
-            pl.ntn = ntn;
-            pl.act_mt = act.mt;
-            pl.act_kchunk = cdiv(act.stages, act.ks) * BK;
-            pl.w_mt = wgt.mt;
-            pl.w_kchunk = cdiv(wgt.stages, wgt.ks) * BK;
-        }
+        constexpr int64_t kParts[] = {1, 2, 3, 4, 6, 8};
+        for (const int64_t ka : kParts)
+            for (const int64_t kw : kParts) {
+                // a part has at least four stages
+                if ((ka > 1 && 4 * ka > act.stages) || (kw > 1 && 4 * kw > wgt.stages)) continue;
+                if ((ka > 1 || kw > 1) && act.mt * ka + wgt.mt * kw > room) continue;
+                act.ks = ka;
+                wgt.ks = kw;
+                const double cost = backward_cost(act, wgt, big);
+                if (cost >= best) continue;
+                best = cost;
+                pl.big = big;
+                pl.ntn = ntn;
+                pl.act_mt = act.mt;
+                pl.act_kchunk = cdiv(act.stages, ka) * BK;
+                pl.w_mt = wgt.mt;
+                pl.w_kchunk = cdiv(wgt.stages, kw) * BK;
+            }
     }
     pl.act_ks = cdiv(pl.op, pl.act_kchunk);
     pl.w_ks = cdiv(pl.Rp, pl.w_kchunk);

@@ -56,8 +56,8 @@ CASES = [
     # 128 x 128 backward tiles in K parts, ragged rows, features and column tile
     (700, 1310, 544, 4, True, "random"),
     # 256 x 256 tiles in K parts; shared factors sum over the blocks
-    (1490, 1510, 1056, 4, True, "random"),
-    (1501, 1480, 1056, 2, False, "random"),
+    (2803, 701, 2080, 4, True, "random"),
+    (2300, 1290, 1568, 2, False, "random"),
 ]
 
 
