@@ -42,22 +42,38 @@ __device__ __forceinline__ i32x8 operand(const Frag& f) {
     return v;
 }
 
-// Four consecutive fp32 C values of row m from column n, with the bias or the accumulate mode.
+// Four consecutive fp32 C values of row m from column n.  (One vector access: as
+// float4, four members, the compiler shared the last with the other branch.)
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ void store_c4(const GemmParams& g, int64_t m, int64_t n, float4 v) {
-    float* crow = g.C + m * g.ldc_out;
-    const float* brow = g.bias ? g.bias + m * g.ldc_out : g.accumulate ? crow : nullptr;
+    float* const c = g.C + m * g.ldc_out + n;
     if (g.vec_ok && n + 3 < g.N) {
-        if (brow) {
-            const float4 o = *reinterpret_cast<const float4*>(brow + n);
-            v = make_float4(o.x + v.x, o.y + v.y, o.z + v.z, o.w + v.w);
-        }
-        *reinterpret_cast<float4*>(crow + n) = v;
+        *reinterpret_cast<f32x4*>(c) = f32x4{v.x, v.y, v.z, v.w};
     } else {
-        if (n + 0 < g.N) crow[n + 0] = brow ? brow[n + 0] + v.x : v.x;
-        if (n + 1 < g.N) crow[n + 1] = brow ? brow[n + 1] + v.y : v.y;
-        if (n + 2 < g.N) crow[n + 2] = brow ? brow[n + 2] + v.z : v.z;
-        if (n + 3 < g.N) crow[n + 3] = brow ? brow[n + 3] + v.w : v.w;
+        c[0] = v.x;
+        if (n + 1 < g.N) c[1] = v.y;
+        if (n + 2 < g.N) c[2] = v.z;
+        if (n + 3 < g.N) c[3] = v.w;
     }
+}
+
+// The values they are added to: the bias, C (accumulate) or zeros; zeros past M and N.
+__device__ __forceinline__ float4 base_c4(const GemmParams& g, int64_t m, int64_t n) {
+    float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+    const float* const src = g.bias ? g.bias : g.accumulate ? g.C : nullptr;
+    if (src && m < g.M && n < g.N) {
+        const float* const b = src + m * g.ldc_out + n;
+        if (g.vec_ok && n + 3 < g.N) {
+            const f32x4 o = *reinterpret_cast<const f32x4*>(b);
+            v = make_float4(o.x, o.y, o.z, o.w);
+        } else {
+            v.x = b[0];
+            if (n + 1 < g.N) v.y = b[1];
+            if (n + 2 < g.N) v.z = b[2];
+            if (n + 3 < g.N) v.w = b[3];
+        }
+    }
+    return v;
 }
 
 // Four consecutive bf16 C values (8-byte stores where C allows 16-byte ones).
@@ -75,21 +91,12 @@ __device__ __forceinline__ void store_b4(const GemmParams& g, int64_t m, int64_t
     }
 }
 
-// Four consecutive values of the residual f = bias + product as two bf16 terms (zero
-// past M and N, up to rows_pad and ldr); their squares are added to sq.
+// Four consecutive values of the residual as two bf16 terms (zero past M and N, up to
+// rows_pad and ldr); their squares are added to sq.
 __device__ __forceinline__ void store_r4(const GemmParams& g, int64_t m, int64_t n, float4 v, double& sq) {
-    float f[4] = {v.x, v.y, v.z, v.w};
-    const float* const b = g.bias + m * g.ldc_out + n;
-    if (m < g.M && g.vec_ok && n + 3 < g.N) {
-        const float4 o = *reinterpret_cast<const float4*>(b);
-        f[0] = o.x + f[0];
-        f[1] = o.y + f[1];
-        f[2] = o.z + f[2];
-        f[3] = o.w + f[3];
-    } else {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) f[e] = (m < g.M && n + e < g.N) ? b[e] + f[e] : 0.0f;
-    }
+    const bool in = m < g.M;
+    const float f[4] = {in && n < g.N ? v.x : 0.f, in && n + 1 < g.N ? v.y : 0.f, in && n + 2 < g.N ? v.z : 0.f,
+                        in && n + 3 < g.N ? v.w : 0.f};
     uint32_t hi[2], lo[2];
 #pragma unroll
     for (int e = 0; e < 4; e += 2) {
@@ -402,7 +409,12 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& g, typename Tile<WN,
 // OUT 0: fp32 (bias, accumulate); 1: bf16; 2: the residual v = bias + product as its
 // two bf16 terms hi = bf16(v), lo = bf16(v - hi), zero in the padding columns and
 // rows up to ldr and rows_pad, and the workgroup's sum of v^2 (fp64).
-template <int WN, int WM, int TN, int TM, int OUT>
+//
+// BASE (the bias or C is added): all loads of a pass are issued before its stores (a
+// wait for a load waits for every store issued before it too).
+// 4096 x 5600 x 2240 and 18432 x 3072 x 3072 onto C, us: 104 and 220 with the loads
+// among the stores, 88 and 188 so.
+template <int WN, int WM, int TN, int TM, int OUT, bool BASE>
 __device__ __forceinline__ void store_tile(const GemmParams& g, uint8_t* lds, int64_t nb0, int64_t mb0,
                                            const f32x16g (&acc)[TN][TM]) {
     typedef Tile<WN, WM, TN, TM> T;
@@ -413,10 +425,29 @@ __device__ __forceinline__ void store_tile(const GemmParams& g, uint8_t* lds, in
     constexpr int RB = T::BN / NP * ES, RS = RB + 16;  // data and stride of a row in bytes
     static_assert(T::BM * RS <= (int)sizeof(typename T::Lds), "a pass fits LDS");
     constexpr int CPR = RB / 16, EPC = 16 / ES;    // 16-byte chunks per row, elements per chunk
+    constexpr int CH = T::BM * CPR / (64 * T::WAVES);  // chunks per thread and pass
     const int t = threadIdx.x;
     const int wave = t >> 6, lane = t & 63;
     const int r = lane & 31, h = lane >> 5, wn = wave / WM, wm = wave % WM;
     const int64_t mend = OUT == 2 ? g.rows_pad : g.M, nend = OUT == 2 ? g.ldr : g.N;
+    // row and column of C of chunk k of pass p: the pass holds TP tiles of each of the WN
+    // waves' column ranges
+    auto place = [&](int t1, int p, int k, int64_t& m, int64_t& n) {
+        const int id = t1 + k * 64 * T::WAVES, row = id / CPR, cl = (id % CPR) * EPC, seg = cl / (32 * TP);
+        m = mb0 + row;
+        n = nb0 + seg * 32 * TN + 32 * p * TP + (cl - seg * 32 * TP);
+    };
+    float4 base[BASE ? CH : 1];
+    auto fetch = [&](int p) {
+        int t1 = t;
+        asm volatile("" : "+v"(t1));  // these addresses are not kept for the stores
+#pragma unroll
+        for (int k = 0; k < CH; ++k) {
+            int64_t m, n;
+            place(t1, p, k, m, n);
+            base[k] = base_c4(g, m, n);
+        }
+    };
     double sq = 0.0;
 #pragma unroll
     for (int p = 0; p < NP; ++p) {
@@ -439,16 +470,18 @@ __device__ __forceinline__ void store_tile(const GemmParams& g, uint8_t* lds, in
                     }
                 }
             }
+        __builtin_amdgcn_sched_barrier(0);  // the pass's accumulators are free for what is loaded
+        if (BASE) fetch(p);
         __syncthreads();
-#pragma unroll 4
-        for (int k = 0; k < T::BM * CPR / (64 * T::WAVES); ++k) {
-            const int id = t + k * 64 * T::WAVES;
-            const int row = id / CPR, ch = id % CPR;
-            // column of the chunk: the pass holds TP tiles of each of the WN waves' column ranges
-            const int cl = ch * EPC, seg = cl / (32 * TP);
-            const int64_t m = mb0 + row, n = nb0 + seg * 32 * TN + 32 * p * TP + (cl - seg * 32 * TP);
+        int t2 = t;
+        if (BASE) asm volatile("" : "+v"(t2));
+#pragma unroll BASE ? CH : 4
+        for (int k = 0; k < CH; ++k) {
+            const int id = t2 + k * 64 * T::WAVES;
+            int64_t m, n;
+            place(t2, p, k, m, n);
             if (m >= mend || n >= nend) continue;
-            const uint4 v = *reinterpret_cast<const uint4*>(lds + row * RS + 16 * ch);
+            const uint4 v = *reinterpret_cast<const uint4*>(lds + id / CPR * RS + 16 * (id % CPR));
             if (BF16) {
                 uint16_t* const c = g.C16 + m * g.ldc_out + n;
                 if (g.vec_ok && n + 7 < g.N) {
@@ -459,11 +492,15 @@ __device__ __forceinline__ void store_tile(const GemmParams& g, uint8_t* lds, in
                     for (int e = 0; e < 8; ++e)
                         if (n + e < g.N) c[e] = (uint16_t)(w[e / 2] >> (16 * (e & 1)));
                 }
-            } else if (OUT == 0) {
-                store_c4(g, m, n, __builtin_bit_cast(float4, v));
-            } else {
-                store_r4(g, m, n, __builtin_bit_cast(float4, v), sq);
+                continue;
             }
+            float4 f = __builtin_bit_cast(float4, v);
+            if (BASE) {
+                const float4 o = base[k];
+                f = make_float4(o.x + f.x, o.y + f.y, o.z + f.z, o.w + f.w);
+            }
+            if (OUT == 0) store_c4(g, m, n, f);
+            else store_r4(g, m, n, f, sq);
         }
     }
     if (OUT == 2) {
@@ -620,11 +657,14 @@ __global__ __launch_bounds__(64 * W) void mxfp4_gemm_split_kernel(const GemmPara
         const int row = k / (BN / 4), col = 4 * (k % (BN / 4));
         const int64_t m = mb0 + row, n = nb0 + col;
         if (m >= mend || n >= nend) continue;
+        const bool based = g.bias || g.accumulate;
+        const float4 b = based ? base_c4(g, m, n) : make_float4(0.f, 0.f, 0.f, 0.f);
         float4 v = *reinterpret_cast<const float4*>(sums + row * RS + col);
         for (int w = 1; w < active; ++w) {
             const float4 o = *reinterpret_cast<const float4*>(sums + (w * BM + row) * RS + col);
             v = make_float4(v.x + o.x, v.y + o.y, v.z + o.z, v.w + o.w);
         }
+        if (based) v = make_float4(b.x + v.x, b.y + v.y, b.z + v.z, b.w + v.w);
         if (g.C16) store_b4(g, m, n, v);
         else if (g.rh) store_r4(g, m, n, v, sq);
         else store_c4(g, m, n, v);
@@ -635,7 +675,8 @@ __global__ __launch_bounds__(64 * W) void mxfp4_gemm_split_kernel(const GemmPara
     }
 }
 
-template <int WN, int WM, int TN, int TM, bool PING, bool DMA_SCALES>
+// OUT, BASE: as store_tile (one kernel each: every epilogue in one is 78 KB of code).
+template <int WN, int WM, int TN, int TM, bool PING, bool DMA_SCALES, int OUT, bool BASE>
 __global__ __launch_bounds__(64 * WN * WM) void mxfp4_gemm_pipe_kernel(const GemmParams g, int64_t gx, int64_t gy) {
     typedef Tile<WN, WM, TN, TM> T;
     __shared__ typename T::Lds lds;
@@ -644,9 +685,7 @@ __global__ __launch_bounds__(64 * WN * WM) void mxfp4_gemm_pipe_kernel(const Gem
     f32x16g acc[TN][TM];
     gemm_tile<WN, WM, TN, TM, PING, DMA_SCALES>(g, lds, tn * T::BN, tm * T::BM, acc);
     uint8_t* const stage = reinterpret_cast<uint8_t*>(&lds);
-    if (g.C16) store_tile<WN, WM, TN, TM, 1>(g, stage, tn * T::BN, tm * T::BM, acc);
-    else if (g.rh) store_tile<WN, WM, TN, TM, 2>(g, stage, tn * T::BN, tm * T::BM, acc);
-    else store_tile<WN, WM, TN, TM, 0>(g, stage, tn * T::BN, tm * T::BM, acc);
+    store_tile<WN, WM, TN, TM, OUT, BASE>(g, stage, tn * T::BN, tm * T::BM, acc);
 }
 
 // The pipelined kernels index a tile's 256 rows with 32-bit byte offsets.
@@ -689,15 +728,25 @@ static void launch_split(const GemmParams& g, hipStream_t st) {
     hipLaunchKernelGGL((mxfp4_gemm_split_kernel<TN, TM, W, D>), dim3((unsigned)(gx * gy)), dim3(64 * W), 0, st, g, gx, gy);
 }
 
+template <int WN, int WM, int TN, int TM, bool PING, bool DMA_SCALES>
+static void launch_pipe_out(const GemmParams& g, hipStream_t st) {
+    typedef Tile<WN, WM, TN, TM> T;
+    const int64_t gx = (g.N + T::BN - 1) / T::BN, gy = (g.M + T::BM - 1) / T::BM;
+    const dim3 grid((unsigned)(gx * gy)), b(64 * T::WAVES);
+#define KQ_PIPE(OUT, BASE) \
+    hipLaunchKernelGGL((mxfp4_gemm_pipe_kernel<WN, WM, TN, TM, PING, DMA_SCALES, OUT, BASE>), grid, b, 0, st, g, gx, gy)
+    if (g.C16) KQ_PIPE(1, false);
+    else if (g.rh) KQ_PIPE(2, true);
+    else if (g.bias || g.accumulate) KQ_PIPE(0, true);
+    else KQ_PIPE(0, false);
+#undef KQ_PIPE
+}
+
 template <int WN, int WM, int TN, int TM, bool PING>
 static void launch_pipe(const GemmParams& g, hipStream_t st) {
-    typedef Tile<WN, WM, TN, TM> T;
-    const int64_t nkb = g.K / 32, gx = (g.N + T::BN - 1) / T::BN, gy = (g.M + T::BM - 1) / T::BM;
-    const dim3 grid((unsigned)(gx * gy)), b(64 * T::WAVES);
-    if (nkb % 4 == 0 && nkb >= 16 && g.scales_aligned)
-        hipLaunchKernelGGL((mxfp4_gemm_pipe_kernel<WN, WM, TN, TM, PING, true>), grid, b, 0, st, g, gx, gy);
-    else
-        hipLaunchKernelGGL((mxfp4_gemm_pipe_kernel<WN, WM, TN, TM, PING, false>), grid, b, 0, st, g, gx, gy);
+    const int64_t nkb = g.K / 32;
+    if (nkb % 4 == 0 && nkb >= 16 && g.scales_aligned) launch_pipe_out<WN, WM, TN, TM, PING, true>(g, st);
+    else launch_pipe_out<WN, WM, TN, TM, PING, false>(g, st);
 }
 
 hipError_t launch_mxfp4_gemm(const GemmParams& g, hipStream_t st) {
