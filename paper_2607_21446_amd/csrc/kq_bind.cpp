@@ -3,8 +3,10 @@
 // either makes the library call and returns its result, or returns None when an
 // argument is not of the plain form checked here (another type, device, layout,
 // size or stream object, a tensor without storage) or the library refuses the call:
-// binding.py then runs its own checks and raises what they say.  A small call's time
-// is the host's: 9.5 us through Python checks and ctypes for a kernel of 2.8.
+// binding.py then runs its own checks and raises what they say.  A call that fails
+// after that (KQ_ERROR_HIP) may have been enqueued, so it is not made again: its
+// error is raised here.  A small call's time is the host's: 9.5 us through Python
+// checks and ctypes for a kernel of 2.8.
 #include <Python.h>
 
 #include <c10/hip/HIPStream.h>
@@ -82,13 +84,33 @@ bool output(PyObject* o, bool want, at::IntArrayRef shape, at::ScalarType dtype,
     return true;
 }
 
+// A call that the HIP runtime reported an error of.
+struct Failed {
+    kq_status status;
+    const char* name;
+};
+
+// True if the call was made, false if the library refused its arguments.
 template <class F>
-bool call(F f) {
+bool call(const char* name, F f) {
     kq_status st;
     Py_BEGIN_ALLOW_THREADS;
     st = f();
     Py_END_ALLOW_THREADS;
+    if (st == KQ_ERROR_HIP) throw Failed{st, name};
     return st == KQ_SUCCESS;
+}
+
+// Sets the binding's KQError.
+PyObject* raise(const Failed& e) {
+    PyObject* const m = PyImport_ImportModule("paper_2607_21446_amd.binding");
+    PyObject* const cls = m ? PyObject_GetAttrString(m, "KQError") : nullptr;
+    PyObject* const err = cls ? PyObject_CallFunction(cls, "iss", (int)e.status, kq_last_error_detail(), e.name) : nullptr;
+    if (err) PyErr_SetObject(cls, err);
+    Py_XDECREF(err);
+    Py_XDECREF(cls);
+    Py_XDECREF(m);
+    return nullptr;
 }
 
 // Everything a function does runs in here: an exception of a tensor call means an
@@ -98,6 +120,8 @@ PyObject* guarded(F f) {
     try {
         PyObject* r = f();
         if (r) return r;
+    } catch (const Failed& e) {
+        return raise(e);
     } catch (...) {
     }
     PyErr_Clear();
@@ -157,13 +181,13 @@ struct Pairs {
 
 // (X, A, B, codes, scales, y, want_y, stream)
 template <class F>
-PyObject* kron(PyObject* const* v, Py_ssize_t n, F f) {
+PyObject* kron(const char* name, PyObject* const* v, Py_ssize_t n, F f) {
     if (n != 8) Py_RETURN_NONE;
     return guarded([&]() -> PyObject* {
         Quant q;
         Pairs p;
         if (!q.parse(v[0], v[3], v[4], v[5], v[6], v[7]) || !p.parse(v[1], v[2], q.X->device())) return nullptr;
-        if (!call([&] {
+        if (!call(name, [&] {
                 return f(q.x(), q.M, q.d, p.A, p.B, (int)p.a, (int)p.b, p.nfac, q.c(), q.s(), q.yp(), q.stream);
             }))
             return nullptr;
@@ -171,8 +195,8 @@ PyObject* kron(PyObject* const* v, Py_ssize_t n, F f) {
     });
 }
 
-PyObject* quantize(PyObject*, PyObject* const* v, Py_ssize_t n) { return kron(v, n, kq_quantize); }
-PyObject* quantize_exact(PyObject*, PyObject* const* v, Py_ssize_t n) { return kron(v, n, kq_quantize_exact); }
+PyObject* quantize(PyObject*, PyObject* const* v, Py_ssize_t n) { return kron("kq_quantize", v, n, kq_quantize); }
+PyObject* quantize_exact(PyObject*, PyObject* const* v, Py_ssize_t n) { return kron("kq_quantize_exact", v, n, kq_quantize_exact); }
 
 // (X, A, B, kpack, codes, scales, y, want_y, stream)
 PyObject* quantize_packed(PyObject*, PyObject* const* v, Py_ssize_t n) {
@@ -183,7 +207,7 @@ PyObject* quantize_packed(PyObject*, PyObject* const* v, Py_ssize_t n) {
         if (!q.parse(v[0], v[4], v[5], v[6], v[7], v[8]) || !p.parse(v[1], v[2], q.X->device())) return nullptr;
         const at::Tensor* k = tensor(v[3]);
         if (!buffer(k, at::kByte, p.nfac * kPackBytes, q.X->device())) return nullptr;
-        if (!call([&] {
+        if (!call("kq_quantize_packed", [&] {
                 return kq_quantize_packed(q.x(), q.M, q.d, p.A, p.B, (int)p.a, (int)p.b, p.nfac, k->data_ptr(), q.c(),
                                           q.s(), q.yp(), q.stream);
             }))
@@ -205,7 +229,7 @@ PyObject* quantize_lu(PyObject*, PyObject* const* v, Py_ssize_t n) {
         if (a < 1 || a > 32 || !dense(lu, at::kFloat) || lu->device() != q.X->device()) return nullptr;
         if (lu->numel() == 0 || lu->numel() % 15) return nullptr;
         if (!output(v[6], want16, {q.M, q.d}, at::kBFloat16, q.M * q.d, q.X->device(), y16)) return nullptr;
-        if (!call([&] {
+        if (!call("kq_quantize_lu", [&] {
                 return kq_quantize_lu(q.x(), q.M, q.d, static_cast<const float*>(lu->data_ptr()), (int)a,
                                       lu->numel() / 15, q.c(), q.s(), q.yp(), static_cast<uint16_t*>(y16.ptr), q.stream);
             }))
@@ -222,7 +246,7 @@ PyObject* smoothquant(PyObject*, PyObject* const* v, Py_ssize_t n) {
         if (!q.parse(v[0], v[2], v[3], v[4], v[5], v[6])) return nullptr;
         const at::Tensor* m = tensor(v[1]);
         if (!buffer(m, at::kFloat, q.d, q.X->device())) return nullptr;
-        if (!call([&] {
+        if (!call("kq_smoothquant_quantize", [&] {
                 return kq_smoothquant_quantize(q.x(), q.M, q.d, static_cast<const float*>(m->data_ptr()), q.c(), q.s(),
                                                q.yp(), q.stream);
             }))
@@ -233,18 +257,18 @@ PyObject* smoothquant(PyObject*, PyObject* const* v, Py_ssize_t n) {
 
 // (X, codes, scales, y, want_y, stream)
 template <class F>
-PyObject* plain(PyObject* const* v, Py_ssize_t n, F f) {
+PyObject* plain(const char* name, PyObject* const* v, Py_ssize_t n, F f) {
     if (n != 6) Py_RETURN_NONE;
     return guarded([&]() -> PyObject* {
         Quant q;
         if (!q.parse(v[0], v[1], v[2], v[3], v[4], v[5])) return nullptr;
-        if (!call([&] { return f(q.x(), q.M, q.d, q.c(), q.s(), q.yp(), q.stream); })) return nullptr;
+        if (!call(name, [&] { return f(q.x(), q.M, q.d, q.c(), q.s(), q.yp(), q.stream); })) return nullptr;
         return q.result(true);
     });
 }
 
-PyObject* hadamard32(PyObject*, PyObject* const* v, Py_ssize_t n) { return plain(v, n, kq_hadamard32_quantize); }
-PyObject* fwht(PyObject*, PyObject* const* v, Py_ssize_t n) { return plain(v, n, kq_fwht_quantize); }
+PyObject* hadamard32(PyObject*, PyObject* const* v, Py_ssize_t n) { return plain("kq_hadamard32_quantize", v, n, kq_hadamard32_quantize); }
+PyObject* fwht(PyObject*, PyObject* const* v, Py_ssize_t n) { return plain("kq_fwht_quantize", v, n, kq_fwht_quantize); }
 
 // (X, codes, scales, stream)
 PyObject* mxfp4(PyObject*, PyObject* const* v, Py_ssize_t n) {
@@ -252,7 +276,7 @@ PyObject* mxfp4(PyObject*, PyObject* const* v, Py_ssize_t n) {
     return guarded([&]() -> PyObject* {
         Quant q;
         if (!q.parse(v[0], v[1], v[2], nullptr, nullptr, v[3])) return nullptr;
-        if (!call([&] { return kq_mxfp4_quantize(q.x(), q.M, q.d, q.c(), q.s(), q.stream); })) return nullptr;
+        if (!call("kq_mxfp4_quantize", [&] { return kq_mxfp4_quantize(q.x(), q.M, q.d, q.c(), q.s(), q.stream); })) return nullptr;
         return q.result(false);
     });
 }
@@ -288,7 +312,7 @@ PyObject* mxfp4_gemm(PyObject*, PyObject* const* v, Py_ssize_t n) {
         const int64_t ldc = (C.given ? *tensor(v[4]) : C.made).stride(0);
         const uint8_t* p[4];
         for (int i = 0; i < 4; ++i) p[i] = static_cast<const uint8_t*>(t[i]->data_ptr());
-        if (!call([&] {
+        if (!call(dtype == at::kFloat ? "kq_mxfp4_gemm" : "kq_mxfp4_gemm_bf16", [&] {
                 return dtype == at::kFloat
                            ? kq_mxfp4_gemm(p[0], p[1], M, p[2], p[3], N, K, static_cast<float*>(C.ptr), ldc, accumulate, st)
                            : kq_mxfp4_gemm_bf16(p[0], p[1], M, p[2], p[3], N, K, static_cast<uint16_t*>(C.ptr), ldc, st);
@@ -318,7 +342,7 @@ PyObject* calib_step(PyObject*, PyObject* const* v, Py_ssize_t n) {
         if (a < 1 || a > 32 || !stream_of(v[10], &st) || !output(v[8], true, {nfac, 5, 3}, at::kFloat, nfac * 15, dev, grad) ||
             !output(v[9], true, {4}, at::kDouble, 4, dev, losses))
             return nullptr;
-        if (!call([&] {
+        if (!call("kq_calib_step", [&] {
                 return kq_calib_step(static_cast<const uint16_t*>(X->data_ptr()), R, d,
                                      static_cast<const uint16_t*>(W->data_ptr()), o, static_cast<const float*>(Y->data_ptr()),
                                      static_cast<float*>(lu->data_ptr()), (int)a, nfac,
