@@ -25,7 +25,9 @@ struct CalibPlan {
     size_t rh = 0, rl = 0;                // the residual's two bf16 terms [Rp, op]
     size_t gpa = 0, gpw = 0, sqa = 0, sqw = 0, sr = 0;
     size_t grad = 0, am = 0, av = 0, lam = 0;
-    size_t total = 0;
+    size_t used = 0;                      // bytes laid out
+    size_t told = 0;                      // the size that kq_calib_step_noalloc goes by
+    size_t total = 0;                     // what a caller's workspace holds: the larger of the two
 };
 
 CalibPlan calib_plan(int64_t R, int64_t o, int64_t d, int a, int64_t nfac);

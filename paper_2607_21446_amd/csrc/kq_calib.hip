@@ -11,22 +11,17 @@
 // is held fixed, and an element clipped at +-6 * scale passes none.  The
 // forward products come from the quantizers and the W4A4 GEMM of the
 // library; this file holds the backward pass:
-//   * calib_gemm_kernel: bf16 matrix-core GEMM (v_mfma_f32_32x32x16_bf16,
-//     128 x 256 workgroup tile for the backward products, 128 x 128 for the
-//     reference product, 32-deep K stages loaded straight into three LDS
-//     buffers, two in flight) on operands stored K-contiguous.  The dequantized MXFP4 operands are exact
-//     in bf16; the fp32 residual enters as two bf16 terms (hi = bf16(r),
-//     lo = bf16(r - hi), |r - hi - lo| <= 2^-17 |r|), so every product term
-//     is exact and sums run in fp32.  Two epilogues: the reference product
-//     X W^T, and the fused gradient epilogue that turns a tile of dL/dQ into
-//     dL/d(transformed operand) (mask, regulariser term) and contracts it at
-//     once with the untransformed operand into 32 x 32 per-block sums
-//     sum_rows left^T g (fp32 matrix cores), so the R x d gradient never
-//     reaches memory;
-//   * residual_prep_kernel / decode_t_kernel: the residual as its two bf16
-//     terms (in its own layout and transposed, plus its sum of squares) and
-//     the dequantized operands laid out K-contiguous for the products;
-//   * gram_reduce_kernel: fixed-order sum of the per-workgroup block sums;
+//   * calib_backward_kernel, calib_reference_kernel: bf16 matrix-core products
+//     (v_mfma_f32_32x32x16_bf16) in 256 x 256 or 128 x 128 workgroup tiles, 32-deep
+//     K stages loaded straight into three LDS buffers, two in flight.  The
+//     dequantized MXFP4 operands are exact in bf16; the fp32 residual enters as two
+//     bf16 terms (hi = bf16(r), lo = bf16(r - hi), |r - hi - lo| <= 2^-17 |r|; the
+//     W4A4 GEMM writes it so), so every product term is exact and sums run in fp32.
+//     Operands whose K index is not the contiguous one are read from LDS transposed.
+//     The gradient epilogue turns a tile of dL/dQ into its per-block sums
+//     sum_rows left^T (P m) at once, so the R x d gradient never reaches memory;
+//   * gram_reduce_kernel: fixed-order sum of the per-workgroup block sums and of the
+//     quantizer's sums over clipped elements;
 //   * lu_grad_kernel: chain rule through T^-T and the Kronecker product to the
 //     2 x 2 factors and their (a, b, c), the losses, and the Adam update.
 #include <hip/hip_runtime.h>
@@ -463,10 +458,10 @@ __global__ __launch_bounds__(64 * WM * WN) void calib_reference_kernel(const Opn
 
 // S = c1 sum over the slots of partial - c2 sum over the quantizer's strips of dpart,
 // summed in fp64 and a fixed order (16 threads per four elements, each every 16th
-// term), in place: partial[0][j][e] the nearest fp32, partial[1][j][e] that of the rest.
+// term), in place: partial[0][j][e] the nearest fp32, dpart[0][j][e] that of the rest.
 struct ReduceSide {
-    float* partial;      // [slots (room for 2 at least), nb, 1024]
-    const float* dpart;  // [strips, nb, 1024]
+    float* partial;      // [slots, nb, 1024]
+    float* dpart;        // [strips, nb, 1024]
     int64_t slots, strips;
     double c1, c2_unit;  // c2 = lambda * c2_unit
 };
@@ -503,10 +498,10 @@ __global__ __launch_bounds__(256) void gram_reduce_kernel(const ReduceSide s0, c
         double t = 0.0;
 #pragma unroll
         for (int k = 0; k < 16; ++k) t += red[k][threadIdx.x >> 2][threadIdx.x & 3];
-        float* const dst = s.partial + j * 1024 + 64 * blockIdx.y + threadIdx.x;
+        const int64_t at = j * 1024 + 64 * blockIdx.y + threadIdx.x;
         const float hi = (float)t;
-        dst[0] = hi;
-        dst[nb * 1024] = (float)(t - (double)hi);
+        s.partial[at] = hi;
+        s.dpart[at] = (float)(t - (double)hi);
     }
 }
 
@@ -532,8 +527,8 @@ __device__ __forceinline__ double block_sum256(double v, double* red) {
 
 struct LuGradArgs {
     const float* lu;
-    const float* ga;   // [2, nb, 32, 32]  dL/dT of every block from the activation side, in two terms
-    const float* gw;   // [2, nb, 32, 32]  dL/dU, U = T^-T, from the weight side
+    const float *ga, *ga_lo;  // [nb, 32, 32]  dL/dT of every block from the activation side, in two terms
+    const float *gw, *gw_lo;  // [nb, 32, 32]  dL/dU, U = T^-T, from the weight side
     int64_t nb, nfac;  // nfac = nb, or 1: the blocks' sums add up
     float* grad;       // [nfac, 15]
     float* lu_out;
@@ -594,8 +589,8 @@ __global__ __launch_bounds__(256) void lu_grad_kernel(const LuGradArgs p) {
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 const int64_t e = j * 1024 + t + 256 * i;
-                a4[i] += double(p.ga[e]) + double(p.ga[p.nb * 1024 + e]);
-                w4[i] += double(p.gw[e]) + double(p.gw[p.nb * 1024 + e]);
+                a4[i] += double(p.ga[e]) + double(p.ga_lo[e]);
+                w4[i] += double(p.gw[e]) + double(p.gw_lo[e]);
             }
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
@@ -770,8 +765,9 @@ static double backward_cost(const SidePlan& act, const SidePlan& wgt, bool big) 
 }
 
 // The least workspace a caller is told of: 6.6 R d + 12 R o + 6.6 o d bytes and the
-// partial sums of 128-row tiles, of which the step now uses less.  Kept, so that
-// the sizes that the fixed scratch of kq_calib_step_noalloc holds stay the same.
+// partial sums of 128-row tiles, of which the step now uses less, but for a few rows
+// of many columns (by up to a third: two block sums of 128 d bytes a side, where
+// this has one).  It also says which sizes kq_calib_step_noalloc takes.
 static size_t told_workspace(int64_t R, int64_t o, int64_t d, int a, int64_t nfac) {
     const int64_t nb = d / 32, ntn = cdiv(d, 256), act_mt = cdiv(R, 128), w_mt = cdiv(o, 128);
     const int64_t Rp = cdiv(R, BK) * BK, op = cdiv(o, BK) * BK, stages = Rp / BK;
@@ -799,7 +795,7 @@ CalibPlan calib_plan(int64_t R, int64_t o, int64_t d, int a, int64_t nfac) {
     pl.nfac = nfac;
     pl.Rp = cdiv(std::max<int64_t>(R, 1), BK) * BK;
     pl.op = cdiv(o, BK) * BK;
-    pl.nsum = std::max<int64_t>(256, cdiv(pl.Rp, 128) * cdiv(pl.op, 128));  // one per workgroup of the GEMM
+    pl.nsum = std::max<int64_t>(256, cdiv(pl.Rp, 64) * cdiv(pl.op, 64));  // one per workgroup of the GEMM, any tile
     size_t off = 0;
     auto take = [&](size_t bytes) {
         const size_t at = off;
@@ -858,8 +854,10 @@ CalibPlan calib_plan(int64_t R, int64_t o, int64_t d, int a, int64_t nfac) {
     }
     pl.act_ks = cdiv(pl.op, pl.act_kchunk);
     pl.w_ks = cdiv(pl.Rp, pl.w_kchunk);
-    pl.gpa = take(size_t(std::max<int64_t>(2, pl.act_mt * pl.act_ks)) * slot);
-    pl.gpw = take(size_t(std::max<int64_t>(2, pl.w_mt * pl.w_ks)) * slot);
+    pl.gpa = take(size_t(pl.act_mt * pl.act_ks) * slot);
+    pl.gpw = take(size_t(pl.w_mt * pl.w_ks) * slot);
+    pl.used = off;
+    pl.told = told;
     pl.total = std::max(off, told);
     return pl;
 }
@@ -908,15 +906,17 @@ hipError_t launch_calib_backward(const CalibPlan& pl, const CalibStepArgs& s, in
     if (pl.big) calib_backward_kernel<4, 2, 2, 4, true><<<works, 512, 0, st>>>(b);
     else calib_backward_kernel<2, 2, 2, 2, false><<<works, 256, 0, st>>>(b);
     const double c1 = 2.0 / (double(R) * double(o));
-    const ReduceSide ra{b.act.partial, reinterpret_cast<const float*>(ws + pl.dA), pl.act_mt * pl.act_ks, pl.strips_a,
+    const ReduceSide ra{b.act.partial, reinterpret_cast<float*>(ws + pl.dA), pl.act_mt * pl.act_ks, pl.strips_a,
                         c1, 2.0 / (double(R) * double(d))};
-    const ReduceSide rw{b.wgt.partial, reinterpret_cast<const float*>(ws + pl.dW), pl.w_mt * pl.w_ks, pl.strips_w,
+    const ReduceSide rw{b.wgt.partial, reinterpret_cast<float*>(ws + pl.dW), pl.w_mt * pl.w_ks, pl.strips_w,
                         c1, 2.0 / (double(o) * double(d))};
     gram_reduce_kernel<<<dim3(unsigned(pl.nb), 16, 2), 256, 0, st>>>(ra, rw, pl.nb, s.lambdas);
     LuGradArgs la{};
     la.lu = s.lu;
     la.ga = ra.partial;
+    la.ga_lo = ra.dpart;
     la.gw = rw.partial;
+    la.gw_lo = rw.dpart;
     la.nb = pl.nb;
     la.nfac = pl.nfac;
     la.grad = s.grad;

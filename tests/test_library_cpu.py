@@ -319,6 +319,16 @@ def test_calib_step_noalloc_refuses_before_any_hip_call():
     assert kq.CALIB_NOALLOC_MAX_BYTES == 64 << 20
 
 
+@pytest.mark.skipif(torch.cuda.is_available(), reason="would make the call with pointers that are none")
+@pytest.mark.parametrize("R,o,d,nfac", [(1, 17, 143808, 1), (2, 64, 88832, 1), (6, 10, 146080, 1), (1, 22, 88224, 2757)])
+def test_calib_step_noalloc_takes_a_few_rows_of_many_columns(R, o, d, nfac):
+    """The block sums of these are most of the workspace; they fit the scratch
+    (without a GPU the call gets as far as its first HIP call)."""
+    st = kq.lib().kq_calib_step_noalloc(FAKE, R, d, FAKE, o, FAKE, FAKE, 4, nfac, FAKE, FAKE, FAKE, None, None, 0, 0.0,
+                                        None)
+    assert st not in (0, INVALID)
+
+
 def test_native_marshalling_leaves_other_arguments_to_python():
     """The binding's native part takes plain device tensors only: everything
     else comes back as None and meets the checks in Python."""
