@@ -329,7 +329,6 @@ static kq::GemmParams gemm_params(const uint8_t* a_codes, const uint8_t* a_scale
     g.ldc_out = ldc;
     g.accumulate = accumulate;
     g.bias = bias;
-    g.vec_ok = aligned(C, 16) && ldc % 4 == 0 && (!bias || aligned(bias, 16));
     g.scales_aligned = aligned(a_scales, 4) && aligned(b_scales, 4);
     return g;
 }
@@ -366,7 +365,6 @@ kq_status kq_mxfp4_gemm_bf16(const uint8_t* a_codes, const uint8_t* a_scales, in
     if (st != KQ_SUCCESS || M == 0 || N == 0) return st;
     kq::GemmParams g = gemm_params(a_codes, a_scales, M, b_codes, b_scales, N, K, nullptr, ldc, 0, nullptr);
     g.C16 = C;
-    g.vec_ok = aligned(C, 16) && ldc % 8 == 0;
     return from_hip(kq::launch_mxfp4_gemm(g, (hipStream_t)stream), "kq_mxfp4_gemm_bf16");
 }
 
@@ -540,7 +538,6 @@ static kq_status calib_step_impl(const kq::CalibPlan& pl, const uint16_t* X, con
     // residual Q(X T) Q(W T^-T)^T - X W^T on the W4A4 GEMM with Yneg as its bias, as two bf16 terms
     kq::GemmParams g =
         gemm_params(ws + pl.cA, ws + pl.sA, pl.R, ws + pl.cW, ws + pl.sW, pl.o, pl.d, nullptr, pl.o, 0, Yneg);
-    g.vec_ok = aligned(Yneg, 16) && pl.o % 4 == 0;
     g.rh = reinterpret_cast<uint16_t*>(ws + pl.rh);
     g.rl = reinterpret_cast<uint16_t*>(ws + pl.rl);
     g.ldr = pl.op;

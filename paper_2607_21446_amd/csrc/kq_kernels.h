@@ -57,7 +57,7 @@ struct GemmParams {
     float* C;                 // [M, ldc_out]
     int64_t ldc_out;
     int accumulate;           // 1: C += product, 0: C = product
-    const float* bias = nullptr;  // if set: C = bias + product (bias [M, ldc_out], vec rule as C)
+    const float* bias = nullptr;  // if set: C = bias + product (bias [M, ldc_out])
     uint16_t* C16 = nullptr;      // if set: bf16 output [M, ldc_out] instead of C (no bias, no accumulate)
     // if rh is set: no C; v = bias + product goes out as the bf16 terms of v, [rows_pad, ldr]
     // (zero beyond M and N; both less than 32 past them), and every workgroup's sum of v^2
@@ -65,7 +65,6 @@ struct GemmParams {
     uint16_t* rl = nullptr;
     int64_t ldr = 0, rows_pad = 0;
     double* sq_part = nullptr;    // [mxfp4_gemm_workgroups]
-    int vec_ok;               // C 16-byte aligned and ldc_out a multiple of 4 (C16: 16-byte and 8)
     int scales_aligned;       // both scale arrays 4-byte aligned
 };
 

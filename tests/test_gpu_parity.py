@@ -663,6 +663,23 @@ def test_mxfp4_gemm_k_tails(M, N, K, off):
     assert np.array_equal(c16, oracle.f32_to_bf16(C))
 
 
+@pytest.mark.parametrize("M,N", [(1, 1), (33, 67), (250, 1251), (700, 1301), (1025, 1153), (2950, 3101)])
+@pytest.mark.parametrize("off", [1, 3])
+def test_mxfp4_gemm_c_at_element_alignment(M, N, off):
+    """C, 32- and 16-bit, that starts at an odd element and has rows of odd
+    length, on every tile of the dispatch: what the aligned call gives, and
+    nothing written before or after it."""
+    K = 160
+    ops = [torch.from_numpy(x).cuda() for x in (*_rand_mx(M, K, seed=M), *_rand_mx(N, K, seed=N + 1))]
+    for dtype, accumulate in ((torch.float32, False), (torch.float32, True), (torch.bfloat16, False)):
+        want = kq.mxfp4_gemm(*ops, out_dtype=dtype)
+        buf = torch.ones(M * N + off + 8, dtype=dtype, device="cuda")
+        C = buf[off:off + M * N].view(M, N)
+        kq.mxfp4_gemm(*ops, C=C, accumulate=accumulate)
+        assert torch.equal(C, want + 1.0 if accumulate else want), (dtype, accumulate)
+        assert bool((buf[:off] == 1).all()) and bool((buf[off + M * N:] == 1).all()), (dtype, accumulate)
+
+
 @pytest.mark.parametrize("M,N,K", [(77, 200, 2240), (33, 70, 1120), (300, 257, 3072), (5, 3, 128), (3000, 2200, 384),
                                    (2500, 2470, 1664)])
 def test_mxfp4_gemm_bf16_output(M, N, K):
