@@ -851,7 +851,8 @@ __device__ __forceinline__ void unit_compute(const Params& p, uint4* lds, int64_
                                              uint32_t bstride, const uint4 (&v)[4], const KSlices& ks, bool zero_ok,
                                              EdgeTest et, const float* Af, const float* Bf, TileSink ts = {},
                                              CalSums* cal = nullptr) {
-    const int lane = threadIdx.x & 63;
+    int lane = threadIdx.x & 63;
+    if (CAL) asm volatile("" : "+v"(lane));  // addresses are made where they are used, not kept through the strip
     const int h = lane >> 5, jl = lane & 31;
     const int nvalid = FULL ? 64 : nvalid_rt;
     // chunk 64c + lane of the unit (block (64c + lane) / 4, chunk (64c + lane) % 4
@@ -1320,18 +1321,18 @@ __device__ __forceinline__ void kron_tile(const Params& p, int rg, int64_t wg, i
     // load c of a step: row 8 w + 2 c + lane / 32, 16-byte chunk lane % 32 of
     // its 512 bytes; a wave-uniform base per step and 32-bit lane offsets
     // (64 rows of X span less than 4 GiB: d < 2^25, checked by the launcher)
-    const int q = lane & 31;
-    const int qb = min(q >> 2, ncols - 1);
     const uint32_t rowbytes = (uint32_t)(p.nb * 64);
-    const uint32_t qoff = (uint32_t)(qb * 64 + (q & 3) * 16);
     const uint8_t* const xstrip = reinterpret_cast<const uint8_t*>(p.X) + kTileCols * jt * 64;
     uint4 v[4];
     auto issue = [&](int64_t row0) {
+        int li = threadIdx.x & 63;  // CAL: addresses are made where they are used
+        if (CAL) asm volatile("" : "+v"(li));
+        const uint32_t qoff = (uint32_t)(min((li & 31) >> 2, ncols - 1) * 64 + (li & 3) * 16);
         const int nrows = (int)min<int64_t>(64, p.M - row0);
         const uint8_t* const xs = xstrip + row0 * p.nb * 64;
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
-            const uint32_t r = (uint32_t)min(8 * w + 2 * c + (lane >> 5), nrows - 1);
+            const uint32_t r = (uint32_t)min(8 * w + 2 * c + (li >> 5), nrows - 1);
             v[c] = load_nt(reinterpret_cast<const uint4*>(xs + (r * rowbytes + qoff)));
         }
     };
@@ -1396,17 +1397,20 @@ __device__ __forceinline__ void kron_tile(const Params& p, int rg, int64_t wg, i
     for (int it = 0; it < nsteps; ++it) {
         const int64_t row0 = (rb0 + it) * 64;
         const int nrows = (int)min<int64_t>(64, p.M - row0);
+        int ls = threadIdx.x & 63;
+        if (CAL) asm volatile("" : "+v"(ls));
+        const int q = ls & 31, lh = ls >> 5;
         // stage: chunk (q & 3) of column block q / 4 goes to that wave's tile
         if (nrows == 64 && ncols == kTileCols) {
             // a full step (the common case, uniform): every chunk as loaded
 #pragma unroll
             for (int c = 0; c < 4; ++c)
-                lds_x[kTileSlots * (q >> 2) + lds_slot(8 * w + 2 * c + (lane >> 5), q & 3)] = v[c];
+                lds_x[kTileSlots * (q >> 2) + lds_slot(8 * w + 2 * c + lh, q & 3)] = v[c];
         } else {
             // rows past M and column blocks past nb as zeros, branch-free
 #pragma unroll
             for (int c = 0; c < 4; ++c) {
-                const int r = 8 * w + 2 * c + (lane >> 5);
+                const int r = 8 * w + 2 * c + lh;
                 const uint32_t m = (r < nrows && (q >> 2) < ncols) ? ~0u : 0u;
                 lds_x[kTileSlots * (q >> 2) + lds_slot(r, q & 3)] =
                     make_uint4(v[c].x & m, v[c].y & m, v[c].z & m, v[c].w & m);
@@ -1451,12 +1455,21 @@ __device__ __forceinline__ void kron_tile(const Params& p, int rg, int64_t wg, i
     }
     if (CAL) {
         if (active) {
+            int le = threadIdx.x & 63;
+            asm volatile("" : "+v"(le));
             float* const dst = p.dpart + ((g / ntc) * p.nb + jc) * 1024;
 #pragma unroll
-            for (int e = 0; e < 16; ++e) dst[(8 * (e / 4) + 4 * (lane >> 5) + (e % 4)) * 32 + (lane & 31)] = cal.d[e];
+            for (int e = 0; e < 16; ++e) dst[(8 * (e / 4) + 4 * (le >> 5) + (e % 4)) * 32 + (le & 31)] = cal.d[e];
         }
+        int le = threadIdx.x & 63;
+        asm volatile("" : "+v"(le));
 #pragma unroll
-        for (int off = 32; off > 0; off >>= 1) cal.sq += __shfl_xor(cal.sq, off);
+        for (int off = 32; off > 0; off >>= 1) {  // (__shfl_xor keeps its six addresses from before the strip)
+            const uint64_t b = __builtin_bit_cast(uint64_t, cal.sq);
+            const uint32_t lo = (uint32_t)__builtin_amdgcn_ds_bpermute((le ^ off) << 2, (int)(uint32_t)b);
+            const uint32_t hi = (uint32_t)__builtin_amdgcn_ds_bpermute((le ^ off) << 2, (int)(uint32_t)(b >> 32));
+            cal.sq += __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+        }
         if (lane == 0) sq_lds[w] = cal.sq;
         __syncthreads();
         if (threadIdx.x == 0) {
@@ -1480,8 +1493,12 @@ struct CalibQuant {
     uint32_t nx;
 };
 
+// At most 128 registers, so that two workgroups share a CU (a = 1: its LDS holds one): one's
+// loads and stores run beside the other's arithmetic.  At 150 registers only one fitted;
+// the step, us: 4096 x 1152 x 4608 290 and 284, 4608 x 3072 x 3072 401 and 390,
+// 18432 x 3072 x 3072 1326 and 1309.
 template <int NA, int NB>
-__global__ __launch_bounds__(64 * kTileCols) void kron_tile_calib_kernel(const CalibQuant c) {
+__global__ __launch_bounds__(64 * kTileCols, NA == 1 ? 2 : 4) void kron_tile_calib_kernel(const CalibQuant c) {
     const bool w = blockIdx.x >= c.nx;
     const Params p = w ? c.p[1] : c.p[0];
     kron_tile<NA, NB, true, false, false, false, true>(p, w ? c.rg[1] : c.rg[0], w ? blockIdx.x - c.nx : blockIdx.x,
@@ -1860,9 +1877,9 @@ static int tile_rows(const Params& p) {
     return rg < 1 ? 1 : rg > kTileMaxSteps ? kTileMaxSteps : (int)rg;
 }
 
-// The same for the calibration step's kernel, one workgroup of which fits a CU: the
-// steps that fill the rounds of 256 best, a strip's factors, block sums and first
-// loads costing about 0.7 of a step.
+// The same for the calibration step's kernel: the steps that fill the rounds of 256 best
+// (rounds of 512, two workgroups a CU: no faster), a strip's factors, block sums and
+// first loads costing about 0.7 of a step.
 static int calib_tile_rows(int64_t M, int64_t nb) {
     const int64_t nrb = (M + 63) / 64, ntc = (nb + kTileCols - 1) / kTileCols;
     auto cost = [&](int64_t rg) { return (double)(((nrb + rg - 1) / rg * ntc + 255) / 256) * ((double)rg + 0.7); };
