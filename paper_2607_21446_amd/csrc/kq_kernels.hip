@@ -53,6 +53,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
 #include <type_traits>
 
 #include "kq_kernels.h"
@@ -1714,14 +1715,7 @@ __global__ __launch_bounds__(kThreads) void e2m1_kernel(const float* __restrict_
 // FWHT baseline of Sec. 4.4 (Table 2), then MXFP4 of every 32-element block.
 // Same butterflies in the same order as the fixed-order definition -- stride
 // h = 1, 2, ..., d/2, then one multiply by the fp32 nearest to 1/sqrt(d) -- so
-// the outputs are bit-identical to it.  A thread owns 32 elements of its row
-// at a time.  Pass q applies the strides 2^(5q) .. 2^(5q+k-1) (k <= 5 index
-// bits) in registers; between passes the row goes through LDS (fp32, one pad
-// float per 32) from one element assignment to the next:
-//   element of slot j in pass (lo, k) =
-//     deposit(v, other bits) | (j mod 2^k) << lo,   v = tl | (j >> k) << (LOG2D - 5),
-// "other bits" being the index bits outside [lo, lo + k) in increasing order,
-// tl the thread's index within its row.  Pass 0 is the thread's own block.
+// the outputs are bit-identical to it.
 // Measurement aid: one lane stores the device's constant-rate real-time
 // counter (100 MHz), so that a stream of launches can be timed between two
 // of these from inside a captured graph.
@@ -1734,6 +1728,10 @@ hipError_t launch_timestamp(uint64_t* dst, hipStream_t st) {
     return hipGetLastError();
 }
 
+// Element of register j where k <= 5 index bits from lo are register bits:
+//   deposit(v, other bits) | (j mod 2^k) << lo,   v = tl | (j >> k) << (LOG2D - 5),
+// "other bits" being the index bits outside [lo, lo + k) in increasing order, tl the
+// thread's index within its row.
 template <int LOG2D>
 __device__ __forceinline__ int fwht_index(int lo, int k, int j, int tl) {
     const int v = tl | ((j >> k) << (LOG2D - 5));
@@ -1742,7 +1740,7 @@ __device__ __forceinline__ int fwht_index(int lo, int k, int j, int tl) {
 }
 
 template <int LOG2D>
-__global__ __launch_bounds__(LOG2D == 14 ? 512 : 256) void fwht_kernel(const Params p) {
+__global__ __launch_bounds__(256) void fwht_kernel(const Params p) {
     constexpr int D = 1 << LOG2D;
     constexpr int TPR = D / 32;                   // threads per row
     constexpr int T = TPR < 256 ? 256 : TPR;      // threads per workgroup
@@ -1815,6 +1813,190 @@ __global__ __launch_bounds__(LOG2D == 14 ? 512 : 256) void fwht_kernel(const Par
         float4* dst = reinterpret_cast<float4*>(p.y + blk * 32);
 #pragma unroll
         for (int m = 0; m < 8; ++m) dst[m] = make_float4(y[4 * m], y[4 * m + 1], y[4 * m + 2], y[4 * m + 3]);
+    }
+}
+
+// Bit RB of the register index and bit LB (4 or 5) of the lane change places.
+template <int LB, int RB>
+__device__ __forceinline__ void fwht_swap(float (&u)[32]) {
+    typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+#pragma unroll
+    for (int j = 0; j < 32; ++j) {
+        if (j & (1 << RB)) continue;
+        const uint32_t a = __float_as_uint(u[j]), b = __float_as_uint(u[j | (1 << RB)]);
+        u32x2 v;
+        if (LB == 4) v = __builtin_bit_cast(u32x2, __builtin_amdgcn_permlane16_swap(a, b, false, false));
+        else v = __builtin_bit_cast(u32x2, __builtin_amdgcn_permlane32_swap(a, b, false, false));
+        u[j] = __uint_as_float(v.x);
+        u[j | (1 << RB)] = __uint_as_float(v.y);
+    }
+}
+
+// The butterflies of bit RB of the register index.
+template <int RB>
+__device__ __forceinline__ void fwht_stage(float (&u)[32]) {
+    constexpr int h = 1 << RB;
+#pragma unroll
+    for (int j = 0; j < 32; ++j) {
+        if (j & h) continue;
+        const float s0 = u[j] + u[j + h];
+        const float s1 = u[j] - u[j + h];
+        u[j] = s0;
+        u[j + h] = s1;
+    }
+}
+
+template <int K>
+__device__ __forceinline__ void fwht_stages(float (&u)[32]) {
+    if (K > 0) fwht_stage<0>(u);
+    if (K > 1) fwht_stage<1>(u);
+    if (K > 2) fwht_stage<2>(u);
+    if (K > 3) fwht_stage<3>(u);
+    if (K > 4) fwht_stage<4>(u);
+}
+
+// Rows of 2048 to 16384 elements.  A thread holds 32 elements: five of the index bits
+// are register bits at a time, and up to two more are lane bits 4 and 5 that change
+// places with register bits (permlane swaps, one instruction per two elements), so a
+// row takes one trip through LDS to the second part of its bits and one back:
+//   n = 11, 12: 5 | 5 + 1, 2 swaps;  13, 14: 5 + 1, 2 swaps | 5 + 2 swaps.
+// A wave's first writes and the writes back stay within the elements that it holds, so
+// a row of 2048 elements (one wave) needs no barrier, a longer one two.  Workgroups stay
+// and load their next rows while they transform (the four that a CU's LDS holds load and
+// compute at about the same time, so one's loads hid little of another's arithmetic),
+// 16 bytes a lane and through LDS, where 64 bytes a lane touch four times the cache lines.
+//
+// Bound by the vector ALUs (n + 5 operations an element) and LDS beside memory.  By
+// fwht_kernel (three trips, six barriers) and here, us: 4096 x 2048 9.9, 8.2; 4096 x 4096
+// 14.8, 12.7; 18432 x 4096 54.4, 46.1; 4096 x 8192 24.1, 23.6; 4096 x 16384 53.3, 46.8.
+// Up to 1024 elements (two passes there as well) fwht_kernel is the faster: 4096 x 1024
+// 4.38, 4.57 in this form.
+template <int LOG2D>
+__global__ __launch_bounds__(LOG2D == 14 ? 512 : 256) void fwht_long_kernel(const Params p, int64_t groups) {
+    constexpr int D = 1 << LOG2D;
+    constexpr int TPR = D / 32;                   // threads per row
+    constexpr int T = TPR < 256 ? 256 : TPR;      // threads per workgroup
+    constexpr int R = T / TPR;                    // rows per workgroup
+    constexpr int SA = LOG2D > 12 ? LOG2D - 12 : 0, LO = 5 + SA;  // swaps and bits of the first part
+    constexpr int SB = LOG2D - LO - 5;            // swaps of the second, 1 or 2
+    static_assert(SB == 1 || SB == 2, "11 to 14 bits");
+    // element i of a row in LDS: bank conflicts of at most two lanes, once, at n >= 13
+    auto pad = [](int i) { return i + (i >> 5) + (SA ? i >> LO : 0) + 16 * (i >> (LO + 5)); };
+    constexpr int RS = D + D / 32 + (SA ? D >> LO : 0) + 16 * (D >> (LO + 5));
+    __shared__ __align__(16) float buf[R * RS];
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+    const int r = t / TPR, tl = t % TPR;
+    float* const rb = buf + r * RS;
+    uint4 v[4];
+    // Of row group g: the wave's 64 blocks of 32 elements are contiguous in X, 16 bytes a lane
+    auto fetch = [&](int64_t g) {
+        const int64_t first = g * T + 64 * wave;
+        const uint4* const src = reinterpret_cast<const uint4*>(p.X) + 4 * first;
+        const int64_t left = p.M * TPR - first;  // blocks from the wave's first to the end
+#pragma unroll
+        for (int m = 0; m < 4; ++m)
+            v[m] = 16 * m + (lane >> 2) < left ? src[64 * m + lane] : make_uint4(0u, 0u, 0u, 0u);
+    };
+    auto row_sync = [] {
+        if (TPR > 64) {  // (of LDS only: the next group's loads stay in flight)
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+            __builtin_amdgcn_s_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+        } else {
+            wave_lds_sync();
+        }
+    };
+    const int l4 = (lane >> 4) & 1, l5 = lane >> 5, wr = tl >> 6;  // wr: wave of the row
+    // through LDS (within the part of buf that the wave's own elements take) to one block a lane
+    uint4* const raw =
+        reinterpret_cast<uint4*>(buf + (64 * wave / TPR) * RS + (TPR > 64 ? pad(32 * (64 * wave % TPR)) : 0));
+    auto stage = [&] {
+        wave_lds_sync();
+#pragma unroll
+        for (int m = 0; m < 4; ++m) {
+            const int b = 16 * m + (lane >> 2);
+            raw[4 * b + ((lane & 3) ^ ((b >> 2) & 3))] = v[m];
+        }
+        wave_lds_sync();
+    };
+    fetch(blockIdx.x);
+    stage();
+    for (int64_t g = blockIdx.x; g < groups; g += gridDim.x) {
+        float u[32];
+        {
+            // this lane's block: lane bits 4 and 5 are the bits to be swapped
+            const int b = SA == 0 ? lane : SA == 1 ? ((lane >> 4) & 1) | ((lane & 15) << 1) | (lane & 32)
+                                                   : (lane >> 4) | ((lane & 15) << 2);
+#pragma unroll
+            for (int m = 0; m < 4; ++m) unpack8(raw[4 * b + (m ^ ((b >> 2) & 3))], u + 8 * m);
+            wave_lds_sync();
+        }
+        if (g + gridDim.x < groups) fetch(g + gridDim.x);
+        fwht_stages<5>(u);
+        if (SA >= 1) {
+            fwht_swap<4, 4>(u);
+            fwht_stage<4>(u);
+        }
+        if (SA >= 2) {
+            fwht_swap<5, 3>(u);
+            fwht_stage<3>(u);
+        }
+        {
+            const int e = SA == 0 ? 32 * tl
+                                  : (l4 << 4) | ((lane & 15) << LO) | (wr << 11) | (SA == 2 ? l5 << 3 : l5 << (LO + 4));
+            float* const at = rb + pad(e);
+#pragma unroll
+            for (int j = 0; j < 32; ++j)
+                at[pad(SA == 0 ? j : (j & 7) | (((j >> 3) & 1) << (SA == 2 ? 6 : 3)) | ((j >> 4) << 5))] = u[j];
+        }
+        row_sync();
+        {
+            // lanes 0..15 along the row, lane bit 4 (and 5) the top bits
+            const int e = (lane & 15) | (l4 << (LO + 5)) | (SB == 2 ? (l5 << (LO + 6)) | (wr << 4) : l5 << 4);
+            const float* const from = rb + pad(e);
+#pragma unroll
+            for (int j = 0; j < 32; ++j) u[j] = from[pad(j << LO)];
+            fwht_stages<5>(u);
+            fwht_swap<4, 4>(u);
+            fwht_stage<4>(u);
+            if (SB == 2) {
+                fwht_swap<5, 3>(u);
+                fwht_stage<3>(u);
+            }
+            const int w = (lane & 15) | (l4 << (LO + 4)) | (SB == 2 ? (l5 << (LO + 3)) | (wr << 4) : l5 << 4);
+            float* const to = rb + pad(w);
+            wave_lds_sync();
+#pragma unroll
+            for (int j = 0; j < 32; ++j)
+                to[pad(((j & 7) << LO) | (((j >> 3) & 1) << (SB == 2 ? LO + 6 : LO + 3)) | ((j >> 4) << (LO + 5)))] = u[j];
+        }
+        row_sync();
+        const float* const own = rb + pad(32 * tl);
+#pragma unroll
+        for (int j = 0; j < 32; ++j) u[j] = own[j];
+        // before this group's stores, which the wait for the loads would wait for too (in the
+        // last round once more what was there)
+        stage();
+        // fp32 nearest to 1/sqrt(d): 2^(-n/2) for even n, fp32(1/sqrt2) * 2^(-(n-1)/2) for odd n
+        const float inv_sqrt_d = (LOG2D & 1) ? __uint_as_float(0x3F3504F3u - ((uint32_t)(LOG2D - 1) / 2u << 23))
+                                             : __uint_as_float((uint32_t)(127 - LOG2D / 2) << 23);
+        float y[32];
+#pragma unroll
+        for (int j = 0; j < 32; ++j) y[j] = u[j] * inv_sqrt_d;
+        const int64_t blk = g * T + t;
+        if (blk < p.M * TPR) {
+            uint32_t w[4];
+            const uint32_t sbyte = encode32(y, w);
+            if (p.codes) {
+                *reinterpret_cast<uint4*>(p.codes + blk * 16) = make_uint4(w[0], w[1], w[2], w[3]);
+                p.scales[blk] = (uint8_t)sbyte;
+            }
+            if (p.y) {
+                float4* dst = reinterpret_cast<float4*>(p.y + blk * 32);
+#pragma unroll
+                for (int m = 0; m < 8; ++m) dst[m] = make_float4(y[4 * m], y[4 * m + 1], y[4 * m + 2], y[4 * m + 3]);
+            }
+        }
     }
 }
 
@@ -2003,13 +2185,21 @@ hipError_t launch(Kind kind, int a, const Params& p, Mapping map, hipStream_t st
     return hipErrorInvalidValue;
 }
 
+// Workgroups (of 256 threads) of the long rows' kernel: the four that a CU's LDS holds.
+constexpr int64_t kFwhtGrid = 1024;
+
 template <int LOG2D>
 static hipError_t launch_fwht_n(const Params& p, hipStream_t st) {
     constexpr int TPR = (1 << LOG2D) / 32;
     constexpr int T = TPR < 256 ? 256 : TPR;
     constexpr int R = T / TPR;
-    const int64_t g = (p.M + R - 1) / R;
-    hipLaunchKernelGGL((fwht_kernel<LOG2D>), dim3((unsigned)g), dim3(T), 0, st, p);
+    const int64_t groups = (p.M + R - 1) / R;
+    if constexpr (LOG2D > 10) {
+        const int64_t g = std::min<int64_t>(groups, kFwhtGrid * 256 / T);
+        hipLaunchKernelGGL((fwht_long_kernel<LOG2D>), dim3((unsigned)g), dim3(T), 0, st, p, groups);
+    } else {
+        hipLaunchKernelGGL((fwht_kernel<LOG2D>), dim3((unsigned)groups), dim3(T), 0, st, p);
+    }
     return hipGetLastError();
 }
 

@@ -442,6 +442,19 @@ def test_fwht_parity(d):
     assert_exact((host(c), host(s_), host(y)), want, f"fwht d={d}")
 
 
+@pytest.mark.parametrize("d", [32, 128, 512, 1024, 2048, 4096, 8192, 16384])
+def test_fwht_row_counts(d):
+    """The full-row FWHT where a workgroup's or wave's last rows are missing
+    (one row, one less and one more than a workgroup's), without the fp32
+    output: bit-identical codes and scales."""
+    per = max(1, 8192 // d)
+    for M in sorted({1, max(1, per - 1), per + 1, 2 * per}):
+        X = synth.activations(M, d, "student_t3", seed=73, chan_frac=0.01, chan_factor=40.0)
+        want = oracle.fwht(X)
+        c, s_, _ = kq.fwht(dev_bf16(X))
+        assert np.array_equal(host(s_), want[1]) and np.array_equal(host(c), want[0]), (M, d)
+
+
 def test_hip_graph_replays_match_eager():
     """The hot-path and comparator launches captured into one HIP graph (as the
     benchmark's power-of-two-d table does) and replayed three times, with eager
