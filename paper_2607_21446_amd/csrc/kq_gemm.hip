@@ -709,6 +709,11 @@ constexpr int64_t kPipeMaxK = int64_t(1) << 24;
 // So the smallest split tile that still gives a CU no more than one workgroup, and
 // past 256 tiles of 64 x 64 the pipelined tile that needs fewer rounds (two 128 x
 // 128 workgroups share a CU and take as long as one of 256 x 256).
+// The residual's epilogue moves 8 bytes an element, as long as the products of a short K:
+// there two workgroups on a CU, one storing while the other multiplies, are the faster
+// at any number of rounds.  The calibration step by 256 x 256 and 128 x 128 tiles, us:
+// 9216 x 512 x 2048 167, 149; 6000 x 1024 x 2900 227, 205; 4096 x 1152 x 4608 296, 273;
+// 18432 x 1152 x 3072 630, 616; 8192 x 1536 x 3072 394, 380; 18432 x 3072 x 3072 1365, 1404.
 enum class GemmTile { Split32, Split32x64, Split64, Pipe128, Pipe256 };
 
 static GemmTile gemm_tile_of(const GemmParams& g) {
@@ -716,6 +721,7 @@ static GemmTile gemm_tile_of(const GemmParams& g) {
     if (tiles(32, 32) <= 256) return GemmTile::Split32;
     if (tiles(32, 64) <= 256) return GemmTile::Split32x64;
     if (tiles(64, 64) <= 256 || g.K > kPipeMaxK) return GemmTile::Split64;
+    if (g.rh && g.K <= 1536) return GemmTile::Pipe128;
     return (tiles(128, 128) + 511) / 512 <= (tiles(256, 256) + 255) / 256 ? GemmTile::Pipe128 : GemmTile::Pipe256;
 }
 
