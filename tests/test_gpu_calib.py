@@ -58,6 +58,8 @@ CASES = [
     # 256 x 256 tiles in K parts; shared factors sum over the blocks
     (2803, 701, 2080, 4, True, "random"),
     (2300, 1290, 1568, 2, False, "random"),
+    # the residual of a short K on more 128 x 128 tiles than one round
+    (4100, 2100, 64, 4, True, "random"),
 ]
 
 
