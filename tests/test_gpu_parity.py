@@ -676,6 +676,13 @@ def test_mxfp4_gemm_k_tails(M, N, K, off):
     assert np.array_equal(c16, oracle.f32_to_bf16(C))
 
 
+@pytest.mark.parametrize("blocks", [*range(1, 19), 30, 70])
+def test_mxfp4_gemm_scale_row_ends(blocks):
+    """The last 1 to 16 scales of a row (in loads of 8, 4, 2 and 1 bytes) and scale
+    rows at every alignment, on the pipelined tile."""
+    test_mxfp4_gemm_k_tails(1025, 1030, 32 * blocks, blocks & 1)
+
+
 @pytest.mark.parametrize("M,N", [(1, 1), (33, 67), (250, 1251), (700, 1301), (1025, 1153), (2950, 3101)])
 @pytest.mark.parametrize("off", [1, 3])
 def test_mxfp4_gemm_c_at_element_alignment(M, N, off):
