@@ -756,26 +756,41 @@ constexpr int64_t kPipeMaxK = int64_t(1) << 24;
 //   256 x 256 pipelined        3000 x 3000: 12.3 / 16.5 / 26.3 / 64.8; 128 x 128 12.5 / 17.6 / 31.0 / 84.8
 // So the smallest split tile that still gives a CU no more than one workgroup, and
 // past 256 tiles of 64 x 64 the pipelined tile that needs fewer rounds (two 128 x
-// 128 workgroups share a CU and take as long as one of 256 x 256).
-// The residual's epilogue moves 8 bytes an element, as long as the products of a short K:
-// there two workgroups on a CU, one storing while the other multiplies, are the faster
-// at any number of rounds.  The calibration step by 256 x 256 and 128 x 128 tiles, us:
-// 9216 x 512 x 2048 167, 149; 6000 x 1024 x 2900 227, 205; 4096 x 1152 x 4608 296, 273;
-// 18432 x 1152 x 3072 630, 616; 8192 x 1536 x 3072 394, 380; 18432 x 3072 x 3072 1365, 1404.
-enum class GemmTile { Split32, Split32x64, Split64, Pipe128, Pipe256 };
+// 128 workgroups share a CU and take as long as one of 256 x 256).  But:
+//
+// K <= 1536: stores (and C, where it is added to) take as long as the products, and of two
+// workgroups on a CU one stores while the other multiplies.  There 128 x 128 unless
+// it needs twice the rounds.  128 x 128 over 256 x 256, in time, 39 sizes with more rounds but
+// less than twice: K 1152 0.72 - 0.97, 1536 0.75 - 1.01, 1920 0.77 - 1.09, 2240 0.83 - 1.16
+// (onto C 0.72 - 0.95, 0.75 - 0.96, 0.78 - 0.98, 0.83 - 1.04); with twice the rounds 0.83 - 1.10 at
+// 1152, 0.86 - 1.14 at 1536.  For the residual, which moves 8 bytes an element and has the
+// most work besides, at any number of rounds: the calibration step by 256 x 256 and 128 x
+// 128 tiles, us: 9216 x 512 x 2048 167, 149; 6000 x 1024 x 2900 227, 205; 4096 x 1152 x 4608
+// 296, 273; 18432 x 1152 x 3072 630, 616; 8192 x 1536 x 3072 394, 380; 18432 x 3072 x 3072 1365, 1404.
+// K <= 128, a single stage: 128 x 128 always (0.79 - 1.03).
+//
+// N <= 32 with more than 256 tiles of 32 x 32 (C is four times narrower than a 128 x 128
+// tile): 32 x 32 tiles of two waves, many on a CU.  Not the residual, whose sums of
+// squares have room for one a tile of 64 x 64.  128 x 128 and so, us, K 64 / 480 / 1152 /
+// 3072: 18432 x 32 4.2 / 5.6 / 6.9 / 12.2 and 3.8 / 4.4 / 5.9 / 15.8; 70000 x 8 onto C
+// 11.3 / 14.4 / 19.4 / 33.8 and 6.6 / 7.9 / 13.5 / 33.7.
+enum class GemmTile { Thin32, Split32, Split32x64, Split64, Pipe128, Pipe256 };
 
 static GemmTile gemm_tile_of(const GemmParams& g) {
     auto tiles = [&](int64_t tm, int64_t tn) { return ((g.M + tm - 1) / tm) * ((g.N + tn - 1) / tn); };
     if (tiles(32, 32) <= 256) return GemmTile::Split32;
+    if (g.N <= 32 && g.K <= 1152 && !g.rh) return GemmTile::Thin32;
     if (tiles(32, 64) <= 256) return GemmTile::Split32x64;
     if (tiles(64, 64) <= 256 || g.K > kPipeMaxK) return GemmTile::Split64;
-    if (g.rh && g.K <= 1536) return GemmTile::Pipe128;
-    return (tiles(128, 128) + 511) / 512 <= (tiles(256, 256) + 255) / 256 ? GemmTile::Pipe128 : GemmTile::Pipe256;
+    const int64_t rounds128 = (tiles(128, 128) + 511) / 512, rounds256 = (tiles(256, 256) + 255) / 256;
+    if (g.K <= 1536 && (g.rh || rounds128 < 2 * rounds256)) return GemmTile::Pipe128;
+    return g.K <= 128 || rounds128 <= rounds256 ? GemmTile::Pipe128 : GemmTile::Pipe256;
 }
 
 int64_t mxfp4_gemm_workgroups(const GemmParams& g) {
     auto tiles = [&](int64_t tm, int64_t tn) { return ((g.M + tm - 1) / tm) * ((g.N + tn - 1) / tn); };
     switch (gemm_tile_of(g)) {
+        case GemmTile::Thin32:
         case GemmTile::Split32: return tiles(32, 32);
         case GemmTile::Split32x64: return tiles(32, 64);
         case GemmTile::Split64: return tiles(64, 64);
@@ -813,6 +828,7 @@ static void launch_pipe(const GemmParams& g, hipStream_t st) {
 
 hipError_t launch_mxfp4_gemm(const GemmParams& g, hipStream_t st) {
     switch (gemm_tile_of(g)) {
+        case GemmTile::Thin32: launch_split<1, 1, 2, 4>(g, st); break;
         case GemmTile::Split32: launch_split<1, 1, 8, 4>(g, st); break;
         case GemmTile::Split32x64: launch_split<2, 1, 8, 3>(g, st); break;
         case GemmTile::Split64: launch_split<2, 2, 8, 2>(g, st); break;

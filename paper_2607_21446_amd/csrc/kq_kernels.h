@@ -70,7 +70,7 @@ struct GemmParams {
 
 hipError_t launch(Kind kind, int a, const Params& p, Mapping map, hipStream_t st);
 hipError_t launch_mxfp4_gemm(const GemmParams& g, hipStream_t st);
-int64_t mxfp4_gemm_workgroups(const GemmParams& g);  // of the call: at most max(256, 128 x 128 tiles)
+int64_t mxfp4_gemm_workgroups(const GemmParams& g);  // of a residual's call: at most max(256, 64 x 64 tiles)
 // The calibration step's two operands in one launch: px with the factors of its LU
 // parameters, pw with those of the inverse blocks; codes, scales and the calibration
 // outputs of both.  An operand of M rows and nb blocks takes calib_quant_strips(M, nb)

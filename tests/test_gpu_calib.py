@@ -60,6 +60,8 @@ CASES = [
     (2300, 1290, 1568, 2, False, "random"),
     # the residual of a short K on more 128 x 128 tiles than one round
     (4100, 2100, 64, 4, True, "random"),
+    # a residual at most 32 wide on more than 256 tiles of 32 x 32
+    (8300, 20, 64, 4, True, "random"),
 ]
 
 

@@ -683,6 +683,16 @@ def test_mxfp4_gemm_scale_row_ends(blocks):
     test_mxfp4_gemm_k_tails(1025, 1030, 32 * blocks, blocks & 1)
 
 
+@pytest.mark.parametrize("M,N,K", [
+    # C at most 32 wide on two-wave tiles: one K chunk, an odd number of them, the last K of the rule and past it
+    (8193, 1, 32), (8225, 31, 96), (8300, 32, 1120), (8200, 20, 1152), (8200, 20, 1184), (8210, 33, 96),
+    # 128 x 128: a single K stage, and more rounds but less than twice those of 256 x 256, up to K 1536
+    (3001, 2999, 96), (3000, 3001, 128), (2200, 7300, 160), (2201, 7301, 1536), (2201, 7301, 1568)])
+def test_mxfp4_gemm_tile_rule(M, N, K):
+    """Both sides of every line of the dispatch that K and the number of rounds draw."""
+    test_mxfp4_gemm_k_tails(M, N, K, 0)
+
+
 @pytest.mark.parametrize("M,N", [(1, 1), (33, 67), (250, 1251), (700, 1301), (1025, 1153), (2950, 3101)])
 @pytest.mark.parametrize("off", [1, 3])
 def test_mxfp4_gemm_c_at_element_alignment(M, N, off):
