@@ -443,11 +443,16 @@ __global__ __launch_bounds__(64 * WM * WN) void calib_backward_kernel(const Back
 // Yneg = -(X W^T): both operands K-contiguous, one term.
 template <int WM, int WN, int TM, int TN, bool PING>
 __global__ __launch_bounds__(64 * WM * WN) void calib_reference_kernel(const Opnd A, const Opnd B, float* out, int64_t K,
-                                                                       int64_t ntn) {
+                                                                       uint32_t ntn) {
     typedef CalibTile<1, WM, WN, TM, TN> T;
     __shared__ __align__(16) uint8_t lds[T::kLdsBytes];
-    const int64_t wk = xcd_work(blockIdx.x, gridDim.x);
-    const int64_t n0 = (wk % ntn) * T::BN, m0 = (wk / ntn) * T::BM;
+    // Rows of tiles one after the other; few rows of many columns, columns one after the other, or
+    // every XCD reads all of W.  Row after row / column after column, us: 8 x 24 tiles
+    // (1024 x 3072 x 1152) 19.8 / 16.2; 8 x 17 (1024 x 2049 x 2304) 25.7 / 27.4; 72 x 96 at d 640 201 / 213.
+    const uint32_t wk = (uint32_t)xcd_work(blockIdx.x, gridDim.x), mt = gridDim.x / ntn;
+    const bool few_rows = ntn >= 24 && 3 * mt <= ntn;
+    const uint32_t fast = few_rows ? mt : ntn, slow_i = wk / fast, fast_i = wk - slow_i * fast;
+    const int64_t n0 = int64_t(few_rows ? slow_i : fast_i) * T::BN, m0 = int64_t(few_rows ? fast_i : slow_i) * T::BM;
     f32x16 acc[TM][TN];
     const Opnd a[1] = {A};
     calib_product<1, false, false, WM, WN, TM, TN, PING>(a, B, lds, m0, n0, 0, K, acc);
@@ -866,11 +871,19 @@ hipError_t launch_calib_reference(const uint16_t* X, int64_t R, int64_t d, const
                                   float* Yneg, hipStream_t st) {
     if (R == 0 || o == 0) return hipSuccess;
     const Opnd A{reinterpret_cast<const uint8_t*>(X), R, d, d * 2}, B{reinterpret_cast<const uint8_t*>(W), o, d, d * 2};
-    if (cdiv(R, 256) * cdiv(o, 256) >= 128) {
-        const int64_t ntn = cdiv(o, 256);
+    // 256 x 256 tiles, unless there are few of them, they need (nearly) as many rounds as 128 x 128
+    // ones (two workgroups a CU), or the stores of a short K outweigh its products: there the
+    // 128 x 128 workgroups of a CU store and multiply beside each other.  128 x 128 / 256 x 256, us:
+    //   100000 x  100 (2, 2 rounds)   d 64: 15.3 / 22.7; 1152: 61 / 73; 3072: 186 / 181
+    //   100000 x  257 (5, 4)          d 640: 72 / 91
+    //    18432 x 3072 (7, 4)          d 64: 37 / 45; 160: 51.5 / 56.4; 320: 72.7 / 71.7; 640: 113 / 101
+    //   100000 x 1152 (14, 8)         d 64: 94 / 108; 160: 167 / 133
+    const int64_t r1 = cdiv(cdiv(R, 128) * cdiv(o, 128), 512), t2 = cdiv(R, 256) * cdiv(o, 256), r2 = cdiv(t2, 256);
+    if (t2 >= 128 && 3 * r1 > 4 * r2 && d > 64 && (d > 160 || R * o > (int64_t(1) << 26))) {
+        const uint32_t ntn = uint32_t(cdiv(o, 256));
         calib_reference_kernel<4, 2, 2, 4, true><<<unsigned(cdiv(R, 256) * ntn), 512, 0, st>>>(A, B, Yneg, d, ntn);
     } else {
-        const int64_t ntn = cdiv(o, 128);
+        const uint32_t ntn = uint32_t(cdiv(o, 128));
         calib_reference_kernel<2, 2, 2, 2, false><<<unsigned(cdiv(R, 128) * ntn), 256, 0, st>>>(A, B, Yneg, d, ntn);
     }
     return hipGetLastError();

@@ -83,6 +83,16 @@ def test_calib_reference_parity(R, o, d):
     assert np.all(np.abs(Y - ref) <= tol), np.max(np.abs(Y - ref) - tol)
 
 
+@pytest.mark.parametrize("R,o,d", [
+    # 128 x 128 tiles: rows of tiles fastest, columns fastest, more tiles than a round by a short K
+    (300, 3100, 160), (300, 2900, 96), (3000, 2999, 64), (3000, 2999, 160),
+    # 256 x 256: rows fastest, columns fastest, the three stage buffers refilled many times
+    (1400, 6200, 192), (3000, 2999, 192), (3000, 2999, 1568)])
+def test_calib_reference_tiles(R, o, d):
+    """Both tiles of the reference product and both orders of its tiles."""
+    test_calib_reference_parity(R, o, d)
+
+
 @pytest.mark.parametrize("R,o,d,a,per_block,start", CASES)
 def test_calib_step_parity(R, o, d, a, per_block, start):
     nfac = d // 32 if per_block else 1
