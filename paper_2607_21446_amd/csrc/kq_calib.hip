@@ -291,7 +291,8 @@ __device__ __forceinline__ void store_neg(const f32x16 (&acc)[TM][TN], float* ou
 // c1 = 2 / (R o), c2 = lambda * 2 / (rows d), and the block transforms take the
 // per-block sums  S_j = left_j^T dL/dy_j  (left = the operand before the transform).
 // The second term's sums come from the quantizer; this epilogue makes the first's,
-// without c1.
+// times the power of two of c1 (c1_pow2, exact: the sums leave fp32's range no sooner than
+// the gradient does).
 struct Side {
     Opnd A[2], B;             // the product: residual terms, dequantized operand
     Opnd left;                // [M, d] bf16
@@ -299,6 +300,7 @@ struct Side {
     float* partial;           // [m_tiles * ks, d / 32, 32, 32]
     int64_t K, kchunk;        // K (a multiple of 32) in ks parts of kchunk
     int64_t ks, works;        // works = m_tiles * ks * ntn
+    float c1_pow2;
 };
 
 // The Gram sums of a tile: left^T (P m) per 32-column block, on the matrix cores with
@@ -345,6 +347,17 @@ __device__ __forceinline__ void gram_tile(const f32x16 (&acc)[TM][TN], const Sid
             if (rows && col < d) pass[i][j] = rows & ~s.clipped[(r0 >> 5) * d + col];
         }
     }
+    // c1_pow2 goes in before the sums where the product is large, after them where it is not
+    // (there it could take terms of a small one below bf16's range)
+    float top = 0.0f;
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) top = fmaxf(top, fabsf(acc[i][j][e]));
+    const bool large = __builtin_amdgcn_ballot_w64(top >= 0x1p30f) != 0u;
+    const float before = large ? s.c1_pow2 : 1.0f, after = large ? 1.0f : s.c1_pow2;
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     stage_barrier();
     f32x16 gram[TN];
@@ -370,7 +383,7 @@ __device__ __forceinline__ void gram_tile(const f32x16 (&acc)[TM][TN], const Sid
                     // accumulator 8 k + u is row 16 k + 8 (u / 4) + 4 h + u % 4
                     const int bit = 16 * k + 8 * (u / 4) + (u % 4);
                     const uint32_t keep = (uint32_t)((int32_t)(bits << (31 - bit)) >> 31);
-                    const float v = __uint_as_float(__float_as_uint(acc[i][j][8 * k + u]) & keep);
+                    const float v = __uint_as_float(__float_as_uint(acc[i][j][8 * k + u] * before) & keep);
                     g[0][u] = (__bf16)v;
                     const float r1 = v - (float)g[0][u];  // exact
                     g[1][u] = (__bf16)r1;
@@ -388,7 +401,7 @@ __device__ __forceinline__ void gram_tile(const f32x16 (&acc)[TM][TN], const Sid
     for (int j = 0; j < TN; ++j) {
         float* const dst = sums + ((wm * WN + wn) * TN + j) * 1024;
 #pragma unroll
-        for (int e = 0; e < 16; ++e) dst[(8 * (e / 4) + 4 * h + (e % 4)) * 32 + l32] = gram[j][e];
+        for (int e = 0; e < 16; ++e) dst[(8 * (e / 4) + 4 * h + (e % 4)) * 32 + l32] = gram[j][e] * after;
     }
     __syncthreads();
     // the WM row groups of a block, in order, and one write per block
@@ -461,14 +474,15 @@ __global__ __launch_bounds__(64 * WM * WN) void calib_reference_kernel(const Opn
 
 // ------------------------------------------------------------ small kernels
 
-// S = c1 sum over the slots of partial - c2 sum over the quantizer's strips of dpart,
+// S = c1 / c1_pow2 sum over the slots of partial - c2 sum over the quantizer's strips of dpart,
 // summed in fp64 and a fixed order (16 threads per four elements, each every 16th
 // term), in place: partial[0][j][e] the nearest fp32, dpart[0][j][e] that of the rest.
 struct ReduceSide {
     float* partial;      // [slots, nb, 1024]
     float* dpart;        // [strips, nb, 1024]
     int64_t slots, strips;
-    double c1, c2_unit;  // c2 = lambda * c2_unit
+    double c1;           // c1 / c1_pow2
+    double c2_unit;      // c2 = lambda * c2_unit
 };
 
 __global__ __launch_bounds__(256) void gram_reduce_kernel(const ReduceSide s0, const ReduceSide s1, int64_t nb,
@@ -497,7 +511,7 @@ __global__ __launch_bounds__(256) void gram_reduce_kernel(const ReduceSide s0, c
         w[3] += x.w;
     }
 #pragma unroll
-    for (int i = 0; i < 4; ++i) red[part][e4][i] = s.c1 * v[i] + c2 * w[i];
+    for (int i = 0; i < 4; ++i) red[part][e4][i] = s.c1 * v[i] + (c2 != 0.0 ? c2 * w[i] : 0.0);
     __syncthreads();
     if (threadIdx.x < 64) {
         double t = 0.0;
@@ -893,6 +907,9 @@ hipError_t launch_calib_backward(const CalibPlan& pl, const CalibStepArgs& s, in
     unsigned char* ws = s.ws;
     const int64_t R = pl.R, o = pl.o, d = pl.d;
     const Opnd rh{ws + pl.rh, pl.Rp, pl.op, pl.op * 2}, rl{ws + pl.rl, pl.Rp, pl.op, pl.op * 2};
+    const double c1 = 2.0 / (double(R) * double(o));
+    // (at most 1/2: what comes out near FLT_MAX still rounds to a finite bf16)
+    const float c1_pow2 = float(std::ldexp(1.0, std::min(std::ilogb(c1), -1)));
     BackwardArgs b{};
     b.ntn = pl.ntn;
     // activation side: P = res . What  (M = R, N = d, K = o)
@@ -904,7 +921,8 @@ hipError_t launch_calib_backward(const CalibPlan& pl, const CalibStepArgs& s, in
                  pl.op,
                  pl.act_kchunk,
                  pl.act_ks,
-                 pl.act_mt * pl.act_ks * pl.ntn};
+                 pl.act_mt * pl.act_ks * pl.ntn,
+                 c1_pow2};
     // weight side: P = res^T . Ahat  (M = o, N = d, K = R)
     b.wgt = Side{{rh, rl},
                  {ws + pl.qA, R, d, d * 2},
@@ -914,15 +932,15 @@ hipError_t launch_calib_backward(const CalibPlan& pl, const CalibStepArgs& s, in
                  pl.Rp,
                  pl.w_kchunk,
                  pl.w_ks,
-                 pl.w_mt * pl.w_ks * pl.ntn};
+                 pl.w_mt * pl.w_ks * pl.ntn,
+                 c1_pow2};
     const unsigned works = unsigned(b.act.works + b.wgt.works);
     if (pl.big) calib_backward_kernel<4, 2, 2, 4, true><<<works, 512, 0, st>>>(b);
     else calib_backward_kernel<2, 2, 2, 2, false><<<works, 256, 0, st>>>(b);
-    const double c1 = 2.0 / (double(R) * double(o));
     const ReduceSide ra{b.act.partial, reinterpret_cast<float*>(ws + pl.dA), pl.act_mt * pl.act_ks, pl.strips_a,
-                        c1, 2.0 / (double(R) * double(d))};
+                        c1 / c1_pow2, 2.0 / (double(R) * double(d))};
     const ReduceSide rw{b.wgt.partial, reinterpret_cast<float*>(ws + pl.dW), pl.w_mt * pl.w_ks, pl.strips_w,
-                        c1, 2.0 / (double(o) * double(d))};
+                        c1 / c1_pow2, 2.0 / (double(o) * double(d))};
     gram_reduce_kernel<<<dim3(unsigned(pl.nb), 16, 2), 256, 0, st>>>(ra, rw, pl.nb, s.lambdas);
     LuGradArgs la{};
     la.lu = s.lu;

@@ -115,6 +115,26 @@ def test_calib_step_parity(R, o, d, a, per_block, start):
     assert err <= 1e-4 * scale
 
 
+@pytest.mark.parametrize("R,o,d,e", [(64, 64, 64, 60), (300, 280, 96, 59), (700, 500, 96, 59), (1, 1, 32, 60)])
+def test_calib_gradient_of_large_activations(R, o, d, e):
+    """Activations times 2^e, lambda_W 0: every term of the gradient is quadratic in
+    them and a power of two is exact, so the gradient is exactly 2^(2 e) times
+    as large.  At these e the sums of the products leave fp32's range if they are
+    kept without their factor 2 / (R o), which the gradient itself does not."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(R + o)
+    X = torch.randn((R, d), generator=g, device="cuda").to(torch.bfloat16)
+    W = torch.randn((o, d), generator=g, device="cuda").to(torch.bfloat16)
+    lu = dev_f32(synth.lu_params(d // 32, seed=7))
+    grads = []
+    for x in (X, (X.float() * 2.0 ** e).to(torch.bfloat16)):
+        for lam in ((0.7, 0.0), (0.0, 0.0)):
+            _, grad = kq.calib_step(x, W, kq.calib_reference(x, W), lu, dev_f32(np.array(lam)), a=4)
+            grads.append(host(grad).astype(np.float64))
+    assert np.abs(grads[0]).max() > 0 and np.all(np.isfinite(grads[2])) and np.all(np.isfinite(grads[3]))
+    assert np.array_equal(grads[2] * 2.0 ** (-2 * e), grads[0]) and np.array_equal(grads[3] * 2.0 ** (-2 * e), grads[1])
+
+
 def test_calib_step_adam_update():
     R, o, d, a = 96, 64, 128, 4
     nfac = d // 32
