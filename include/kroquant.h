@@ -356,8 +356,12 @@ kq_status kq_lu_to_factors(const float* abc, int a, int64_t nfac, float* A, floa
  * loss sums are fp64.
  *
  * kq_calib_workspace_size -- bytes of device workspace that kq_calib_step and
- * kq_calibrate need for these sizes (about 6.6 R d + 8 R o + 6.6 o d bytes
- * plus per-workgroup partial sums).  Same size checks as kq_calib_step.
+ * kq_calibrate need for these sizes: about 2.7 R d + 4 R o + 2.7 o d bytes and
+ * per-workgroup partial sums.  Small sizes are told more (up to 6.6 R d + 12 R o +
+ * 6.6 o d bytes and partial sums, or just above KQ_CALIB_NOALLOC_MAX_BYTES): what
+ * exceeds KQ_CALIB_NOALLOC_MAX_BYTES here is what kq_calib_step_noalloc refuses.
+ * A workspace sized by an earlier build of the library is large enough.  Same
+ * size checks as kq_calib_step.
  */
 kq_status kq_calib_workspace_size(int64_t R, int64_t o, int64_t d, int a, int64_t nfac, size_t* bytes);
 
@@ -393,7 +397,7 @@ kq_status kq_calib_step(const uint16_t* X, int64_t R, int64_t d, const uint16_t*
                         float* adam_m, float* adam_v, int adam_t, float lr, void* workspace,
                         size_t workspace_bytes, void* stream);
 
-/* Workspace size that kq_calib_step_noalloc goes up to (64 MiB). */
+/* Scratch bytes held per GPU for kq_calib_step_noalloc (64 MiB). */
 #define KQ_CALIB_NOALLOC_MAX_BYTES (64u << 20)
 
 /*
@@ -401,14 +405,13 @@ kq_status kq_calib_step(const uint16_t* X, int64_t R, int64_t d, const uint16_t*
  * without any allocation, for callers that cannot allocate device memory
  * (code under HIP graph capture, tight loops, harnesses that forbid
  * hipMalloc).  Its workspace is a scratch array of the library in device
- * memory, 96 MiB, one copy per GPU, held from the library's first use on that
- * GPU until the process ends; its device address is looked up once per GPU on
- * the first call there (with that GPU current).
+ * memory, KQ_CALIB_NOALLOC_MAX_BYTES bytes, one copy per GPU, held from the
+ * library's first use on that GPU until the process ends; its device address
+ * is looked up once per GPU on the first call there (with that GPU current).
  * Arguments, results and errors as kq_calib_step; sizes whose workspace
  * (kq_calib_workspace_size) exceeds KQ_CALIB_NOALLOC_MAX_BYTES return
  * KQ_ERROR_INVALID_VALUE before any HIP call (e.g. R = 2048 rows with
- * o = d = 1024 fit, R = 4096 with o = d = 1152 do not; a few rows of very many
- * columns fit up to a workspace size a third larger).  The step writes every
+ * o = d = 1024 fit, R = 4096 with o = d = 1152 do not).  The step writes every
  * part of the scratch it reads, so what an earlier call left there does not
  * matter.  All calls on one GPU share its scratch: calls that overlap in time
  * on one GPU (concurrent streams, or host threads enqueueing on different

@@ -595,10 +595,7 @@ kq_status kq_calib_step(const uint16_t* X, int64_t R, int64_t d, const uint16_t*
 // the host that name is a stand-in, not a device address): the device address
 // of each GPU's copy comes from hipGetSymbolAddress, taken once per device
 // with that device current, and only that address reaches the kernels.
-// Sizes whose told workspace is at most KQ_CALIB_NOALLOC_MAX_BYTES use at most 1.4 times
-// that (a single row of a wide layer; ordinary ones use less than they are told).
-constexpr size_t kCalibScratchBytes = size_t(KQ_CALIB_NOALLOC_MAX_BYTES) / 2 * 3;
-static __device__ __align__(256) unsigned char calib_scratch[kCalibScratchBytes];
+static __device__ __align__(256) unsigned char calib_scratch[KQ_CALIB_NOALLOC_MAX_BYTES];
 
 namespace {
 
@@ -638,10 +635,11 @@ kq_status kq_calib_step_noalloc(const uint16_t* X, int64_t R, int64_t d, const u
     kq_status st = check_step(X, R, d, W, o, Yneg, lu, a, nfac, lambdas, grad, losses, adam_m, adam_v, adam_t);
     if (st != KQ_SUCCESS) return st;
     const kq::CalibPlan pl = kq::calib_plan(R, o, d, a, nfac);
-    if (pl.told > (size_t)KQ_CALIB_NOALLOC_MAX_BYTES || pl.used > kCalibScratchBytes)
+    if (pl.total > (size_t)KQ_CALIB_NOALLOC_MAX_BYTES)
         return fail(KQ_ERROR_INVALID_VALUE,
-                    "kq_calib_step_noalloc: these sizes need %zu bytes of scratch, more than the %zu it holds "
-                    "(use kq_calib_step with a workspace)", pl.total, (size_t)KQ_CALIB_NOALLOC_MAX_BYTES);
+                    "kq_calib_step_noalloc: kq_calib_workspace_size is %zu bytes for these sizes, more than the %zu of "
+                    "scratch it goes up to (use kq_calib_step with a workspace)",
+                    pl.total, (size_t)KQ_CALIB_NOALLOC_MAX_BYTES);
     void* ws = nullptr;
     if ((st = scratch_address(&ws)) != KQ_SUCCESS) return st;
     // every buffer of the plan is written before it is read within the step,

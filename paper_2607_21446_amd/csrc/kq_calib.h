@@ -12,6 +12,7 @@ struct CalibPlan {
     int64_t R = 0, o = 0, d = 0, nb = 0, nfac = 0;
     int a = 4;
     bool big = true;                      // 256 x 256 tiles of the backward products, else 128 x 128
+    bool fold = false;                    // the backward products' block sums go onto the quantizer's, no gpa and gpw
     int64_t ntn = 0;                      // column tiles of the d axis
     int64_t act_mt = 0, act_ks = 0, act_kchunk = 0;  // activation side: row tiles, K parts and their length
     int64_t w_mt = 0, w_ks = 0, w_kchunk = 0;        // weight side
@@ -25,9 +26,7 @@ struct CalibPlan {
     size_t rh = 0, rl = 0;                // the residual's two bf16 terms [Rp, op]
     size_t gpa = 0, gpw = 0, sqa = 0, sqw = 0, sr = 0;
     size_t grad = 0, am = 0, av = 0, lam = 0;
-    size_t used = 0;                      // bytes laid out
-    size_t told = 0;                      // the size that kq_calib_step_noalloc goes by
-    size_t total = 0;                     // what a caller's workspace holds: the larger of the two
+    size_t total = 0;                     // what a caller's workspace holds
 };
 
 CalibPlan calib_plan(int64_t R, int64_t o, int64_t d, int a, int64_t nfac);

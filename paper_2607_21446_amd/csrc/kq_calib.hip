@@ -32,6 +32,7 @@
 
 #include "kq_calib.h"
 #include "kq_kernels.h"
+#include "kroquant.h"
 
 namespace kq {
 namespace {
@@ -301,6 +302,11 @@ struct Side {
     int64_t K, kchunk;        // K (a multiple of 32) in ks parts of kchunk
     int64_t ks, works;        // works = m_tiles * ks * ntn
     float c1_pow2;
+    // FOLD (one m tile, one K part): the side's gradient sums, in place of strip 0 of the quantizer's
+    float* sums;              // [strips, d / 32, 32, 32]
+    int64_t strips;
+    double c1, c2_unit;       // c1 / c1_pow2; c2 = lambda * c2_unit
+    const float* lambda;
 };
 
 // The Gram sums of a tile: left^T (P m) per 32-column block, on the matrix cores with
@@ -311,7 +317,10 @@ struct Side {
 // 16 memory latencies) and read transposed, its K index in the order the
 // accumulators have: k-step s, lane half h holds rows 16 s + 4 h + 0..3, 16 s + 8 + 4 h + 0..3.
 // 18432 x 3072 x 3072, both sides: 335 us before, of 1250.
-template <int WM, int WN, int TM, int TN>
+//
+// FOLD: a few rows and features of very many columns, where partial sums of their own
+// would be most of the workspace.
+template <int WM, int WN, int TM, int TN, bool FOLD>
 __device__ __forceinline__ void gram_tile(const f32x16 (&acc)[TM][TN], const Side& s, uint8_t* lds_generic, int64_t slot,
                                           int64_t m0, int64_t n0) {
     constexpr int WAVES = WM * WN, BM = 32 * WM * TM, BN = 32 * WN * TN;
@@ -414,6 +423,20 @@ __device__ __forceinline__ void gram_tile(const f32x16 (&acc)[TM][TN], const Sid
             const float4 o = *reinterpret_cast<const float4*>(sums + w * (WN * TN * 1024) + k);
             v = make_float4(v.x + o.x, v.y + o.y, v.z + o.z, v.w + o.w);
         }
+        if (FOLD) {
+            float* const at = s.sums + blk * 1024 + k % 1024;
+            const double c2 = -(double)*s.lambda * s.c2_unit;
+            double x[4] = {s.c1 * v.x, s.c1 * v.y, s.c1 * v.z, s.c1 * v.w};
+            for (int64_t c = 0; c < s.strips && c2 != 0.0; ++c) {
+                const float4 q = *reinterpret_cast<const float4*>(at + c * nb * 1024);
+                x[0] += c2 * q.x;
+                x[1] += c2 * q.y;
+                x[2] += c2 * q.z;
+                x[3] += c2 * q.w;
+            }
+            *reinterpret_cast<float4*>(at) = make_float4((float)x[0], (float)x[1], (float)x[2], (float)x[3]);
+            continue;
+        }
         *reinterpret_cast<float4*>(s.partial + (slot * nb + blk) * 1024 + k % 1024) = v;
     }
 }
@@ -435,7 +458,7 @@ struct BackwardArgs {
 // side P = res^T . Ahat (K = rows, strided in both).  A work is (m tile, K part,
 // column tile), the column tile fastest: the column tiles of one m tile and K
 // part read the same rows of the residual and run on one XCD.
-template <int WM, int WN, int TM, int TN, bool PING>
+template <int WM, int WN, int TM, int TN, bool PING, bool FOLD>
 __global__ __launch_bounds__(64 * WM * WN) void calib_backward_kernel(const BackwardArgs p) {
     typedef CalibTile<2, WM, WN, TM, TN> T;
     static_assert(WM * WN * TN * 4096 <= T::kLdsBytes && 2 * T::BM * T::BN <= T::kLdsBytes,
@@ -450,7 +473,7 @@ __global__ __launch_bounds__(64 * WM * WN) void calib_backward_kernel(const Back
     f32x16 acc[TM][TN];
     if (act) calib_product<2, false, true, WM, WN, TM, TN, PING>(s.A, s.B, lds, m0, n0, k_lo, k_hi, acc);
     else calib_product<2, true, true, WM, WN, TM, TN, PING>(s.A, s.B, lds, m0, n0, k_lo, k_hi, acc);
-    gram_tile<WM, WN, TM, TN>(acc, s, lds, slot, m0, n0);
+    gram_tile<WM, WN, TM, TN, FOLD>(acc, s, lds, slot, m0, n0);
 }
 
 // Yneg = -(X W^T): both operands K-contiguous, one term.
@@ -572,6 +595,9 @@ struct LuGradArgs {
 //   dL/dG_k[u][v] = sum_{p, q: bit_k(p) = u, bit_k(q) = v} dT[p][q] prod_{l != k} G_l[bit_l(p)][bit_l(q)]
 // (bit_1 the most significant of the 5-bit index), and for G = [[a, b], [c a, c b - 1/a]]:
 //   dL/da = dG00 + c dG10 + dG11 / a^2,  dL/db = dG01 + c dG11,  dL/dc = a dG10 + b dG11.
+//
+// TWO: the sums come in two terms (else ga and gw are all there is).
+template <bool TWO>
 __global__ __launch_bounds__(256) void lu_grad_kernel(const LuGradArgs p) {
     __shared__ float sU[32][33];
     __shared__ float sGW[32][33];
@@ -608,8 +634,8 @@ __global__ __launch_bounds__(256) void lu_grad_kernel(const LuGradArgs p) {
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 const int64_t e = j * 1024 + t + 256 * i;
-                a4[i] += double(p.ga[e]) + double(p.ga_lo[e]);
-                w4[i] += double(p.gw[e]) + double(p.gw_lo[e]);
+                a4[i] += TWO ? double(p.ga[e]) + double(p.ga_lo[e]) : double(p.ga[e]);
+                w4[i] += TWO ? double(p.gw[e]) + double(p.gw_lo[e]) : double(p.gw[e]);
             }
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
@@ -783,11 +809,12 @@ static double backward_cost(const SidePlan& act, const SidePlan& wgt, bool big) 
     return end + (n1 * l1 + n2 * l2) / S;
 }
 
-// The least workspace a caller is told of: 6.6 R d + 12 R o + 6.6 o d bytes and the
-// partial sums of 128-row tiles, of which the step now uses less, but for a few rows
-// of many columns (by up to a third: two block sums of 128 d bytes a side, where
-// this has one).  It also says which sizes kq_calib_step_noalloc takes.
-static size_t told_workspace(int64_t R, int64_t o, int64_t d, int a, int64_t nfac) {
+// The bytes that a workspace may hold at most, so that one sized by an earlier build of the
+// library is large enough (buffers of 6.6 R d + 12 R o + 6.6 o d bytes, and partial sums
+// of 128-row tiles): what the step itself leaves of them is the budget of its
+// partial sums.  kq_calib_step_noalloc takes the sizes for which this is at most
+// KQ_CALIB_NOALLOC_MAX_BYTES.
+static size_t workspace_budget(int64_t R, int64_t o, int64_t d, int a, int64_t nfac) {
     const int64_t nb = d / 32, ntn = cdiv(d, 256), act_mt = cdiv(R, 128), w_mt = cdiv(o, 128);
     const int64_t Rp = cdiv(R, BK) * BK, op = cdiv(o, BK) * BK, stages = Rp / BK;
     const int64_t act_chunks = std::max<int64_t>(1, std::min(act_mt, cdiv(2048, ntn)));
@@ -845,9 +872,9 @@ CalibPlan calib_plan(int64_t R, int64_t o, int64_t d, int a, int64_t nfac) {
     pl.av = take(size_t(nfac) * 15 * 4);
     pl.lam = take(2 * 4);
     // both sides with 256 x 256 or both with 128 x 128 tiles, whichever is cheaper, with
-    // as many K parts as the partial sums have room for in the workspace that is told anyway
-    const size_t told = told_workspace(R, o, d, a, nfac), slot = size_t(pl.nb) * 4096;
-    const int64_t room = told > off ? int64_t((told - off) / slot) : 0;
+    // as many K parts as the budget has room for partial sums
+    const size_t budget = workspace_budget(R, o, d, a, nfac), slot = size_t(pl.nb) * 4096;
+    const int64_t room = budget > off ? int64_t((budget - off) / slot) : 0;
     double best = HUGE_VAL;
     for (const bool big : {true, false}) {
         const int64_t T = big ? 256 : 128, ntn = cdiv(d, T);
@@ -873,11 +900,20 @@ CalibPlan calib_plan(int64_t R, int64_t o, int64_t d, int a, int64_t nfac) {
     }
     pl.act_ks = cdiv(pl.op, pl.act_kchunk);
     pl.w_ks = cdiv(pl.Rp, pl.w_kchunk);
-    pl.gpa = take(size_t(pl.act_mt * pl.act_ks) * slot);
-    pl.gpw = take(size_t(pl.w_mt * pl.w_ks) * slot);
-    pl.used = off;
-    pl.told = told;
-    pl.total = std::max(off, told);
+    // no room for one partial sum a side (R + o up to about 70): none of its own
+    pl.fold = pl.act_mt * pl.act_ks + pl.w_mt * pl.w_ks > room && R <= 128 && o <= 128;
+    if (pl.fold) {
+        pl.big = false;
+        pl.ntn = cdiv(d, 128);
+        pl.act_mt = pl.w_mt = pl.act_ks = pl.w_ks = 1;
+        pl.act_kchunk = pl.op;
+        pl.w_kchunk = pl.Rp;
+    } else {
+        pl.gpa = take(size_t(pl.act_mt * pl.act_ks) * slot);
+        pl.gpw = take(size_t(pl.w_mt * pl.w_ks) * slot);
+    }
+    // never below kq_calib_step_noalloc's limit where the budget is above it: callers go by this
+    pl.total = std::max(off, std::min(budget, size_t(KQ_CALIB_NOALLOC_MAX_BYTES) + 256));
     return pl;
 }
 
@@ -922,7 +958,12 @@ hipError_t launch_calib_backward(const CalibPlan& pl, const CalibStepArgs& s, in
                  pl.act_kchunk,
                  pl.act_ks,
                  pl.act_mt * pl.act_ks * pl.ntn,
-                 c1_pow2};
+                 c1_pow2,
+                 reinterpret_cast<float*>(ws + pl.dA),
+                 pl.strips_a,
+                 c1 / c1_pow2,
+                 2.0 / (double(R) * double(d)),
+                 s.lambdas};
     // weight side: P = res^T . Ahat  (M = o, N = d, K = R)
     b.wgt = Side{{rh, rl},
                  {ws + pl.qA, R, d, d * 2},
@@ -933,21 +974,27 @@ hipError_t launch_calib_backward(const CalibPlan& pl, const CalibStepArgs& s, in
                  pl.w_kchunk,
                  pl.w_ks,
                  pl.w_mt * pl.w_ks * pl.ntn,
-                 c1_pow2};
+                 c1_pow2,
+                 reinterpret_cast<float*>(ws + pl.dW),
+                 pl.strips_w,
+                 c1 / c1_pow2,
+                 2.0 / (double(o) * double(d)),
+                 s.lambdas + 1};
     const unsigned works = unsigned(b.act.works + b.wgt.works);
-    if (pl.big) calib_backward_kernel<4, 2, 2, 4, true><<<works, 512, 0, st>>>(b);
-    else calib_backward_kernel<2, 2, 2, 2, false><<<works, 256, 0, st>>>(b);
-    const ReduceSide ra{b.act.partial, reinterpret_cast<float*>(ws + pl.dA), pl.act_mt * pl.act_ks, pl.strips_a,
-                        c1 / c1_pow2, 2.0 / (double(R) * double(d))};
-    const ReduceSide rw{b.wgt.partial, reinterpret_cast<float*>(ws + pl.dW), pl.w_mt * pl.w_ks, pl.strips_w,
-                        c1 / c1_pow2, 2.0 / (double(o) * double(d))};
-    gram_reduce_kernel<<<dim3(unsigned(pl.nb), 16, 2), 256, 0, st>>>(ra, rw, pl.nb, s.lambdas);
+    if (pl.fold) calib_backward_kernel<2, 2, 2, 2, false, true><<<works, 256, 0, st>>>(b);
+    else if (pl.big) calib_backward_kernel<4, 2, 2, 4, true, false><<<works, 512, 0, st>>>(b);
+    else calib_backward_kernel<2, 2, 2, 2, false, false><<<works, 256, 0, st>>>(b);
+    auto reduce_side = [&](const Side& x) {
+        return ReduceSide{x.partial, x.sums, x.works / pl.ntn, x.strips, x.c1, x.c2_unit};
+    };
+    if (!pl.fold)
+        gram_reduce_kernel<<<dim3(unsigned(pl.nb), 16, 2), 256, 0, st>>>(reduce_side(b.act), reduce_side(b.wgt), pl.nb, s.lambdas);
     LuGradArgs la{};
     la.lu = s.lu;
-    la.ga = ra.partial;
-    la.ga_lo = ra.dpart;
-    la.gw = rw.partial;
-    la.gw_lo = rw.dpart;
+    la.ga = pl.fold ? b.act.sums : b.act.partial;
+    la.ga_lo = b.act.sums;
+    la.gw = pl.fold ? b.wgt.sums : b.wgt.partial;
+    la.gw_lo = b.wgt.sums;
     la.nb = pl.nb;
     la.nfac = pl.nfac;
     la.grad = s.grad;
@@ -967,7 +1014,8 @@ hipError_t launch_calib_backward(const CalibPlan& pl, const CalibStepArgs& s, in
     la.n_w = double(o) * double(d);
     la.lambdas = s.lambdas;
     la.losses = s.losses;
-    lu_grad_kernel<<<unsigned(pl.nfac + 1), 256, 0, st>>>(la);
+    if (pl.fold) lu_grad_kernel<false><<<unsigned(pl.nfac + 1), 256, 0, st>>>(la);
+    else lu_grad_kernel<true><<<unsigned(pl.nfac + 1), 256, 0, st>>>(la);
     return hipGetLastError();
 }
 

@@ -93,6 +93,14 @@ def test_calib_reference_tiles(R, o, d):
     test_calib_reference_parity(R, o, d)
 
 
+@pytest.mark.parametrize("R,o,d,a", [(1, 1, 3072, 4), (2, 25, 960, 4), (9, 7, 544, 1), (66, 1, 1024, 4), (1, 70, 2048, 2),
+                                     (30, 40, 160, 8)])
+def test_calib_step_of_few_rows_and_features(R, o, d, a):
+    """Shared factors and so few rows and features that the block sums of the products
+    go onto the quantizer's (one strip of it and two), or just do not."""
+    test_calib_step_parity(R, o, d, a, False, "random")
+
+
 @pytest.mark.parametrize("R,o,d,a,per_block,start", CASES)
 def test_calib_step_parity(R, o, d, a, per_block, start):
     nfac = d // 32 if per_block else 1

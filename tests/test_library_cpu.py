@@ -329,6 +329,33 @@ def test_calib_step_noalloc_takes_a_few_rows_of_many_columns(R, o, d, nfac):
     assert st not in (0, INVALID)
 
 
+@pytest.mark.parametrize("R,o,d,a,nfac,bytes_", [
+    # a few rows and features: the block sums are most of it
+    (1, 1, 32, 4, 1, 25600), (1, 1, 3072, 4, 1, 1219584), (2, 25, 960, 4, 1, 501248), (66, 1, 3072, 4, 1, 2525952),
+    (1, 17, 143808, 4, 1, 66974464), (1, 70, 12288, 2, 1, 10266880),
+    (2048, 1024, 1024, 4, 32, 56482560), (18432, 3072, 3072, 4, 96, 1244032000)])
+def test_calib_workspace_size_never_grows(R, o, d, a, nfac, bytes_):
+    """A workspace of the size that the library once asked for stays large enough."""
+    n = ctypes.c_size_t(0)
+    assert kq.lib().kq_calib_workspace_size(R, o, d, a, nfac, ctypes.byref(n)) == 0
+    assert 0 < n.value <= bytes_
+
+
+@pytest.mark.parametrize("R,o,d,nfac,fits", [(2048, 1024, 1024, 32, True), (4096, 1152, 1152, 36, False),
+                                             (1, 17, 143808, 1, True), (1, 17, 144064, 1, True), (1, 17, 144096, 1, False),
+                                             (18432, 3072, 3072, 96, False)])
+def test_calib_step_noalloc_goes_by_the_workspace_size(R, o, d, nfac, fits):
+    """kq_calib_step_noalloc takes exactly the sizes whose kq_calib_workspace_size is at
+    most KQ_CALIB_NOALLOC_MAX_BYTES (its refusal needs no GPU)."""
+    n = ctypes.c_size_t(0)
+    assert kq.lib().kq_calib_workspace_size(R, o, d, 4, nfac, ctypes.byref(n)) == 0
+    assert (n.value <= kq.CALIB_NOALLOC_MAX_BYTES) == fits
+    if not fits:
+        assert kq.lib().kq_calib_step_noalloc(FAKE, R, d, FAKE, o, FAKE, FAKE, 4, nfac, FAKE, FAKE, FAKE, None, None, 0,
+                                              0.0, None) == INVALID
+        assert str(n.value).encode() in kq.lib().kq_last_error_detail()
+
+
 def test_native_marshalling_leaves_other_arguments_to_python():
     """The binding's native part takes plain device tensors only: everything
     else comes back as None and meets the checks in Python."""

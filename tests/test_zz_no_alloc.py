@@ -62,7 +62,8 @@ def _step_both(R, o, d, a, per_block, seed, t):
 
 
 @pytest.mark.parametrize("first,second", [((1024, 1152, 1152, 4, True, 11, 1), (300, 96, 640, 2, True, 12, 3)),
-                                          ((512, 256, 512, 8, False, 13, 2), (40, 24, 64, 4, True, 14, 1))])
+                                          ((512, 256, 512, 8, False, 13, 2), (40, 24, 64, 4, True, 14, 1)),
+                                          ((66, 1, 3072, 4, False, 15, 2), (2, 25, 960, 4, False, 16, 1))])
 def test_noalloc_step_matches_workspace_step(first, second):
     for case in (first, second):
         ref, got = _step_both(*case)
