@@ -59,11 +59,10 @@ struct Opnd {
 // A load straight into LDS (lane l's 16 bytes land at the wave-uniform LDS
 // address + 16 l), as asm: the compiler puts a vmcnt(0) before LDS reads that may
 // alias such a load it knows of, which would drain the stages in flight.  The
-// waits are explicit (wait_stage), the load has no register result, and nothing
-// else in these kernels uses m0.
+// waits are explicit (wait_stage), and the load has no register result.
 __device__ __forceinline__ void lds_dma16(uint32_t lds, uint32_t voff, const uint8_t* base) {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(voff), "s"(base)
-                 : "memory");
+                 : "memory", "m0");
 }
 
 __device__ __forceinline__ void stage_barrier() {

@@ -145,11 +145,10 @@ constexpr int kStages = 4;  // LDS stage buffers: one in use, three in flight
 
 // One such load, as asm: the compiler puts a vmcnt(0) before LDS reads that may
 // alias a load into LDS it knows of, which would drain the stages in flight.
-// The waits are explicit here (wait_stage), the load has no register result,
-// and nothing else in these kernels uses m0.
+// The waits are explicit here (wait_stage), and the load has no register result.
 __device__ __forceinline__ void lds_dma16(uint32_t lds, uint32_t voff, const uint8_t* base) {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(voff), "s"(base)
-                 : "memory");
+                 : "memory", "m0");
 }
 
 __device__ __forceinline__ void stage_barrier() {
