@@ -62,6 +62,10 @@ CASES = [
     (4100, 2100, 64, 4, True, "random"),
     # a residual at most 32 wide on more than 256 tiles of 32 x 32
     (8300, 20, 64, 4, True, "random"),
+    # the residual on 256 x 256 tiles (K past 1536, more than one round of 128 x 128), scales by way of
+    # registers and straight into LDS
+    (3000, 2999, 1568, 4, True, "random"),
+    (3000, 2999, 1664, 8, False, "random"),
 ]
 
 

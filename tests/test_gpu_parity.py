@@ -455,6 +455,18 @@ def test_fwht_row_counts(d):
         assert np.array_equal(host(s_), want[1]) and np.array_equal(host(c), want[0]), (M, d)
 
 
+@pytest.mark.parametrize("M,d", [(4099, 2048), (9001, 2048), (2051, 4096), (4701, 4096), (1027, 8192), (515, 16384), (1301, 16384)])
+def test_fwht_rounds(M, d):
+    """More groups of rows than workgroups stay on the chip (1024 of 256 threads, 512 of 512):
+    two and three rounds, in which a workgroup loads its next rows beside the
+    transform of the last, and a last group that is not whole where a group
+    holds several rows."""
+    X = synth.activations(M, d, "student_t3", seed=75, chan_frac=0.01, chan_factor=40.0)
+    want = oracle.fwht(X, want_y=True)
+    c, s_, y = kq.fwht(dev_bf16(X), want_y=True)
+    assert_exact((host(c), host(s_), host(y)), want, f"fwht M={M} d={d}")
+
+
 def test_hip_graph_replays_match_eager():
     """The hot-path and comparator launches captured into one HIP graph (as the
     benchmark's power-of-two-d table does) and replayed three times, with eager
@@ -1031,10 +1043,26 @@ def test_native_marshalling_matches_python(monkeypatch, given):
         lambda k: kq.calib_step(X, W, Y, lu, lam, a=4, workspace=work, stream=st),
     ]
     native = binding._native()
+    taken = []
+
+    class Recorder:
+        """The native part; every call that it makes is noted."""
+
+        def __getattr__(self, name):
+            def f(*args):
+                r = getattr(native, name)(*args)
+                taken.append(None if r is None else name)
+                return r
+            return f
+
+    names = ["quantize", "quantize_exact", "quantize_packed", "quantize_lu", "smoothquant", "hadamard32", "fwht", "mxfp4",
+             "mxfp4_gemm", "mxfp4_gemm", "calib_step"]
     for i, call in enumerate(calls):
         k = bufs()
-        monkeypatch.setattr(binding, "_native", lambda: native)
+        taken.clear()
+        monkeypatch.setattr(binding, "_native", Recorder)
         got = call(k)
+        assert taken[-1] == names[i] and None not in taken, (i, taken)
         if given and i < 8:
             assert got[0] is k["codes"] and got[1] is k["scales"], i
         monkeypatch.setattr(binding, "_native", _NoNative)
