@@ -320,7 +320,7 @@ struct Side {
 // FOLD: a few rows and features of very many columns, where partial sums of their own
 // would be most of the workspace.
 template <int WM, int WN, int TM, int TN, bool FOLD>
-__device__ __forceinline__ void gram_tile(const f32x16 (&acc)[TM][TN], const Side& s, uint8_t* lds_generic, int64_t slot,
+__device__ __forceinline__ void gram_tile(f32x16 (&acc)[TM][TN], const Side& s, uint8_t* lds_generic, int64_t slot,
                                           int64_t m0, int64_t n0) {
     constexpr int WAVES = WM * WN, BM = 32 * WM * TM, BN = 32 * WN * TN;
     constexpr int RPI = 512 / BN, LPR = 64 / RPI, LOADS = 2 * BM * BN / 1024 / WAVES;
@@ -365,7 +365,13 @@ __device__ __forceinline__ void gram_tile(const f32x16 (&acc)[TM][TN], const Sid
 #pragma unroll
             for (int e = 0; e < 16; ++e) top = fmaxf(top, fabsf(acc[i][j][e]));
     const bool large = __builtin_amdgcn_ballot_w64(top >= 0x1p30f) != 0u;
-    const float before = large ? s.c1_pow2 : 1.0f, after = large ? 1.0f : s.c1_pow2;
+    const float after = large ? 1.0f : s.c1_pow2;
+    if (large) {
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j) acc[i][j] *= s.c1_pow2;
+    }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     stage_barrier();
     f32x16 gram[TN];
@@ -391,7 +397,7 @@ __device__ __forceinline__ void gram_tile(const f32x16 (&acc)[TM][TN], const Sid
                     // accumulator 8 k + u is row 16 k + 8 (u / 4) + 4 h + u % 4
                     const int bit = 16 * k + 8 * (u / 4) + (u % 4);
                     const uint32_t keep = (uint32_t)((int32_t)(bits << (31 - bit)) >> 31);
-                    const float v = __uint_as_float(__float_as_uint(acc[i][j][8 * k + u] * before) & keep);
+                    const float v = __uint_as_float(__float_as_uint(acc[i][j][8 * k + u]) & keep);
                     g[0][u] = (__bf16)v;
                     const float r1 = v - (float)g[0][u];  // exact
                     g[1][u] = (__bf16)r1;
