@@ -5,8 +5,10 @@ kernels of the library.  torch supplies device memory and the current HIP
 stream.  There is no fallback: if the library is missing the first call raises.
 
 The calls that a loop repeats go through _kqbind (csrc/kq_bind.cpp), which makes
-the library call for plain arguments and returns None for all others; those come
-to the checks here, which name what is wrong.
+the library call for plain arguments and returns None for all others (a stream
+object, a subclass, what the library refuses); those come to the checks here,
+which name what is wrong.  A calibration step with an Adam update or without a
+workspace is marshalled here.
 """
 from __future__ import annotations
 

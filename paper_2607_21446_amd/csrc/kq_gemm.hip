@@ -140,7 +140,7 @@ __device__ __forceinline__ void block_squares(double sq, double* red, const Gemm
 // K advances 128 (four 32-blocks) per stage.  Codes and scales go from global
 // memory straight into LDS (global_load_lds: lane l's 16 bytes land at the
 // wave-uniform LDS address + 16 l), three stages ahead, so there is no register
-// staging and no ds_write.
+// staging and no ds_write (scale rows that no such load can take: see DMA_SCALES).
 constexpr int kStages = 4;  // LDS stage buffers: one in use, three in flight
 
 // One such load, as asm: the compiler puts a vmcnt(0) before LDS reads that may
@@ -239,7 +239,8 @@ __device__ __forceinline__ uint4 load_scales16(const uint8_t* p, int nvalid) {
 // The last such load of the last row would pass the end of the array, so it
 // ends there instead and is read at an offset.  Otherwise each thread loads
 // its row's 16 bytes into registers (byte-exact) and parks them in LDS two
-// stages later.
+// stages later; the compiler waits for them with vmcnt(0), which drains the stages in
+// flight once per four stages (the other path never does).
 template <int WN, int WM, int TN, int TM, bool PING, bool DMA_SCALES>
 __device__ __forceinline__ void gemm_tile(const GemmParams& g, typename Tile<WN, WM, TN, TM>::Lds& lds, int64_t nb0,
                                           int64_t mb0, f32x16g (&acc)[TN][TM]) {
@@ -425,7 +426,7 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& g, typename Tile<WN,
 // The tile's accumulators, acc[i][j][4q + e] = C[mb0 + 32 (wm TM + j) + r][nb0 +
 // 32 (wn TN + i) + 8 q + 4 h + e], to C through LDS, so that C (and the bias) is
 // accessed along its rows, 512 bytes at a time, and not in 8- or 16-byte pieces
-// of 32 rows (4608 x 12288 x 3072, bf16 / fp32: 141 / 155 us so, 119 / 137 along rows).
+// of 32 rows (4608 x 12288 x 3072, bf16 / fp32: 141 / 155 us so, 119 / 131 along rows).
 // Rows in LDS are 16 bytes apart from a multiple of 512 (256), so that the 16 rows of a
 // write phase cover all banks.  When a tile of fp32 does not fit, it goes in NP passes of
 // TN / NP of every wave's column tiles.
@@ -747,12 +748,12 @@ __global__ __launch_bounds__(64 * WN * WM) void mxfp4_gemm_pipe_kernel(const Gem
 constexpr int64_t kPipeMaxK = int64_t(1) << 24;
 
 // Tile of a call.  Measured, us (bf16 C, K 512 / 1152 / 3072 / 9600):
-//   32 x 32 split (8 waves)     128 x  512: 3.3 / 3.7 /  6.9 / 10.9; 128 x 128 5.1 / 7.0 / 12.1 / 30.7
-//   32 (M) x 64 (N) split       256 x 1152: 3.9 / 4.3 /  9.4 / 18.6; 32 x 32 3.9 / 4.5 / 11.0 / 22.0
-//   64 x 64 split               512 x 2048: 4.9 / 6.1 / 12.8 / 25.9; 128 x 128 5.4 / 7.3 / 13.1 / 32.4
-//   128 x 128 pipelined         512 x 4096: 5.7 / 7.8 / 13.8 / 32.8; 64 x 64 8.4 / 10.8 / 24.0 / 47.9
-//                              4096 x 2048: 9.5 / 13.5 / 24.3 / 63.8; 256 x 256 11.7 / 16.7 / 27.1 / 64.6
-//   256 x 256 pipelined        3000 x 3000: 12.3 / 16.5 / 26.3 / 64.8; 128 x 128 12.5 / 17.6 / 31.0 / 84.8
+//   32 x 32 split (8 waves)     128 x  512: 3.4 / 3.8 /  7.0 / 11.0; 128 x 128 4.7 / 6.7 / 11.9 / 30.3
+//   32 (M) x 64 (N) split       256 x 1152: 3.9 / 4.4 /  9.2 / 15.3; 32 x 32 3.9 / 4.5 / 10.9 / 19.0
+//   64 x 64 split               512 x 2048: 5.0 / 6.0 / 12.2 / 24.9; 128 x 128 5.0 / 6.9 / 12.0 / 30.7
+//   128 x 128 pipelined         512 x 4096: 5.4 / 7.4 / 12.9 / 32.0; 64 x 64 8.6 / 10.6 / 22.8 / 48.2
+//                              4096 x 2048: 8.4 / 12.1 / 23.9 / 62.5; 256 x 256 11.2 / 15.1 / 25.8 / 63.8
+//   256 x 256 pipelined        3000 x 3000: 11.1 / 15.5 / 25.8 / 63.9; 128 x 128 10.8 / 16.1 / 30.8 / 83.7
 // So the smallest split tile that still gives a CU no more than one workgroup, and
 // past 256 tiles of 64 x 64 the pipelined tile that needs fewer rounds (two 128 x
 // 128 workgroups share a CU and take as long as one of 256 x 256).  But:
@@ -764,15 +765,15 @@ constexpr int64_t kPipeMaxK = int64_t(1) << 24;
 // (onto C 0.72 - 0.95, 0.75 - 0.96, 0.78 - 0.98, 0.83 - 1.04); with twice the rounds 0.83 - 1.10 at
 // 1152, 0.86 - 1.14 at 1536.  For the residual, which moves 8 bytes an element and has the
 // most work besides, at any number of rounds: the calibration step by 256 x 256 and 128 x
-// 128 tiles, us: 9216 x 512 x 2048 167, 149; 6000 x 1024 x 2900 227, 205; 4096 x 1152 x 4608
-// 296, 273; 18432 x 1152 x 3072 630, 616; 8192 x 1536 x 3072 394, 380; 18432 x 3072 x 3072 1365, 1404.
+// 128 tiles, us: 9216 x 512 x 2048 158, 147; 6000 x 1024 x 2900 223, 204; 4096 x 1152 x 4608
+// 271, 259; 18432 x 1152 x 3072 626, 614; 8192 x 1536 x 3072 387, 381; 18432 x 3072 x 3072 1295, 1300.
 // K <= 128, a single stage: 128 x 128 always (0.79 - 1.03).
 //
 // N <= 32 with more than 256 tiles of 32 x 32 (C is four times narrower than a 128 x 128
 // tile): 32 x 32 tiles of two waves, many on a CU.  Not the residual, whose sums of
 // squares have room for one a tile of 64 x 64.  128 x 128 and so, us, K 64 / 480 / 1152 /
-// 3072: 18432 x 32 4.2 / 5.6 / 6.9 / 12.2 and 3.8 / 4.4 / 5.9 / 15.8; 70000 x 8 onto C
-// 11.3 / 14.4 / 19.4 / 33.8 and 6.6 / 7.9 / 13.5 / 33.7.
+// 3072: 18432 x 32 4.2 / 5.5 / 6.8 / 12.2 and 3.8 / 4.3 / 5.7 / 15.6; 70000 x 8 onto C
+// 11.1 / 14.5 / 20.3 / 33.9 and 6.7 / 8.0 / 13.5 / 33.7.
 enum class GemmTile { Thin32, Split32, Split32x64, Split64, Pipe128, Pipe256 };
 
 static GemmTile gemm_tile_of(const GemmParams& g) {
