@@ -360,7 +360,7 @@ kq_status kq_lu_to_factors(const float* abc, int a, int64_t nfac, float* A, floa
  * per-workgroup partial sums.  Small sizes are told more (up to 6.6 R d + 12 R o +
  * 6.6 o d bytes and partial sums, or just above KQ_CALIB_NOALLOC_MAX_BYTES): what
  * exceeds KQ_CALIB_NOALLOC_MAX_BYTES here is what kq_calib_step_noalloc refuses.
- * A workspace sized by an earlier build of the library is large enough.  Same
+ * A workspace sized by an earlier version of the library is large enough.  Same
  * size checks as kq_calib_step.
  */
 kq_status kq_calib_workspace_size(int64_t R, int64_t o, int64_t d, int a, int64_t nfac, size_t* bytes);

@@ -814,7 +814,7 @@ static double backward_cost(const SidePlan& act, const SidePlan& wgt, bool big) 
     return end + (n1 * l1 + n2 * l2) / S;
 }
 
-// The bytes that a workspace may hold at most, so that one sized by an earlier build of the
+// The bytes that a workspace may hold at most, so that one sized by an earlier version of the
 // library is large enough (buffers of 6.6 R d + 12 R o + 6.6 o d bytes, and partial sums
 // of 128-row tiles): what the step itself leaves of them is the budget of its
 // partial sums.  kq_calib_step_noalloc takes the sizes for which this is at most
