@@ -48,6 +48,7 @@ __device__ __forceinline__ i32x8 operand(const Frag& f) {
 // us: 4608 x 3001 x 3072 bf16 54.9 with the quantizer, 40.0 now; 4608 x 3004 x 1152 38.8
 // and 23.5 (3072 columns: 23.1); 4096 x 3001 x 1152 fp32 37.5 and 26.7.
 typedef float f32x4 __attribute__((ext_vector_type(4), aligned(4)));
+typedef uint32_t u32b __attribute__((aligned(2)));
 typedef uint32_t u32x2b __attribute__((ext_vector_type(2), aligned(2)));
 typedef uint32_t u32x4b __attribute__((ext_vector_type(4), aligned(2)));
 
@@ -542,13 +543,13 @@ __device__ __forceinline__ void store_tile(const GemmParams& g, uint8_t* lds, in
 #pragma unroll
             for (int k = 0; k < CH; ++k) {
                 if (trow + k * STEP > last) break;
-                if (BF16) {
+                if (BF16) {  // 1 to 7 values, as four, two and one
                     const uint4 v = *reinterpret_cast<const uint4*>(from + k * STEP * RS);
-                    const uint32_t w[4] = {v.x, v.y, v.z, v.w};
                     uint16_t* const c = g.C16 + at + k * STEP * g.ldc_out;
-#pragma unroll
-                    for (int e = 0; e < 7; ++e)
-                        if (e <= left) c[e] = (uint16_t)(w[e / 2] >> (16 * (e & 1)));
+                    const int n = left + 1;
+                    if (n & 4) *reinterpret_cast<u32x2b*>(c) = u32x2b{v.x, v.y};
+                    if (n & 2) *reinterpret_cast<u32b*>(c + (n & 4)) = n & 4 ? v.z : v.x;
+                    if (n & 1) c[n & 6] = (uint16_t)(n & 4 ? (n & 2 ? v.w : v.z) : (n & 2 ? v.y : v.x));
                 } else {
                     const float4 f = value(k);
                     float* const c = g.C + at + k * STEP * g.ldc_out;

@@ -705,6 +705,13 @@ def test_mxfp4_gemm_tile_rule(M, N, K):
     test_mxfp4_gemm_k_tails(M, N, K, 0)
 
 
+@pytest.mark.parametrize("tail", range(1, 8))
+def test_mxfp4_gemm_row_ends(tail):
+    """The last 1 to 7 columns of a row of C on the pipelined tile: all of them and
+    nothing past them, at an odd start (in 16 bits as four, two and one)."""
+    test_mxfp4_gemm_c_at_element_alignment(1025, 1024 + tail, 1)
+
+
 @pytest.mark.parametrize("M,N", [(1, 1), (33, 67), (250, 1251), (700, 1301), (1025, 1153), (2950, 3101)])
 @pytest.mark.parametrize("off", [1, 3])
 def test_mxfp4_gemm_c_at_element_alignment(M, N, off):
