@@ -32,6 +32,7 @@
 
 #include "kq_calib.h"
 #include "kq_kernels.h"
+#include "kq_lds.h"
 #include "kroquant.h"
 
 namespace kq {
@@ -55,21 +56,6 @@ struct Opnd {
     const uint8_t* p;
     int64_t rows, cols, ld;  // ld in bytes
 };
-
-// A load straight into LDS (lane l's 16 bytes land at the wave-uniform LDS
-// address + 16 l), as asm: the compiler puts a vmcnt(0) before LDS reads that may
-// alias such a load it knows of, which would drain the stages in flight.  The
-// waits are explicit (wait_stage), and the load has no register result.
-__device__ __forceinline__ void lds_dma16(uint32_t lds, uint32_t voff, const uint8_t* base) {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(voff), "s"(base)
-                 : "memory", "m0");
-}
-
-__device__ __forceinline__ void stage_barrier() {
-    __builtin_amdgcn_sched_barrier(0);
-    asm volatile("s_barrier" ::: "memory");
-    __builtin_amdgcn_sched_barrier(0);
-}
 
 // Until only this wave's LOADS loads of a later stage (if there is one) are outstanding.
 template <int LOADS>

@@ -22,6 +22,7 @@
 #include <type_traits>
 
 #include "kq_kernels.h"
+#include "kq_lds.h"
 
 namespace kq {
 
@@ -143,20 +144,6 @@ __device__ __forceinline__ void block_squares(double sq, double* red, const Gemm
 // wave-uniform LDS address + 16 l), three stages ahead, so there is no register
 // staging and no ds_write (scale rows that no such load can take: see DMA_SCALES).
 constexpr int kStages = 4;  // LDS stage buffers: one in use, three in flight
-
-// One such load, as asm: the compiler puts a vmcnt(0) before LDS reads that may
-// alias a load into LDS it knows of, which would drain the stages in flight.
-// The waits are explicit here (wait_stage), and the load has no register result.
-__device__ __forceinline__ void lds_dma16(uint32_t lds, uint32_t voff, const uint8_t* base) {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(voff), "s"(base)
-                 : "memory", "m0");
-}
-
-__device__ __forceinline__ void stage_barrier() {
-    __builtin_amdgcn_sched_barrier(0);
-    asm volatile("s_barrier" ::: "memory");
-    __builtin_amdgcn_sched_barrier(0);
-}
 
 // Until at most 4 * later code loads of this wave are outstanding.
 __device__ __forceinline__ void wait_stage(int later) {
